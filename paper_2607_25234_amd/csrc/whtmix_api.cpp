@@ -633,12 +633,18 @@ int module_backward_impl(const void *x, const void *w_in, int gain_kind, const f
         m.events[i] = options ? static_cast<hipEvent_t>(options->events[i]) : nullptr;
     // workspace: Z, Z', dZ'; packed weights; weight-gradient partials; the
     // mixer's forward and backward workspaces
+    // (with the weight gradients inside the fused backward's last pass, no Z,
+    // Z', dZ' and no forward workspace)
     const int64_t rows = B * N;
-    const int64_t zb = align256(rows * C * 4);
+    m.tiles = whtmix::module_backward_fused_call(m) && c.K <= 25 &&
+              whtmix::wgrad_tiles_shape(whtmix::module_split(c.K).A, cbits);
+    const int64_t zb = m.tiles ? 0 : align256(rows * C * 4);
     const int64_t pk = align256((int64_t)(3 * wb));
     const whtmix::WgradPlan wp = whtmix::wgrad_plan((uint64_t)rows, cbits);
-    const int64_t part = align256((int64_t)wp.partial_floats(cbits) * 4);
-    const int64_t mix = align256(c.ws_bytes);
+    const int64_t part =
+        m.tiles ? align256(2 * (int64_t)whtmix::wgrad_tiles_parts(c.K, cbits, B, m.nvalid) * C * C * 4)
+                : align256((int64_t)wp.partial_floats(cbits) * 4);
+    const int64_t mix = m.tiles ? 0 : align256(c.ws_bytes);
     const whtmix::BackwardLayout lay = whtmix::backward_layout(c.plan, c.K, B, C, sep);
     const int64_t bwd = align256((int64_t)(lay.floats * 4));
     std::lock_guard<std::mutex> lock(g_ws_mutex);

@@ -116,10 +116,65 @@ inline bool module_backward_fused(int plan, int cbits, int dtype, int K)
     return dtype == DTYPE_BF16 && cbits == kPairModuleCbits && K >= 26 && K <= 28;
 }
 
+// Weight gradients inside the last pass (whtmix_wgrad.hip), for the fused
+// backward's tiles of 2^A elements and C = 2^cbits channels: the product
+// layout needs three token bits in a lane's registers beside the channel
+// strips its wave holds, and every token bit below layout A-5 in registers.
+// That is every fused shape but C = 128 on 2^11 tiles (K = 16, 17) and
+// C = 16 on 2^15 tiles (K = 24, 25).
+constexpr bool wgrad_tiles_shape(int A, int cbits)
+{
+    const int tw = A - 11, sb = cbits - 4;
+    const int rt = 5 - (sb > tw ? sb - tw : 0);
+    return rt >= 3 && A - 5 - cbits >= 0 && A - 5 - cbits <= rt;
+}
+
+// Outer tiles of one slice that hold real rows (nvalid = N * C).
+inline uint32_t wgrad_live_tiles(int K, uint32_t nvalid)
+{
+    const Split sp = module_split(K);
+    return (uint32_t)(((uint64_t)nvalid + (uint64_t(1) << sp.A) - 1) >> sp.A);
+}
+
+// Workgroups (and partial sums) per weight gradient: two workgroups per CU
+// over both, one where a workgroup has 1024 threads or its waves hold more
+// than one strip of channels (over 128 registers), and no more than there
+// are tile groups.  Each adds up its tile groups in registers, so its
+// partial C x C matrix is written once.
+inline uint32_t wgrad_tiles_parts(int K, int cbits, int64_t B, uint32_t nvalid)
+{
+    const Split sp = module_split(K);
+    const int e = sp.A < 14 ? 14 - sp.A : 0;   // log2 of tiles per group
+    const uint64_t groups =
+        ((uint64_t)B * wgrad_live_tiles(K, nvalid) + (uint64_t(1) << e) - 1) >> e;
+    const uint64_t most = sp.A == 15 || cbits - 4 > sp.A - 11 ? 128 : 256;
+    return (uint32_t)(groups < most ? groups : most);
+}
+
+struct WgradTilesArgs {
+    const float *wsx;       // middle pass's output of Z and of dZ'
+    const float *wsd;
+    const void *x;
+    const void *dy;
+    float *part;            // 2 * wgrad_tiles_parts * C * C floats
+    float *dw_in;
+    float *dw_out;
+    int cbits;
+    int64_t B;              // > 0
+    int K;                  // 12 .. 25, wgrad_tiles_shape(module_split(K).A, cbits)
+    uint32_t nvalid;        // N * C
+    int dtype;
+    hipStream_t stream;
+};
+
+hipError_t launch_wgrad_tiles(const WgradTilesArgs &a);
+
 // A validated backward call of the block.  Workspace pieces (floats unless
-// noted): z, zp, dzp [B*N*C] (Z = X W_in, Z' = mixer(Z), dZ' then dZ);
+// noted): z, zp, dzp [B*N*C] (Z = X W_in, Z' = mixer(Z), dZ' then dZ; unused
+// and absent with `tiles`);
 // wpack: W_in, W_out^T and W_in^T packed (3*C*C elements of the dtype);
-// wpart: wgrad_plan(B*N, cbits).chunks * C*C partial sums; mix_ws: the
+// wpart: the weight gradients' partial sums (wgrad_plan, or
+// wgrad_tiles_parts with `tiles`); mix_ws: the
 // THREE_PASS workspace (B * 2^K, else none); bwd_ws: the mixer backward's
 // workspace (backward_layout).
 struct ModuleBackwardArgs {
@@ -148,6 +203,7 @@ struct ModuleBackwardArgs {
                             // dZ', dW_out, [2] the mixer's gradient, [3] dX and dW_in;
                             // fused, [1] the transforms of Z and dZ' and dG, [2] Z'
                             // and dW_out, [3] dX and dW_in
+    bool tiles;             // fused, with the weight gradients inside the last pass
     float *z;
     float *zp;
     float *dzp;
@@ -156,6 +212,16 @@ struct ModuleBackwardArgs {
     float *mix_ws;
     float *bwd_ws;
 };
+
+// Whether this call runs the fused backward: the shape (above), a requested
+// gain gradient, and a first launch of 2*B*2^K/32 work-items (a 32-bit grid).
+inline bool module_backward_fused_call(const ModuleBackwardArgs &m)
+{
+    const bool want_dg = m.gain_kind == GAIN_LOG_SEPARABLE ? (m.dgt != nullptr)
+                                                           : (m.dgain != nullptr);
+    return want_dg && m.B > 0 && ((uint64_t)m.B << m.K) / 16u <= 0xffffffffull &&
+           module_backward_fused(m.plan, m.cbits, m.dtype, m.K);
+}
 
 hipError_t launch_module_backward(const ModuleBackwardArgs &m);
 

@@ -2129,10 +2129,12 @@ hipError_t wgrad(const Ta *a, const Tb *b, float *part, float *out, uint32_t row
 //   OUTER_FWD of Z = X W_in and dZ' = dY W_out^T, matrix-core prologues, one
 //   launch -> the backward's middle phase: dG, and both Z and dZ' through the
 //   gain up to their last pass, in place in wsx and wsd                 [1]
-//   -> OUTER_INV of wsx -> Z' (float32); dW_out = Z'^T dY                 [2]
-//   -> OUTER_INV of wsd with the epilogue: dZ (float32) and dX = dZ W_in^T;
-//      dW_in = X^T dZ                                                     [3]
-// Z and dZ' never reach memory: they exist only as the outer transforms.
+//   -> dW_out = Z'^T dY and dW_in = X^T dZ from wsx and wsd, whose token bits
+//      are finished in the same kernel (whtmix_wgrad.hip)                 [2]
+//   -> OUTER_INV of wsd with the epilogue: dX = dZ W_in^T                  [3]
+// Z, dZ', Z' and dZ never reach memory: they exist only as partial transforms.
+// The two shapes wgrad_tiles_shape leaves out store Z' (OUTER_INV of wsx) and
+// dZ (beside dX) in float32 for wgrad_mfma_kernel instead.
 template <typename T, int K, int CB>
 hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
 {
@@ -2141,7 +2143,7 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
     static_assert(A == three_pass_split(K).A && R == three_pass_split(K).R,
                   "the backward's middle phase runs the mixer's split");
     const hipStream_t st = m.stream;
-    const uint32_t rows = (uint32_t)(((uint64_t)m.B * m.nvalid) >> CB);
+    [[maybe_unused]] const uint32_t rows = (uint32_t)(((uint64_t)m.B * m.nvalid) >> CB);
     const uint32_t CC = 1u << (2 * CB);
     const T *x = static_cast<const T *>(m.x);
     const T *dy = static_cast<const T *>(m.dy);
@@ -2186,15 +2188,41 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
     g.stream = st;
     if ((e = launch_backward_middle(g)) != hipSuccess) return e;
     if ((e = record(m.events[1], st)) != hipSuccess) return e;
-    if ((e = launch_outer_inv<K, float>(wsx, m.zp, m.B, m.nvalid, st)) != hipSuccess) return e;
-    if ((e = wgrad<float, T>(m.zp, dy, m.wpart, m.dw_out, rows, CB, st)) != hipSuccess) return e;
-    if ((e = record(m.events[2], st)) != hipSuccess) return e;
-    // dZ (float32, for dW_in) and dX = dZ W_in^T from one pass over wsd
-    hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true>),
-                       dim3((uint32_t)(m.B << HB)), dim3(1u << (A - VB)), 0, st, wsd, p_in_te,
-                       static_cast<T *>(m.dx), m.dzp, m.nvalid);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = wgrad<T, float>(x, m.dzp, m.wpart, m.dw_in, rows, CB, st)) != hipSuccess) return e;
+    T *dx = static_cast<T *>(m.dx);
+    const dim3 grid((uint32_t)(m.B << HB)), block(1u << (A - VB));
+    if constexpr (wgrad_tiles_shape(A, CB)) {
+        WgradTilesArgs w{};
+        w.wsx = wsx;
+        w.wsd = wsd;
+        w.x = x;
+        w.dy = dy;
+        w.part = m.wpart;
+        w.dw_in = m.dw_in;
+        w.dw_out = m.dw_out;
+        w.cbits = CB;
+        w.B = m.B;
+        w.K = K;
+        w.nvalid = m.nvalid;
+        w.dtype = m.dtype;
+        w.stream = st;
+        if ((e = launch_wgrad_tiles(w)) != hipSuccess) return e;
+        if ((e = record(m.events[2], st)) != hipSuccess) return e;
+        // dX = dZ W_in^T last: dX may be dY itself
+        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB>), grid, block, 0, st, wsd,
+                           p_in_te, dx, nullptr, m.nvalid);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
+        if ((e = launch_outer_inv<K, float>(wsx, m.zp, m.B, m.nvalid, st)) != hipSuccess) return e;
+        if ((e = wgrad<float, T>(m.zp, dy, m.wpart, m.dw_out, rows, CB, st)) != hipSuccess)
+            return e;
+        if ((e = record(m.events[2], st)) != hipSuccess) return e;
+        // dZ (float32, for dW_in) and dX = dZ W_in^T from one pass over wsd
+        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true>), grid, block, 0, st,
+                           wsd, p_in_te, dx, m.dzp, m.nvalid);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = wgrad<T, float>(x, m.dzp, m.wpart, m.dw_in, rows, CB, st)) != hipSuccess)
+            return e;
+    }
     return record(m.events[3], st);
 }
 
@@ -2278,10 +2306,7 @@ hipError_t module_backward_fused_cb(const ModuleBackwardArgs &m)
 template <typename T>
 hipError_t module_backward(const ModuleBackwardArgs &m)
 {
-    const bool want_dg = m.gain_kind == GAIN_LOG_SEPARABLE ? (m.dgt != nullptr)
-                                                           : (m.dgain != nullptr);
-    if (want_dg && m.B > 0 && ((uint64_t)m.B << m.K) / 16u <= 0xffffffffull &&
-        module_backward_fused(m.plan, m.cbits, m.dtype, m.K)) {
+    if (module_backward_fused_call(m)) {
         switch (m.cbits) {
         case 4: return module_backward_fused_cb<T, 4>(m);
         case 5: return module_backward_fused_cb<T, 5>(m);
