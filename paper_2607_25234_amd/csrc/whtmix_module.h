@@ -136,18 +136,44 @@ inline uint32_t wgrad_live_tiles(int K, uint32_t nvalid)
     return (uint32_t)(((uint64_t)nvalid + (uint64_t(1) << sp.A) - 1) >> sp.A);
 }
 
-// Workgroups (and partial sums) per weight gradient: two workgroups per CU
-// over both, one where a workgroup has 1024 threads or its waves hold more
-// than one strip of channels (over 128 registers), and no more than there
-// are tile groups.  Each adds up its tile groups in registers, so its
-// partial C x C matrix is written once.
-inline uint32_t wgrad_tiles_parts(int K, int cbits, int64_t B, uint32_t nvalid)
+// The form without an exchange: waves that hold channel strips only, with
+// 2^6 values per lane at most.
+constexpr bool wgrad_direct_shape(int A, int cbits)
+{
+    const int tw = A - 11, sb = cbits - 4;
+    return wgrad_tiles_shape(A, cbits) && A - 6 - (sb < tw ? sb : tw) <= 6;
+}
+
+// log2 of the outer tiles a workgroup takes at a time (Wd::E, Wg::E).
+constexpr int wgrad_group_bits(int A, int cbits)
+{
+    const int tw = A - 11, sb = cbits - 4, sw = sb < tw ? sb : tw;
+    if (wgrad_direct_shape(A, cbits))
+        return (A - 6 - sw > 5 && sw < 3 ? 2 : 3) - sw;
+    return (tw > 3 ? tw : 3) - tw;
+}
+
+// Workgroups (and partial sums) per weight gradient: as many as fit the CUs
+// over both (two 8-wave ones; three 4-wave ones with 64 values per lane; one
+// with 1024 threads or over 128 registers: several strips of channels per
+// wave, float32 at C = 128), and no more than there are tile groups.  Each adds up its tile
+// groups in registers, so its partial C x C matrix is written once.
+inline uint32_t wgrad_tiles_parts(int K, int cbits, int dtype, int64_t B, uint32_t nvalid)
 {
     const Split sp = module_split(K);
-    const int e = sp.A < 14 ? 14 - sp.A : 0;   // log2 of tiles per group
+    const int e = wgrad_group_bits(sp.A, cbits);
+    const int tw = sp.A - 11, sb = cbits - 4, sw = sb < tw ? sb : tw;
     const uint64_t groups =
         ((uint64_t)B * wgrad_live_tiles(K, nvalid) + (uint64_t(1) << e) - 1) >> e;
-    const uint64_t most = sp.A == 15 || cbits - 4 > sp.A - 11 ? 128 : 256;
+    uint64_t most = sb > tw ? 128 : 256;
+    if (wgrad_direct_shape(sp.A, cbits)) {
+        if (sp.A - 6 - sw > 5)
+            most = sw < 3 ? 384 : 128;
+        else if (dtype == DTYPE_F32 && cbits == 7)
+            most = 128;
+    } else if (sp.A == 15) {
+        most = 128;
+    }
     return (uint32_t)(groups < most ? groups : most);
 }
 

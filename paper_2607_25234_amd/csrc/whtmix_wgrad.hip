@@ -18,13 +18,14 @@
 // the splits and the products.
 //
 // Products (float32 accumulation), Z' / dZ rows against dY / X columns:
-//   v_mfma_f32_16x16x32_bf16 on three-term bf16 splits of the float operand
-//   (residual below 2^-27 of each value) against bf16 dY / X, exact, or
-//   against the same split of float32 dY / X: the six products down to 2^-25
-//   of the largest, below float32's own rounding, at 2.7 times the rate of the
-//   fp32 instruction.
+//   v_mfma_f32_16x16x32_bf16 on three-term bf16 splits of the float operand,
+//   against bf16 dY / X (both exact) or against the same split of float32 dY /
+//   X: the six products down to 2^-25 of the largest, below float32's own
+//   rounding, at 2.7 times the rate of the fp32 instruction.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "whtmix_launch.h"
 #include "whtmix_module.h"
@@ -37,10 +38,28 @@ namespace {
 using namespace tile;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A staged plane of dY / X: [channel][2^NB chunks of 8 tokens], in 16-byte
+// units.  Column j of the product's column block n is channel NNB j + n, so
+// that the chunks of a channel can be permuted by j alone: the 16 lanes of an
+// operand read (one chunk, one n) fall on different 16-byte bank groups and
+// n is a constant offset; the transposing writes, whose lanes hold different
+// j, spread the same way.  Rows of fewer than 16 chunks are shifted besides.
+template <int NB, int CB>
+struct Plane {
+    static constexpr int NNB = 1 << (CB - 4);
+    __host__ __device__ static constexpr uint32_t at(uint32_t j, uint32_t n, uint32_t chunk)
+    {
+        constexpr uint32_t mask = NB < 4 ? (1u << NB) - 1u : 15u;
+        const uint32_t row = ((j << (CB - 4)) | n) << NB;
+        return row + (NB < 4 ? ((j >> NB) << NB) : 0u) + (chunk ^ (j & mask));
+    }
+    static constexpr uint32_t UNITS =
+        (16u << (CB - 4 + NB)) + (NB < 4 ? ((15u >> NB) << NB) : 0u);
+};
 
 // How a 2^A tile of C = 2^CB channels lies in the waves for the products: lane
 // 16 q + i of the MFMA operand holds channel 16 strip + i and, per k step,
@@ -88,7 +107,7 @@ struct Wg {
     template <typename T>
     static constexpr int chunk_bits() { return rounds<T>() == 1 ? NCHB : NCHB - 1; }
     template <typename T>
-    static constexpr uint32_t plane_bytes() { return (2u << A) / rounds<T>(); }
+    static constexpr uint32_t plane_bytes() { return 16u * Plane<chunk_bits<T>(), CB>::UNITS; }
     template <typename T>
     static constexpr uint32_t xwords()
     {
@@ -108,18 +127,6 @@ struct Wg {
         const uint32_t cc = TEAMS > 1 ? (uint32_t)C * C : 0u;   // team sums at the end
         return w > cc ? w : cc;
     }
-    // Chunk permutation of a plane with 2^NB chunks per channel: the 16 lanes
-    // of an operand read (consecutive channels, one chunk) and, from 16 chunks,
-    // of a transposing write (every eighth channel) fall on different 16-byte
-    // bank groups.
-    // Bitwise linear: swz(a | b) = swz(a) ^ swz(b) for disjoint a, b.
-    template <int NB>
-    __host__ __device__ static constexpr uint32_t swz(uint32_t c)
-    {
-        constexpr int sh = NB < 4 ? 4 - NB : 0;
-        constexpr uint32_t mask = NB < 4 ? (1u << NB) - 1u : 15u;
-        return ((c >> sh) ^ (c >> 3)) & mask;
-    }
     __device__ static uint32_t base(uint32_t t)   // thread t of the tile
     {
         const uint32_t lane = t & 63u, w = t >> 6;
@@ -132,18 +139,170 @@ struct Wg {
     }
 };
 
-// Three-term bf16 split of eight floats: v = hi + mid + lo + d, each term the
-// nearest bf16 of what the previous ones leave, |d| <= 2^-27 |v|.
+// The high halves of two words: two bf16, the first in the low half.
+__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b)   // round to nearest even
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
+}
+__device__ __forceinline__ float as_f32(uint32_t v) { return __builtin_bit_cast(float, v); }
+__device__ __forceinline__ uint32_t as_u32(float v) { return __builtin_bit_cast(uint32_t, v); }
+
+// Three-term bf16 split of two floats, v = hi + mid + lo.
+// EXACT: each term the leading 8 bits of what is left, so 24 bits are split
+// without residue (the terms have v's sign and shrink by 2^-7 only).
+// Otherwise each term is the nearest bf16 of what is left: |mid| <= 2^-8 |v|,
+// |lo| <= 2^-17 |v|, of either sign, which the products dropped from float32
+// times float32 rely on.
+template <bool EXACT>
+__device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, uint32_t &mid,
+                                            uint32_t &lo)
+{
+    if constexpr (EXACT) {
+        const float r0 = z0 - as_f32(as_u32(z0) & 0xffff0000u);
+        const float r1 = z1 - as_f32(as_u32(z1) & 0xffff0000u);
+        hi = high_halves(as_u32(z0), as_u32(z1));
+        const float s0 = r0 - as_f32(as_u32(r0) & 0xffff0000u);
+        const float s1 = r1 - as_f32(as_u32(r1) & 0xffff0000u);
+        mid = high_halves(as_u32(r0), as_u32(r1));
+        lo = high_halves(as_u32(s0), as_u32(s1));
+    } else {
+        hi = cvt2_bf16(z0, z1);
+        const float r0 = z0 - as_f32(hi << 16), r1 = z1 - as_f32(hi & 0xffff0000u);
+        mid = cvt2_bf16(r0, r1);
+        lo = cvt2_bf16(r0 - as_f32(mid << 16), r1 - as_f32(mid & 0xffff0000u));
+    }
+}
+
+template <bool EXACT>
 __device__ __forceinline__ void split3(const float (&z)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
 {
+    u32x4 h, m, l;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const __bf16 h = (__bf16)z[e];
-        const float r1 = z[e] - (float)h;
-        const __bf16 m = (__bf16)r1;
-        hi[e] = h;
-        mid[e] = m;
-        lo[e] = (__bf16)(r1 - (float)m);
+    for (int e = 0; e < 4; ++e) {
+        uint32_t a, b, c;
+        split3_pair<EXACT>(z[2 * e], z[2 * e + 1], a, b, c);
+        h[e] = a;
+        m[e] = b;
+        l[e] = c;
+    }
+    hi = __builtin_bit_cast(bf16x8, h);
+    mid = __builtin_bit_cast(bf16x8, m);
+    lo = __builtin_bit_cast(bf16x8, l);
+}
+
+// acc += a b over k steps [s0, s1) of a round (a: the lane's float operand, b:
+// the staged planes; rs0 the round's first step).  Steps go in groups whose
+// split operand takes 48 registers, the registers of 32 values and a half.
+// Each group's sum is formed from zero, the leading product apart from the
+// others, and added to the running sum in float32: a chain of accumulations
+// in the matrix unit rounds at every step at the size of the running sum,
+// which measured up to twice the error of the sums it replaces.
+template <typename T, int CB, int NB, int RT, int SR, int S0, int S1, int NS, int NNB, int VV>
+__device__ __forceinline__ void multiply(f32x4 (&acc)[NS][NNB], const float (&v)[VV],
+                                         const float *region, uint32_t j, uint32_t chunk0)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr uint32_t PLANE = Plane<NB, CB>::UNITS;
+    constexpr int GS = S1 - S0 < 4 / NS ? S1 - S0 : 4 / NS;
+    static_assert(GS >= 1 && (S1 - S0) % GS == 0, "whole groups of k steps");
+    const bf16x8 *xb = reinterpret_cast<const bf16x8 *>(region);
+#pragma unroll
+    for (int s0 = S0; s0 < S1; s0 += GS) {
+        bf16x8 a0[GS][NS], a1[GS][NS], a2[GS][NS];
+        const bf16x8 *col[GS];
+#pragma unroll
+        for (int g = 0; g < GS; ++g) {
+            col[g] = xb + Plane<NB, CB>::at(j, 0, chunk0 | (uint32_t)(s0 - S0 + g));
+#pragma unroll
+            for (int sr = 0; sr < NS; ++sr) {
+                float z[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    z[e] = v[sr | ((8 * (s0 + g) + e) << SR)];
+                split3<!F32>(z, a0[g][sr], a1[g][sr], a2[g][sr]);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < NNB; ++n) {
+            f32x4 lead[NS], rest[NS];
+#pragma unroll
+            for (int sr = 0; sr < NS; ++sr)
+                lead[sr] = rest[sr] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int g = 0; g < GS; ++g) {
+                const bf16x8 b0 = col[g][n << NB];
+                bf16x8 b1, b2;
+                if constexpr (F32) {
+                    b1 = col[g][(n << NB) + PLANE];
+                    b2 = col[g][(n << NB) + 2u * PLANE];
+                }
+#pragma unroll
+                for (int sr = 0; sr < NS; ++sr) {
+                    f32x4 d = rest[sr];
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[g][sr], b0, d, 0, 0, 0);
+                    if constexpr (F32) {
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[g][sr], b2, d, 0, 0, 0);
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[g][sr], b1, d, 0, 0, 0);
+                    }
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[g][sr], b0, d, 0, 0, 0);
+                    if constexpr (F32)
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[g][sr], b1, d, 0, 0, 0);
+                    rest[sr] = d;
+                    lead[sr] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[g][sr], b0, lead[sr], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int sr = 0; sr < NS; ++sr)
+                acc[sr][n] += lead[sr] + rest[sr];
+            __builtin_amdgcn_sched_barrier(0);   // few operand reads in registers at a time
+        }
+    }
+}
+
+// The workgroup's sums: lane 16 q + j holds rows a = 16 strip + 4 q + [0, 4) of
+// column b = NNB j + n, strip = strip0 | sr << SW.  The teams' sums are added
+// in team order through LDS and stored to part[blockIdx.x][b][a].
+template <int C, int NS, int NNB, int SW, int CB>
+__device__ __forceinline__ void store_sums(f32x4 (&acc)[NS][NNB], float *lds,
+                                           float *__restrict__ part, uint32_t team,
+                                           uint32_t teams, uint32_t strip0, uint32_t lane)
+{
+    const uint32_t j = lane & 15u, q = lane >> 4;
+    const auto at = [&](int sr, int n) {
+        return (((uint32_t)NNB * j + n) << CB) + 16u * (strip0 | ((uint32_t)sr << SW)) + 4u * q;
+    };
+    for (uint32_t k = 1; k < teams; ++k) {
+        __syncthreads();
+        if (team == k) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int n = 0; n < NNB; ++n)
+                    *reinterpret_cast<f32x4 *>(lds + at(s, n)) = acc[s][n];
+        }
+        __syncthreads();
+        if (team == 0) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int n = 0; n < NNB; ++n)
+                    acc[s][n] += *reinterpret_cast<const f32x4 *>(lds + at(s, n));
+        }
+    }
+    if (team == 0) {
+        float *out = part + ((size_t)blockIdx.x << (2 * CB));
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int n = 0; n < NNB; ++n)
+                *reinterpret_cast<f32x4 *>(out + at(s, n)) = acc[s][n];
     }
 }
 
@@ -178,8 +337,56 @@ __device__ __forceinline__ void load_x(u32x4 (&xr)[V * sizeof(T) / 16], const T 
     }
 }
 
-// Round h of the staged tile: 8-byte writes of four tokens of a channel
-// (float32 in one round: both halves).
+// Transposing writes of a piece group (channels 2^LV cg + [0, 2^LV) of the
+// four tokens 4 quad + i, LV = 3 for bf16, 2 for float32): 8 bytes of four
+// tokens per channel, into the three planes of the split for float32.
+template <int NB, int CB, typename T>
+__device__ __forceinline__ void stage_quad(float *lds, const u32x4 *x, uint32_t cg, uint32_t quad)
+{
+    constexpr int LV = sizeof(T) == 2 ? 3 : 2, NNB = 1 << (CB - 4);
+    constexpr uint32_t PLANE = 16u * Plane<NB, CB>::UNITS;
+    char *const base = reinterpret_cast<char *>(lds) + 8u * (quad & 1u);
+#pragma unroll
+    for (uint32_t i = 0; i < (1u << LV); ++i) {
+        // channel 2^LV cg + i = NNB j + n
+        uint32_t j, n;
+        if constexpr (NNB >= (1 << LV)) {
+            j = cg / (NNB >> LV);
+            n = ((cg & ((NNB >> LV) - 1u)) << LV) + i;
+        } else {
+            j = cg * ((1u << LV) / NNB) + i / NNB;
+            n = i % NNB;
+        }
+        char *d = base + 16u * (Plane<NB, CB>::at(j, 0, quad >> 1) + (n << NB));
+        if constexpr (sizeof(T) == 2) {
+            const uint32_t w = i >> 1;
+            u32x2 o;
+            if (i & 1u) {
+                o[0] = high_halves(x[0][w], x[1][w]);
+                o[1] = high_halves(x[2][w], x[3][w]);
+            } else {
+                o[0] = __builtin_amdgcn_perm(x[1][w], x[0][w], 0x05040100u);
+                o[1] = __builtin_amdgcn_perm(x[3][w], x[2][w], 0x05040100u);
+            }
+            *reinterpret_cast<u32x2 *>(d) = o;
+        } else {
+            u32x2 p0, p1, p2;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                uint32_t a, b, c;
+                split3_pair<false>(as_f32(x[2 * k][i]), as_f32(x[2 * k + 1][i]), a, b, c);
+                p0[k] = a;
+                p1[k] = b;
+                p2[k] = c;
+            }
+            *reinterpret_cast<u32x2 *>(d) = p0;
+            *reinterpret_cast<u32x2 *>(d + PLANE) = p1;
+            *reinterpret_cast<u32x2 *>(d + 2u * PLANE) = p2;
+        }
+    }
+}
+
+// Round h of the staged tile (float32 in one round: both halves).
 template <int A, int CB, typename T>
 __device__ __forceinline__ void stage_x(float *lds, const u32x4 (&xr)[V * sizeof(T) / 16],
                                         uint32_t t, [[maybe_unused]] int h)
@@ -188,58 +395,15 @@ __device__ __forceinline__ void stage_x(float *lds, const u32x4 (&xr)[V * sizeof
     constexpr int NB = W::template chunk_bits<T>();
     constexpr int LV = sizeof(T) == 2 ? 3 : 2;
     const uint32_t cg = t & ((1u << (CB - LV)) - 1u), u = t >> (CB - LV);
-    char *const base = reinterpret_cast<char *>(lds);
     if constexpr (sizeof(T) == 2) {
+        stage_quad<NB, CB, T>(lds, xr, cg, u);
+    } else if constexpr (W::template rounds<T>() == 1) {
+        // u gets its missing bit back (RT = 3: bit 0)
 #pragma unroll
-        for (uint32_t i = 0; i < 8; ++i) {
-            const uint32_t w = i >> 1;
-            u32x2 d;
-            if (i & 1u) {
-                d[0] = (xr[0][w] >> 16) | (xr[1][w] & 0xffff0000u);
-                d[1] = (xr[2][w] >> 16) | (xr[3][w] & 0xffff0000u);
-            } else {
-                d[0] = (xr[0][w] & 0xffffu) | (xr[1][w] << 16);
-                d[1] = (xr[2][w] & 0xffffu) | (xr[3][w] << 16);
-            }
-            *reinterpret_cast<u32x2 *>(
-                base + 16u * ((cg << (NB + 3)) + (i << NB) +
-                              (((u >> 1) ^ W::template swz<NB>(8u * cg)) ^ W::template swz<NB>(i))) +
-                8u * (u & 1u)) = d;
-        }
+        for (uint32_t hh = 0; hh < 2; ++hh)
+            stage_quad<NB, CB, T>(lds, xr + 4 * hh, cg, (u << 1) | hh);
     } else {
-        constexpr uint32_t PLANE = W::template plane_bytes<T>();
-        constexpr int ROUNDS = W::template rounds<T>();
-#pragma unroll
-        for (int hh = ROUNDS == 1 ? 0 : h; hh < (ROUNDS == 1 ? 2 : h + 1); ++hh) {
-            // in one round u gets its missing bit back (RT = 3: bit 0)
-            const uint32_t quad = ROUNDS == 1 ? (u << 1) | (uint32_t)hh : u;
-            f32x4 row[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                row[i] = __builtin_bit_cast(f32x4, xr[4 * hh + i]);
-#pragma unroll
-            for (uint32_t i = 0; i < 4; ++i) {
-                bf16x4 p0, p1, p2;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float z = row[k][i];
-                    const __bf16 hi = (__bf16)z;
-                    const float r1 = z - (float)hi;
-                    const __bf16 mid = (__bf16)r1;
-                    p0[k] = hi;
-                    p1[k] = mid;
-                    p2[k] = (__bf16)(r1 - (float)mid);
-                }
-                char *d = base +
-                          16u * ((cg << (NB + 2)) + (i << NB) +
-                                 (((quad >> 1) ^ W::template swz<NB>(4u * cg)) ^
-                                  W::template swz<NB>(i))) +
-                          8u * (quad & 1u);
-                *reinterpret_cast<bf16x4 *>(d) = p0;
-                *reinterpret_cast<bf16x4 *>(d + PLANE) = p1;
-                *reinterpret_cast<bf16x4 *>(d + 2u * PLANE) = p2;
-            }
-        }
+        stage_quad<NB, CB, T>(lds, xr + 4 * h, cg, u);
     }
 }
 
@@ -274,10 +438,12 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
     const uint32_t ngroups = (ntiles + (1u << W::E) - 1u) >> W::E;
     const auto locate = [&](uint32_t g, size_t &b, uint32_t &hi) -> uint32_t {
         const uint32_t i = (g << W::E) | sub;
-        const uint32_t sl = i / live;
+        // past the last tile: tile 0 again, none of its rows real
+        const bool past = W::E > 0 && i >= ntiles;
+        const uint32_t sl = past ? 0u : i / live;
         b = sl;
-        hi = i - sl * live;
-        return i < ntiles ? tile_valid<A>(nvalid, hi) : 0u;
+        hi = past ? 0u : i - sl * live;
+        return past ? 0u : tile_valid<A>(nvalid, hi);
     };
 
     f32x4 acc[NS][NNB];
@@ -297,19 +463,24 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
     uint32_t hi;
     uint32_t valid = locate(p, b, hi);
     const uint32_t voff = Run::at(layout_base<A - VB>(t)) * 4u;
-    const auto load_ws = [&](size_t bb, uint32_t hh, bool any) {
+    const auto load_ws = [&]() {
         const __amdgpu_buffer_rsrc_t r =
-            buffer(ws + (bb << (A + HB)) + ((size_t)hh << R), extent_bytes<Run, A, float>());
+            buffer(ws + (b << (A + HB)) + ((size_t)hi << R), extent_bytes<Run, A, float>());
 #pragma unroll
         for (int k = 0; k < V; ++k)
-            v[k] = W::E == 0 || any ? Elt<float>::load(r, voff, Run::at((uint32_t)k << (A - VB)) * 4u) : 0.0f;
+            v[k] = Elt<float>::load(r, voff, Run::at((uint32_t)k << (A - VB)) * 4u);
     };
     constexpr bool PREFETCH_X = sizeof(T) == 2;   // float32: 32 registers more
     if constexpr (PREFETCH_X)
         load_x<A, CB, T>(xr, xs + b * nvalid + ((size_t)hi << A), valid, t);
-    load_ws(b, hi, valid > 0);
+    load_ws();
+#pragma unroll 1
     for (uint32_t g = p; g < ngroups; g += nwg) {   // uniform over the workgroup
         const bool more = g + nwg < ngroups;
+        const bool real = W::E == 0 || valid > 0;
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+            v[k] = real ? v[k] : 0.0f;
         // token bits [A-5, A), then [CB, A-5) in the product layout
         butterflies<0, VB>(v);
         __syncthreads();   // the previous group's product reads are done
@@ -332,9 +503,8 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
         uint32_t ln = lane, tt = t;
         asm volatile("" : "+v"(ln), "+v"(tt));
         const uint32_t j = ln & 15u, q = ln >> 4;
-        const bf16x8 *xb = reinterpret_cast<const bf16x8 *>(region);
-#pragma unroll
-        for (int h = 0; h < ROUNDS; ++h) {
+        const auto round = [&](auto H) {
+            constexpr int h = decltype(H)::value;
             __syncthreads();   // exchange reads, or the previous round's, are done
             stage_x<A, CB, T>(region, xr, tt, h);
             if (h == ROUNDS - 1 && more) {
@@ -343,94 +513,293 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                     load_x<A, CB, T>(xr, xs + b * nvalid + ((size_t)hi << A), valid, t);
             }
             __syncthreads();
-#pragma unroll
-            for (int s = h * STEPS / ROUNDS; s < (h + 1) * STEPS / ROUNDS; ++s) {
-                // k step: tokens 8 s + [0, 8) of each group q
-                const uint32_t sh = (uint32_t)(s - h * STEPS / ROUNDS);
-                const uint32_t chunk = ROUNDS == 1
-                                           ? (uint32_t)s | (q << (W::RT - 3)) | (tw << (W::RT - 1))
-                                           : sh | (q << (W::RT - 4)) | (tw << (W::RT - 2));
-                const uint32_t xo = chunk ^ W::template swz<NB>(j);
-                bf16x8 a0[NS], a1[NS], a2[NS];
-#pragma unroll
-                for (int sr = 0; sr < NS; ++sr) {
-                    float z[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        z[e] = v[sr | ((8 * s + e) << W::SR)];
-                    split3(z, a0[sr], a1[sr], a2[sr]);
-                }
-#pragma unroll
-                for (int n = 0; n < NNB; ++n) {
-                    const bf16x8 *src =
-                        xb + (j << NB) + (xo ^ W::template swz<NB>(16u * n)) + (16u * n << NB);
-                    const bf16x8 b0 = src[0];
-                    bf16x8 b1, b2;
-                    if constexpr (sizeof(T) == 4) {
-                        b1 = src[W::template plane_bytes<T>() / 16u];
-                        b2 = src[W::template plane_bytes<T>() / 8u];
-                    }
-#pragma unroll
-                    for (int sr = 0; sr < NS; ++sr) {
-                        f32x4 d = acc[sr][n];
-                        if constexpr (sizeof(T) == 4) {   // products down to 2^-25 of the largest
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[sr], b0, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[sr], b2, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[sr], b1, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[sr], b0, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[sr], b1, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[sr], b0, d, 0, 0, 0);
-                        } else {
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[sr], b0, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[sr], b0, d, 0, 0, 0);
-                            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[sr], b0, d, 0, 0, 0);
-                        }
-                        acc[sr][n] = d;
-                    }
-                    if (n % 2 == 1)   // few operand reads in registers at a time
-                        __builtin_amdgcn_sched_barrier(0);
-                }
-                __builtin_amdgcn_sched_barrier(0);   // later steps' splits stay below
-            }
-        }
+            // k step s: tokens 8 s + [0, 8) of each group q
+            constexpr int SB2 = W::RT - 3 - (ROUNDS - 1);   // step bits of a round
+            multiply<T, CB, NB, W::RT, W::SR, h * STEPS / ROUNDS, (h + 1) * STEPS / ROUNDS>(
+                acc, v, region, j, (q << SB2) | (tw << (SB2 + 2)));
+        };
+        round(std::integral_constant<int, 0>{});
+        if constexpr (ROUNDS == 2)
+            round(std::integral_constant<int, 1>{});
         if (more)
-            load_ws(b, hi, valid > 0);
+            load_ws();
     }
 
-    // lane 16 q + j holds rows a = 16 strip + 4 q + [0, 4) of column b = 16 n + j;
-    // the teams' sums are added in team order through LDS
-    const uint32_t j = lane & 15u, q = lane >> 4;
-    const uint32_t team = wave >> W::SW;
+    store_sums<C, NS, NNB, W::SW, CB>(acc, lds, part, wave >> W::SW, W::TEAMS,
+                                      wave & ((1u << W::SW) - 1u), lane);
+}
+
+// ---------------------------------------------------------------- direct form
+// Where the waves of a tile hold nothing but channel strips (2^6 values per
+// lane at most), no token bit lies across waves and the tile needs no exchange
+// at all: every lane loads its values straight in a product layout,
+//   lanes 0-3   channel bits 0-3        (64-byte pieces of the runs)
+//   lanes 4-5   token bits 0, 1
+//   waves       SW channel bits from 4
+//   registers   SR channel bits, then token bits RT, RT+1, 2 .. RT-1,
+// transforms the RT token bits in its registers, and trades token bits 0 and
+// 1 for RT and RT+1 between lanes 4-5 and registers (v_permlane16/32_swap) to
+// transform those too.  That ends in the product layout above with q = token
+// bits RT, RT+1.  LDS holds the staged dY / X only.
+template <int A, int CB>
+struct Wd {
+    static constexpr int C = 1 << CB;
+    static constexpr int TW = A - 11;
+    static constexpr int SB = CB - 4;
+    static constexpr int SW = SB < TW ? SB : TW;       // wave bits of a tile
+    static constexpr int SR = SB - SW;
+    static constexpr int LB = A - 6 - SW;              // log2 of values per lane
+    static constexpr int VV = 1 << LB;
+    static constexpr int RT = LB - SR;
+    static constexpr int WB = LB > VB && SW < 3 ? 2 : 3;   // wave bits of the workgroup
+    static constexpr int E = WB - SW;
+    static constexpr uint32_t THREADS = 64u << WB;
+    static constexpr uint32_t TEAMS = 1u << E;
+    static constexpr int NNB = C / 16;
+    static constexpr int NS = 1 << SR;
+    static constexpr int NCHB = A - CB - 3;
+    static_assert(A - CB == RT + 2, "every token bit in a lane or its registers");
+    // waves per SIMD the registers are held to: two 8-wave workgroups per CU
+    // with one strip (one with float32 at C = 128, whose operands take more),
+    // three 4-wave ones with 64 values per lane
+    template <typename T>
+    static constexpr int waves()
+    {
+        return LB > VB ? (WB == 2 ? 3 : 2) : (NS == 1 && !(sizeof(T) == 4 && CB == 7) ? 4 : 2);
+    }
+
+    template <typename T>
+    static constexpr int rounds() { return sizeof(T) == 2 || RT == 3 ? 1 : 2; }
+    template <typename T>
+    static constexpr int chunk_bits() { return rounds<T>() == 1 ? NCHB : NCHB - 1; }
+    template <typename T>
+    static constexpr uint32_t plane_bytes() { return 16u * Plane<chunk_bits<T>(), CB>::UNITS; }
+    template <typename T>
+    static constexpr uint32_t region()   // words of one tile
+    {
+        return (sizeof(T) == 2 ? 1u : 3u) * plane_bytes<T>() / 4u;
+    }
+    template <typename T>
+    static constexpr uint32_t lds_words()
+    {
+        const uint32_t w = region<T>() << E;
+        const uint32_t cc = TEAMS > 1 ? (uint32_t)C * C : 0u;
+        return w > cc ? w : cc;
+    }
+    // 16-byte pieces of dY / X a thread stages per round
+    template <typename T>
+    static constexpr int pieces() { return VV * (int)sizeof(T) / 16 / rounds<T>(); }
+
+    __device__ static uint32_t base(uint32_t lane, uint32_t strips)
+    {
+        return (lane & 15u) | (strips << 4) | ((lane >> 4) << CB);
+    }
+    __host__ __device__ static constexpr uint32_t reg(uint32_t k)
+    {
+        const uint32_t tok = k >> SR;
+        return ((k & ((1u << SR) - 1u)) << (4 + SW)) | ((tok & 3u) << (CB + RT)) |
+               ((tok >> 2) << (CB + 2));
+    }
+};
+
+// Butterflies over register bits [J0, J1) of VV values.
+template <int J0, int J1, int VV>
+__device__ __forceinline__ void bfly(float (&v)[VV])
+{
+#pragma unroll
+    for (int j = J0; j < J1; ++j) {
+#pragma unroll
+        for (int k = 0; k < VV; ++k) {
+            if (!(k & (1 << j))) {
+                const float a = v[k], b = v[k | (1 << j)];
+                v[k] = a + b;
+                v[k | (1 << j)] = a - b;
+            }
+        }
+    }
+}
+
+// Trades lane bit 4 (W = 16) or 5 (W = 32) for register bit J.
+template <int W, int J, int VV>
+__device__ __forceinline__ void swap_lane_bit(float (&v)[VV])
+{
+#pragma unroll
+    for (int k = 0; k < VV; ++k) {
+        if (!(k & (1 << J))) {
+            const uint32_t a = __builtin_bit_cast(uint32_t, v[k]);
+            const uint32_t b = __builtin_bit_cast(uint32_t, v[k | (1 << J)]);
+            if constexpr (W == 16) {
+                const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+                v[k] = __builtin_bit_cast(float, (uint32_t)r[0]);
+                v[k | (1 << J)] = __builtin_bit_cast(float, (uint32_t)r[1]);
+            } else {
+                const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+                v[k] = __builtin_bit_cast(float, (uint32_t)r[0]);
+                v[k | (1 << J)] = __builtin_bit_cast(float, (uint32_t)r[1]);
+            }
+        }
+    }
+}
+
+// Round h of the thread's dY / X pieces.  Piece group m (four pieces): channels
+// 2^LV cg + [0, 2^LV) of tokens 4 quad + i, quad = (t >> (CB - LV)) + m * QS
+// of the round's half of the tokens (two rounds: token bit RT-1 is the round).
+template <int A, int CB, typename T>
+struct StageX {
+    using W = Wd<A, CB>;
+    static constexpr int LV = sizeof(T) == 2 ? 3 : 2;
+    static constexpr int ROUNDS = W::template rounds<T>();
+    static constexpr int NP = W::template pieces<T>();
+    static constexpr int NM = NP / 4;
+    static constexpr uint32_t QS = (64u << W::SW) >> (CB - LV);   // quads per pass of the threads
+    static_assert(6 + W::SW >= CB - LV, "a tile's threads cover a row of pieces");
+    static_assert(NP % 4 == 0, "whole groups of four tokens");
+
+    // the quad of the tile (all tokens) from the round's quad
+    __device__ static uint32_t full(uint32_t quad, int h)
+    {
+        if constexpr (ROUNDS == 1)
+            return quad;
+        constexpr int B = W::RT - 3;   // quad bit of token bit RT-1
+        return (quad & ((1u << B) - 1u)) | ((uint32_t)h << B) | ((quad >> B) << (B + 1));
+    }
+    template <bool WHOLE>
+    __device__ static void load_rows(u32x4 (&xr)[NP], const T *tile, uint32_t valid, uint32_t t,
+                                     int h)
+    {
+        const __amdgpu_buffer_rsrc_t r = buffer(tile, valid * (uint32_t)sizeof(T));
+        const uint32_t cg = t & ((1u << (CB - LV)) - 1u), q0 = t >> (CB - LV);
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const uint32_t e0 = (full(q0 + m * QS, h) << (CB + 2)) + (cg << LV);
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                if (WHOLE || e0 + (i << CB) < valid)
+                    xr[4 * m + i] = __builtin_bit_cast(
+                        u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                   r, e0 * (uint32_t)sizeof(T), (i << CB) * (uint32_t)sizeof(T),
+                                   kStreaming));
+                else
+                    xr[4 * m + i] = (u32x4){0u, 0u, 0u, 0u};
+        }
+    }
+    // valid real elements of the tile, a multiple of C; rows past it read as zero
+    __device__ static void load(u32x4 (&xr)[NP], const T *tile, uint32_t valid, uint32_t t, int h)
+    {
+        if (valid >= (1u << A))   // uniform over the wave
+            load_rows<true>(xr, tile, valid, t, h);
+        else
+            load_rows<false>(xr, tile, valid, t, h);
+    }
+    __device__ static void stage(float *lds, const u32x4 (&xr)[NP], uint32_t t)
+    {
+        const uint32_t cg = t & ((1u << (CB - LV)) - 1u), q0 = t >> (CB - LV);
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+            stage_quad<W::template chunk_bits<T>(), CB, T>(lds, xr + 4 * m, cg, q0 + m * QS);
+    }
+};
+
+template <int A, int HB, int R, typename T, int CB>
+__global__ void __launch_bounds__((Wd<A, CB>::THREADS), (Wd<A, CB>::template waves<T>()))
+wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
+                    const float *__restrict__ wsd, const T *__restrict__ x,
+                    float *__restrict__ part, uint32_t nvalid, uint32_t live, uint32_t ntiles,
+                    uint32_t nwg)
+{
+    using W = Wd<A, CB>;
+    using X = StageX<A, CB, T>;
+    using Run = RunMap<HB, R>;
+    constexpr int C = W::C, NNB = W::NNB, NS = W::NS, VV = W::VV;
+    __shared__ __attribute__((aligned(16))) float lds[W::template lds_words<T>()];
+    const uint32_t tau = threadIdx.x;
+    const uint32_t t = tau & ((64u << W::SW) - 1u);   // thread of the tile
+    const uint32_t lane = tau & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tau >> 6);
+    const uint32_t team = wave >> W::SW;              // tile of the group
     const uint32_t strip0 = wave & ((1u << W::SW) - 1u);
-    const auto at = [&](int sr, int n) {
-        return ((16u * n + j) << CB) + 16u * (strip0 | ((uint32_t)sr << W::SW)) + 4u * q;
+    float *const region = lds + team * W::template region<T>();
+    const bool second = blockIdx.x >= nwg;
+    const uint32_t p = blockIdx.x - (second ? nwg : 0u);
+    const float *ws = second ? wsd : wsx;
+    const T *xs = second ? x : dy;
+    const uint32_t ngroups = (ntiles + (1u << W::E) - 1u) >> W::E;
+    const auto locate = [&](uint32_t g, size_t &b, uint32_t &hi) -> uint32_t {
+        const uint32_t i = (g << W::E) | team;
+        // past the last tile: tile 0 again, none of its rows real
+        const bool past = W::E > 0 && i >= ntiles;
+        const uint32_t sl = past ? 0u : i / live;
+        b = sl;
+        hi = past ? 0u : i - sl * live;
+        return past ? 0u : tile_valid<A>(nvalid, hi);
     };
-    for (uint32_t k = 1; k < W::TEAMS; ++k) {
-        __syncthreads();
-        if (team == k) {
+
+    f32x4 acc[NS][NNB];
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
+    for (int s = 0; s < NS; ++s)
 #pragma unroll
-                for (int n = 0; n < NNB; ++n)
-                    *reinterpret_cast<f32x4 *>(lds + at(s, n)) = acc[s][n];
-        }
-        __syncthreads();
-        if (team == 0) {
+        for (int n = 0; n < NNB; ++n)
+            acc[s][n] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+
+    constexpr int ROUNDS = X::ROUNDS, STEPS = 1 << (W::RT - 3);
+    constexpr int NB = W::template chunk_bits<T>();
+    float v[VV];
+    u32x4 xr[X::NP];
+    size_t b;
+    uint32_t hi;
+    uint32_t valid = locate(p, b, hi);
+    const uint32_t voff = Run::at(W::base(lane, strip0)) * 4u;
+    const auto load_ws = [&]() {
+        const __amdgpu_buffer_rsrc_t r =
+            buffer(ws + (b << (A + HB)) + ((size_t)hi << R), extent_bytes<Run, A, float>());
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
+        for (int k = 0; k < VV; ++k)
+            v[k] = Elt<float>::load(r, voff, Run::at(W::reg((uint32_t)k)) * 4u);
+    };
+    X::load(xr, xs + b * nvalid + ((size_t)hi << A), valid, t, 0);
+    load_ws();
+#pragma unroll 1
+    for (uint32_t g = p; g < ngroups; g += nwg) {   // uniform over the workgroup
+        const bool more = g + nwg < ngroups;
+        const bool real = W::E == 0 || valid > 0;
+        // opaque per group: the operand and staging addresses are cheap to form
+        // and, hoisted out of the loop, would take some forty registers
+        uint32_t ln = lane, tt = t;
+        asm volatile("" : "+v"(ln), "+v"(tt));
+        const uint32_t j = ln & 15u, q = ln >> 4;
+        const auto round = [&](auto H) {
+            constexpr int h = decltype(H)::value;
+            __syncthreads();   // the previous round's product reads are done
+            X::stage(region, xr, tt);
+            // the next round's pieces, or the next group's
+            if (h + 1 < ROUNDS) {
+                X::load(xr, xs + b * nvalid + ((size_t)hi << A), valid, tt, h + 1);
+            } else if (more) {
+                valid = locate(g + nwg, b, hi);
+                X::load(xr, xs + b * nvalid + ((size_t)hi << A), valid, tt, 0);
+            }
+            if constexpr (h == 0) {
 #pragma unroll
-                for (int n = 0; n < NNB; ++n)
-                    acc[s][n] += *reinterpret_cast<const f32x4 *>(lds + at(s, n));
-        }
+                for (int k = 0; k < VV; ++k)
+                    v[k] = real ? v[k] : 0.0f;
+                bfly<W::SR, W::LB>(v);
+                swap_lane_bit<16, W::SR>(v);
+                swap_lane_bit<32, W::SR + 1>(v);
+                bfly<W::SR, W::SR + 2>(v);
+            }
+            __syncthreads();
+            // k step s: tokens 8 s + [0, 8) of each group q
+            constexpr int SB2 = W::RT - 3 - (ROUNDS - 1);   // step bits of a round
+            multiply<T, CB, NB, W::RT, W::SR, h * STEPS / ROUNDS, (h + 1) * STEPS / ROUNDS>(
+                acc, v, region, j, q << SB2);
+        };
+        round(std::integral_constant<int, 0>{});
+        if constexpr (ROUNDS == 2)
+            round(std::integral_constant<int, 1>{});
+        if (more)
+            load_ws();
     }
-    if (team == 0) {
-        float *out = part + ((size_t)blockIdx.x << (2 * CB));
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-            for (int n = 0; n < NNB; ++n)
-                *reinterpret_cast<f32x4 *>(out + at(s, n)) = acc[s][n];
-    }
+    store_sums<C, NS, NNB, W::SW, CB>(acc, lds, part, team, W::TEAMS, strip0, lane);
 }
 
 // Block b < C: column b of dW_out, block C + b: row b of dW_in.  Adds the
@@ -495,13 +864,19 @@ hipError_t launch_k(const WgradTilesArgs &a)
 {
     constexpr Split sp = module_split(K);
     if constexpr (wgrad_tiles_shape(sp.A, CB)) {
-        using W = Wg<sp.A, CB>;
         const uint32_t live = wgrad_live_tiles(K, a.nvalid);
         const uint32_t ntiles = (uint32_t)a.B * live;
-        const uint32_t nwg = wgrad_tiles_parts(K, CB, a.B, a.nvalid);
-        hipLaunchKernelGGL((wgrad_tiles_kernel<sp.A, sp.HB, sp.R, T, CB>), dim3(2u * nwg),
-                           dim3(W::THREADS), 0, a.stream, a.wsx, static_cast<const T *>(a.dy),
-                           a.wsd, static_cast<const T *>(a.x), a.part, a.nvalid, live, ntiles, nwg);
+        const uint32_t nwg = wgrad_tiles_parts(K, CB, a.dtype, a.B, a.nvalid);
+        if constexpr (wgrad_direct_shape(sp.A, CB))
+            hipLaunchKernelGGL((wgrad_direct_kernel<sp.A, sp.HB, sp.R, T, CB>), dim3(2u * nwg),
+                               dim3(Wd<sp.A, CB>::THREADS), 0, a.stream, a.wsx,
+                               static_cast<const T *>(a.dy), a.wsd, static_cast<const T *>(a.x),
+                               a.part, a.nvalid, live, ntiles, nwg);
+        else
+            hipLaunchKernelGGL((wgrad_tiles_kernel<sp.A, sp.HB, sp.R, T, CB>), dim3(2u * nwg),
+                               dim3(Wg<sp.A, CB>::THREADS), 0, a.stream, a.wsx,
+                               static_cast<const T *>(a.dy), a.wsd, static_cast<const T *>(a.x),
+                               a.part, a.nvalid, live, ntiles, nwg);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((wgrad_final_kernel<CB>), dim3(2u << CB), dim3(256), 0, a.stream,

@@ -42,9 +42,28 @@ class Wg:
         return ((k & ((1 << self.SR) - 1)) << (4 + self.SW)) | ((k >> self.SR) << self.cb)
 
     @staticmethod
-    def swz(nb, c):
-        sh = 4 - nb if nb < 4 else 0
-        return ((c >> sh) ^ (c >> 3)) & ((1 << min(nb, 4)) - 1)
+    def plane(nb, cb, j, n, chunk):
+        """16-byte unit of chunk `chunk` of channel NNB j + n."""
+        row = ((j << (cb - 4)) | n) << nb
+        return row + ((j >> nb) << nb if nb < 4 else 0) + (chunk ^ (j & ((1 << min(nb, 4)) - 1)))
+
+    @staticmethod
+    def plane_units(nb, cb):
+        return (16 << (cb - 4 + nb)) + ((15 >> nb) << nb if nb < 4 else 0)
+
+    def stage(self, nb, lv, cg, quad):
+        """(half-word address, channel) of the writes of stage_quad."""
+        nnb = 1 << (self.cb - 4)
+        for i in range(1 << lv):
+            if nnb >= 1 << lv:
+                j, n = cg // (nnb >> lv), ((cg & ((nnb >> lv) - 1)) << lv) + i
+            else:
+                j, n = cg * ((1 << lv) // nnb) + i // nnb, i % nnb
+            c = (cg << lv) + i
+            assert c == nnb * j + n
+            byte = 16 * (self.plane(nb, self.cb, j, 0, quad >> 1) + (n << nb)) + 8 * (quad & 1)
+            assert byte + 8 <= 16 * self.plane_units(nb, self.cb)
+            yield byte // 2, c
 
 
 def test_shapes_covered():
@@ -96,15 +115,10 @@ def test_layout_exchange_and_operands(shape):
                     tok0 = 4 * uq + (hh << (w.RT - 1))
                     assert ((tok0 + 3) << cb) + (cg << lv) + (1 << lv) <= 1 << A
                     quad = u if bf16 or rounds == 2 else (u << 1) | hh
-                    for i in range(1 << lv):
-                        c = (cg << lv) + i
-                        byte = (16 * ((cg << (nb + lv)) + (i << nb)
-                                      + ((quad >> 1) ^ w.swz(nb, cg << lv) ^ w.swz(nb, i)))
-                                + 8 * (quad & 1))
-                        assert byte + 8 <= (2 << A) // rounds
+                    for a, c in w.stage(nb, lv, cg, quad):
                         for e in range(4):
-                            assert byte // 2 + e not in half
-                            half[byte // 2 + e] = (tok0 + e, c)
+                            assert a + e not in half
+                            half[a + e] = (tok0 + e, c)
             assert len(half) == (1 << A) // rounds
             for t in range(1 << (A - 5)):
                 lane, wave = t & 63, t >> 6
@@ -112,12 +126,13 @@ def test_layout_exchange_and_operands(shape):
                 for s in range(h * steps // rounds, (h + 1) * steps // rounds):
                     chunk = (s | (q << (w.RT - 3)) | (tw << (w.RT - 1)) if rounds == 1 else
                              (s - h * steps // rounds) | (q << (w.RT - 4)) | (tw << (w.RT - 2)))
-                    xo = chunk ^ w.swz(nb, j)
                     for n in (0, C // 16 - 1):
-                        unit = (j << nb) + (xo ^ w.swz(nb, 16 * n)) + (16 * n << nb)
+                        unit = w.plane(nb, cb, j, 0, chunk) + (n << nb)
                         got = [half[8 * unit + e] for e in range(8)]
-                        assert got == [(int(tok_of[t, (8 * s + e) << w.SR]), 16 * n + j)
+                        assert got == [(int(tok_of[t, (8 * s + e) << w.SR]), C // 16 * j + n)
                                        for e in range(8)]
+                    if lane == 0:   # the 16 lanes of an operand read: 16 bank groups
+                        assert len({w.plane(nb, cb, k, 0, chunk) % 16 for k in range(16)}) == 16
     # the strips of the registers: channel 16 (strip0 | sr << SW) + i
     for t in (0, 63, (1 << (A - 5)) - 1):
         strip0 = (t >> 6) & ((1 << w.SW) - 1)
@@ -133,3 +148,103 @@ def test_channel_inverse_commutes_with_the_token_sum():
     u, d = rng.standard_normal((tokens, C)), rng.standard_normal((tokens, C))
     H = hadamard(C).astype(float)
     assert np.allclose((u @ H).T @ d, H @ (u.T @ d))
+
+
+class Wd:
+    """The constants of the direct form's Wd<A, CB>."""
+
+    def __init__(self, A, cb):
+        self.A, self.cb = A, cb
+        self.TW, self.SB = A - 11, cb - 4
+        self.SW = min(self.SB, self.TW)
+        self.SR = self.SB - self.SW
+        self.LB = A - 6 - self.SW
+        self.RT = self.LB - self.SR
+        self.NCHB = A - cb - 3
+
+    plane, plane_units = staticmethod(Wg.plane), staticmethod(Wg.plane_units)
+
+    @property
+    def ok(self):
+        return Wg(self.A, self.cb).ok and self.LB <= 6
+
+    def base(self, t):
+        lane, strips = t & 63, t >> 6
+        return (lane & 15) | (strips << 4) | ((lane >> 4) << self.cb)
+
+    def reg(self, k):
+        tok = k >> self.SR
+        return (((k & ((1 << self.SR) - 1)) << (4 + self.SW)) | ((tok & 3) << (self.cb + self.RT))
+                | ((tok >> 2) << (self.cb + 2)))
+
+
+def swap(idx, lane_bit, j):
+    """v_permlane16/32_swap on register pairs (k, k | 1 << j): lane bit
+    lane_bit and register bit j change places."""
+    out = idx.copy()
+    lanes = np.arange(64)
+    lo, hi = lanes[(lanes >> lane_bit) & 1 == 0], lanes[(lanes >> lane_bit) & 1 == 1]
+    for k in range(idx.shape[1]):
+        if not k & (1 << j):
+            out[hi, k] = idx[lo, k | (1 << j)]
+            out[lo, k | (1 << j)] = idx[hi, k]
+    return out
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES if Wd(*s).ok])
+def test_direct_form(shape):
+    w = Wd(*shape)
+    A, cb, C = w.A, w.cb, 1 << w.cb
+    VV, threads = 1 << w.LB, 64 << w.SW
+    t_all, k = np.arange(threads), np.arange(VV)
+    idx = w.base(t_all)[:, None] + w.reg(k)[None, :]
+    assert np.array_equal(np.sort(idx.ravel()), np.arange(1 << A))
+    # transformed: register token bits, then the two traded in from the lanes
+    done = {int(np.log2(w.reg(1 << j))) for j in range(w.SR, w.LB)}
+    waves = []
+    for wv in range(1 << w.SW):
+        x = idx[64 * wv:64 * wv + 64]
+        x = swap(swap(x, 4, w.SR), 5, w.SR + 1)
+        waves.append(x)
+    for j in (w.SR, w.SR + 1):
+        done |= {int(np.log2(abs(int(waves[0][0, 1 << j]) - int(waves[0][0, 0]))))}
+    assert done == set(range(cb, A))
+    for bf16 in (True, False):
+        rounds = 1 if bf16 or w.RT == 3 else 2
+        nb = w.NCHB - (rounds == 2)
+        lv = 3 if bf16 else 2
+        np_ = VV * (2 if bf16 else 4) // 16 // rounds
+        qs = threads >> (cb - lv)
+        assert qs >= 1 and np_ % 4 == 0
+        B = w.RT - 3
+        steps = 1 << (w.RT - 3)
+        for h in range(rounds):
+            half = {}
+            for t in range(threads):
+                cg, q0 = t & ((1 << (cb - lv)) - 1), t >> (cb - lv)
+                for m in range(np_ // 4):
+                    quad = q0 + m * qs
+                    full = quad if rounds == 1 else ((quad & ((1 << B) - 1)) | (h << B)
+                                                     | ((quad >> B) << (B + 1)))
+                    assert (full << (cb + 2)) + (3 << cb) + (cg << lv) + (1 << lv) <= 1 << A
+                    for a, c in Wg.stage(w, nb, lv, cg, quad):
+                        for e in range(4):
+                            assert a + e not in half
+                            half[a + e] = (4 * full + e, c)
+            assert len(half) == (1 << A) // rounds
+            for wv in range(1 << w.SW):
+                for lane in range(64):
+                    j, q = lane & 15, lane >> 4
+                    for s in range(h * steps // rounds, (h + 1) * steps // rounds):
+                        chunk = (s | (q << (w.RT - 3)) if rounds == 1 else
+                                 (s - h * steps // rounds) | (q << (w.RT - 4)))
+                        for n in (0, C // 16 - 1):
+                            unit = Wg.plane(nb, cb, j, 0, chunk) + (n << nb)
+                            got = [half[8 * unit + e] for e in range(8)]
+                            for sr in (0, (1 << w.SR) - 1):
+                                el = [int(waves[wv][lane, sr | ((8 * s + e) << w.SR)])
+                                      for e in range(8)]
+                                assert [(v >> cb, C // 16 * j + n) for v in el] == got
+                                # the operand's row: channel 16 strip + lane mod 16
+                                assert {v & (C - 1) for v in el} == {
+                                    16 * (wv | (sr << w.SW)) + (lane & 15)}
