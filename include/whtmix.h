@@ -332,13 +332,15 @@ WHTMIX_API int whtmix_module_forward_separable(const void *x, const void *w_in,
  *   dgain         [N_pad][C] float32, overwritten, or NULL to skip.
  * No output may overlap an input or another output (except dx == dy); B*N <
  * 2^31.  Weight gradients are summed over row chunks in a fixed order, so
- * results are bitwise reproducible.  Workspace: 3*B*N*C floats plus the
- * mixer's forward and backward workspaces, 3*C*C packed weight elements and
- * the weight-gradient partial sums.  Other conventions as
+ * results are bitwise reproducible.  Workspace: the mixer's backward
+ * workspace, 3*C*C packed weight elements and the weight-gradient partial
+ * sums; where the projections or the weight gradients run apart from the
+ * mixer's passes (any other shape, C = 16 on 2^24 and 2^25 elements, C = 128 on
+ * 2^16 and 2^17, and C = 256) 3*B*N*C floats and the forward workspace besides.  Other conventions as
  * whtmix_module_forward (events: [0] before, then after each phase: [1]
  * dW_out, [2] the mixer's gradients, [3] dX and dW_in; with the projections
- * inside the mixer's passes [1] the gain gradient, [2] dW_out, [3] dX and
- * dW_in).
+ * inside the mixer's passes [1] the gain gradient, [2] dW_out (and dW_in
+ * where the two are formed together), [3] dX and dW_in).
  */
 WHTMIX_API int whtmix_module_backward(const void *x, const void *w_in,
                            const float *gain, const void *w_out,

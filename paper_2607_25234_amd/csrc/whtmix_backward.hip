@@ -31,10 +31,11 @@ using namespace tile;
 // workgroup owns one workspace run (2^HB x 2^R elements) for a chunk of
 // slices: forward over the HB high bits for both operands, multiply,
 // accumulate; then 2^-K times the sum is stored at the run's positions of G.
-template <int A, int HB, int R>
+// LIVE: only the first `live` rows of the tiles exist (with_live).
+template <int A, int HB, int R, bool LIVE>
 __global__ void __launch_bounds__(1 << (HB + R - VB))
 grad_middle_kernel(const float *__restrict__ wsx, const float *__restrict__ wsd,
-                   float *__restrict__ out, uint32_t nslices, uint32_t per_chunk)
+                   float *__restrict__ out, uint32_t nslices, uint32_t per_chunk, uint32_t live)
 {
     constexpr int M = HB + R;
     using G = Groups<M, R>;
@@ -52,8 +53,8 @@ grad_middle_kernel(const float *__restrict__ wsx, const float *__restrict__ wsd,
     for (uint32_t b = b0; b < b1; ++b) {   // uniform over the workgroup
         const size_t off = ((size_t)b << (A + HB)) + ((size_t)run << M);
         float vx[V], vd[V];
-        load_layout<G::TOP, ContigMap, float>(vx, buffer(wsx + off, (1u << M) * 4u), tau);
-        load_layout<G::TOP, ContigMap, float>(vd, buffer(wsd + off, (1u << M) * 4u), tau);
+        load_middle<G::TOP, M, LIVE>(vx, wsx + off, live << R, tau);
+        load_middle<G::TOP, M, LIVE>(vd, wsd + off, live << R, tau);
         butterflies<G::JT, VB>(vx);
         butterflies<G::JT, VB>(vd);
         forward_groups<M, R, 0, G::TOP, true>(lds, vx, tau);
@@ -196,15 +197,18 @@ __device__ __forceinline__ void sep_tile_sums_single(
 // back to wsx (the forward mixer's middle pass on x, for the block's backward,
 // which needs Z' as well), after the product and before the next slice's load.
 //
+// LIVE: only the first `live` rows of the tiles exist (with_live).
+//
 // SEPSUM (separable gains, R = 5, HB >= 6, R <= log2 C <= A): instead of
 // storing dG the workgroup forms the two log-gain gradients' partial sums of
 // dG * G over its tile and writes them to rowpart / colpart (sep_tile_sums
 // with several slices per chunk, sep_tile_sums_single with one).
-template <int A, int HB, int R, class Gain, bool SINGLE, bool MIX_X = false, bool SEPSUM = false>
+template <int A, int HB, int R, class Gain, bool SINGLE, bool MIX_X, bool SEPSUM, bool LIVE>
 __global__ void __launch_bounds__(1 << (HB + R - VB))
 grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain gain,
                        float *__restrict__ out, uint32_t nslices, uint32_t per_chunk,
-                       float *__restrict__ rowpart, float *__restrict__ colpart, uint32_t cbits)
+                       float *__restrict__ rowpart, float *__restrict__ colpart, uint32_t cbits,
+                       uint32_t live)
 {
     constexpr int M = HB + R;
     using G = Groups<M, R>;
@@ -216,8 +220,8 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
     const uint32_t chunk = blockIdx.x >> (A - R);
     const uint32_t b0 = chunk * per_chunk;
     const uint32_t b1 = min(b0 + per_chunk, nslices);
-    const auto tile = [&](const float *ws, uint32_t b) {
-        return buffer(ws + ((size_t)b << (A + HB)) + ((size_t)run << M), (1u << M) * 4u);
+    const auto tile = [&](float *ws, uint32_t b) {
+        return ws + ((size_t)b << (A + HB)) + ((size_t)run << M);
     };
     static_assert(!SEPSUM || (R == VB && G::SL == R && HB >= 6),
                   "the fused separable sums take the product in layout R = 5");
@@ -225,8 +229,8 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
                       : out + ((size_t)chunk << (A + HB)) + ((size_t)run << R) +
                             GM::at(layout_base<G::SL>(tau));
     float vx[V], vd[V];
-    load_layout<G::TOP, ContigMap, float>(vx, tile(wsx, b0), tau);
-    load_layout<G::TOP, ContigMap, float>(vd, tile(wsd, b0), tau);
+    load_middle<G::TOP, M, LIVE>(vx, tile(wsx, b0), live << R, tau);
+    load_middle<G::TOP, M, LIVE>(vd, tile(wsd, b0), live << R, tau);
     if constexpr (SINGLE) {
         butterflies<G::JT, VB>(vx);
         butterflies<G::JT, VB>(vd);
@@ -250,13 +254,13 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
             if constexpr (G::NBOT > 0)
                 inverse_groups<M, R, G::NBOT - 1>(lds, vx, tau);
             butterflies<G::JT, VB>(vx);
-            store_layout<G::TOP, ContigMap, float>(vx, tile(wsx, b0), tau);
+            store_middle<G::TOP, M, LIVE>(vx, tile(wsx, b0), live << R, tau);
         }
         apply_gain<A + HB>(vd, gv);
         if constexpr (G::NBOT > 0)
             inverse_groups<M, R, G::NBOT - 1>(lds, vd, tau);
         butterflies<G::JT, VB>(vd);
-        store_layout<G::TOP, ContigMap, float>(vd, tile(wsd, b0), tau);
+        store_middle<G::TOP, M, LIVE>(vd, tile(wsd, b0), live << R, tau);
     } else {
         float acc[V], gv[V];
 #pragma unroll
@@ -277,17 +281,17 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
                 if constexpr (G::NBOT > 0)
                     inverse_groups<M, R, G::NBOT - 1>(lds, vx, tau);
                 butterflies<G::JT, VB>(vx);
-                store_layout<G::TOP, ContigMap, float>(vx, tile(wsx, b), tau);
+                store_middle<G::TOP, M, LIVE>(vx, tile(wsx, b), live << R, tau);
             }
             if (more)
-                load_layout<G::TOP, ContigMap, float>(vx, tile(wsx, b + 1), tau);
+                load_middle<G::TOP, M, LIVE>(vx, tile(wsx, b + 1), live << R, tau);
             apply_gain<A + HB>(vd, gv);
             if constexpr (G::NBOT > 0)
                 inverse_groups<M, R, G::NBOT - 1>(lds, vd, tau);
             butterflies<G::JT, VB>(vd);
-            store_layout<G::TOP, ContigMap, float>(vd, tile(wsd, b), tau);
+            store_middle<G::TOP, M, LIVE>(vd, tile(wsd, b), live << R, tau);
             if (more)
-                load_layout<G::TOP, ContigMap, float>(vd, tile(wsd, b + 1), tau);
+                load_middle<G::TOP, M, LIVE>(vd, tile(wsd, b + 1), live << R, tau);
         }
         if constexpr (SEPSUM) {
             float p[V];
@@ -660,10 +664,13 @@ hipError_t grad_three_pass(const T *x, const T *dy, float *dst, const BackwardAr
     if ((e = launch_outer_fwd<K, T>(x, wsx, a.B, a.nvalid, st)) != hipSuccess) return e;
     if ((e = launch_outer_fwd<K, T>(dy, wsd, a.B, a.nvalid, st)) != hipSuccess) return e;
     float *o = lay.nchunks > 1 ? a.ws + lay.part : dst;
-    hipLaunchKernelGGL((grad_middle_kernel<A, HB, R>), dim3(lay.nchunks << (A - R)),
-                       dim3(1u << (HB + R - VB)), 0, st, wsx, wsd, o, (uint32_t)a.B,
-                       lay.per_chunk);
-    return hipGetLastError();
+    const uint32_t live = live_tiles(a.nvalid, A);
+    return with_live(live, HB, [&](auto l) {
+        hipLaunchKernelGGL((grad_middle_kernel<A, HB, R, decltype(l)::value>),
+                           dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st, wsx,
+                           wsd, o, (uint32_t)a.B, lay.per_chunk, live);
+        return hipGetLastError();
+    });
 }
 
 template <int K, typename T>
@@ -854,6 +861,7 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
     const hipStream_t st = a.stream;
     float *wsx = a.ws + lay.wsx;
     float *wsd = a.ws + lay.wsd;
+    const uint32_t live = live_tiles(a.nvalid, A);
     hipError_t e;
     if constexpr (std::is_same_v<Gain, LogSeparableGain> && R == VB && HB >= 6 &&
                   HB + R <= kMaxTile) {
@@ -863,11 +871,16 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
             // per chunk; the one-slice form for 2^15), then one small kernel
             // adds them up
             constexpr bool single = HB + R == kMaxTile;
-            hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, Gain, single, MIX_X, true>),
-                               dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
-                               wsx, wsd, gain, nullptr, (uint32_t)a.B, lay.per_chunk,
-                               a.ws + lay.rowpart, a.ws + lay.fcolpart, (uint32_t)a.cbits);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
+            e = with_live(live, HB, [&](auto l) {
+                hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, Gain, single, MIX_X, true,
+                                                           decltype(l)::value>),
+                                   dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
+                                   wsx, wsd, gain, nullptr, (uint32_t)a.B, lay.per_chunk,
+                                   a.ws + lay.rowpart, a.ws + lay.fcolpart, (uint32_t)a.cbits,
+                                   live);
+                return hipGetLastError();
+            });
+            if (e != hipSuccess) return e;
             const uint32_t P = (uint32_t)((uint64_t(1) << K) >> a.cbits);
             const uint32_t nrowblk = (P + 255u) / 256u;
             hipLaunchKernelGGL(sep_fused_final_kernel, dim3(nrowblk + (1u << a.cbits)),
@@ -881,10 +894,13 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
     float *o = lay.nchunks > 1 ? a.ws + lay.part : dst;
     if (lay.per_chunk == 1) {
         e = with_middle_gain(gain, a.B, [&](auto g) {
-            hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, decltype(g), true, MIX_X>),
-                               dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
-                               wsx, wsd, g, o, (uint32_t)a.B, 1u, nullptr, nullptr, 0u);
-            return hipGetLastError();
+            return with_live(live, HB, [&](auto l) {
+                hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, decltype(g), true, MIX_X,
+                                                           false, decltype(l)::value>),
+                                   dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
+                                   wsx, wsd, g, o, (uint32_t)a.B, 1u, nullptr, nullptr, 0u, live);
+                return hipGetLastError();
+            });
         });
         if (e != hipSuccess) return e;
     } else if constexpr (HB + R < kMaxTile) {
@@ -892,11 +908,14 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
         // slices: a joint gain streams (non-temporal), so it does not displace
         // the two workspaces
         e = with_streamed_gain(gain, [&](auto g) {
-            hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, decltype(g), false, MIX_X>),
-                               dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
-                               wsx, wsd, g, o, (uint32_t)a.B, lay.per_chunk, nullptr, nullptr,
-                               0u);
-            return hipGetLastError();
+            return with_live(live, HB, [&](auto l) {
+                hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, decltype(g), false, MIX_X,
+                                                           false, decltype(l)::value>),
+                                   dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
+                                   wsx, wsd, g, o, (uint32_t)a.B, lay.per_chunk, nullptr, nullptr,
+                                   0u, live);
+                return hipGetLastError();
+            });
         });
         if (e != hipSuccess) return e;
     } else {

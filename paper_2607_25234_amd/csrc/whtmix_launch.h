@@ -101,8 +101,9 @@ hipError_t launch_backward(const BackwardArgs &a);
 hipError_t launch_backward_middle(const BackwardArgs &a);
 
 // Enqueues only the middle pass of the block's three-pass plan (module_split,
-// or pair_split when a.pair_outer; a.ws holds the first outer pass's output);
-// a.x, a.y, a.nvalid and a.dtype are not used.
+// or pair_split when a.pair_outer; a.ws holds the first outer pass's output, which
+// leaves out the wholly padded outer tiles that a.nvalid gives); a.x, a.y and
+// a.dtype are not used.
 hipError_t launch_middle(const LaunchArgs &a);
 
 

@@ -778,6 +778,8 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds, const T *__res
     const size_t b = blk >> HB;
     const uint32_t hi = blk & ((1u << HB) - 1u);
     const uint32_t valid = tile_valid<A>(nvalid, hi);
+    if (valid == 0)
+        return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     XFrag<T, CB> f;
     load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, valid >= (1u << A), tau);
     stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
@@ -1011,6 +1013,8 @@ __device__ __forceinline__ void module_outer_fwd_pair_tile(float *lds, const __b
     const size_t b = blk >> HB;
     const uint32_t hi = blk & ((1u << HB) - 1u);
     const uint32_t valid = tile_valid<A>(nvalid, hi);
+    if (valid == 0)
+        return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     bf16x8 a[kPairKs];
     load_x_pair(a, x + b * nvalid + ((size_t)hi << A), valid, tau);
     stage_weights_dma<kPairWChunks, kPairThreads>(lds, w_in, tau);
@@ -1488,6 +1492,7 @@ LaunchArgs middle_args(const ModuleArgs &m, bool pair_outer)
     a.ws = m.ws;
     a.B = m.B;
     a.K = m.K;
+    a.nvalid = m.nvalid;
     a.plan = PLAN_THREE_PASS;
     a.stream = m.stream;
     a.pair_outer = pair_outer;
