@@ -148,9 +148,9 @@ def _options(plan: str | int = "auto", events=None, spin_limit: int = 0) -> Opti
 
 
 def _opt_arg(plan: str | int = "auto", events=None, spin_limit: int = 0):
-    """The options argument of an entry point: NULL when every option is
-    its default (the library then takes AUTO, no events, the default spin
-    limit), which saves building the structure on each call."""
+    """The options argument of a ctypes call: NULL when every option is its
+    default (the library then takes AUTO, no events, the default spin
+    limit)."""
     if events is None and not spin_limit and (plan == "auto" or plan == 0):
         return None
     return ctypes.byref(_options(plan, events, spin_limit))
@@ -188,7 +188,7 @@ _call_mod = None
 
 
 def _call():
-    """The CPython call module of the forward entry points
+    """The CPython call module of the entry points
     (csrc/whtmix_pycall.c), bound to the functions of the loaded library.
     It is built with the library; there is no fallback."""
     global _call_mod
@@ -203,6 +203,21 @@ def _call():
                ctypes.cast(L.whtmix_forward_separable, ctypes.c_void_p).value)
         _call_mod = m
     return _call_mod
+
+
+_entry = {}
+
+
+def _call_entry(name, *args, plan="auto", events=None) -> int:
+    """The entry point `name` through the call module, by the address of the
+    function in the loaded library."""
+    addr = _entry.get(name)
+    if addr is None:
+        addr = _entry[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+    o, opt = _opt_address(plan, events, 0)
+    st = _call().call(addr, *args, opt)
+    del o
+    return st
 
 
 def _opt_address(plan, events, spin_limit):
@@ -250,11 +265,11 @@ def forward_separable_raw(x_ptr: int, gt_ptr: int, gc_ptr: int, y_ptr: int, B: i
 def _check(x, out):
     import torch
 
-    if x.device.type != "cuda":
+    if not x.is_cuda:
         raise ValueError("x must be on a GPU device")
-    if x.dtype == torch.float32:
+    if x.dtype is torch.float32:
         dt = DTYPE_F32
-    elif x.dtype == torch.bfloat16:
+    elif x.dtype is torch.bfloat16:
         dt = DTYPE_BF16
     else:
         raise TypeError(f"x must be float32 or bfloat16, got {x.dtype}")
@@ -274,10 +289,27 @@ def _check(x, out):
 def _gain(t, shape, x, what):
     import torch
 
-    if t.device != x.device or t.dtype != torch.float32 or not t.is_contiguous():
+    # get_device() is -1 on the CPU
+    if t.get_device() != x.get_device() or t.dtype is not torch.float32 or not t.is_contiguous():
         raise ValueError(f"{what} must be a contiguous float32 tensor on x's device")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{what} shape {tuple(t.shape)} != {tuple(shape)}")
+
+
+def _on_device(x, stream, raw, ptrs, sizes, *options) -> int:
+    """raw(*ptrs, *sizes, stream, *options) with x's device current, on `stream`
+    or the device's current stream.  The device is switched only when it is
+    not current already, and the stream's handle is read without building a
+    Stream object: entering torch.cuda.device and torch.cuda.current_stream
+    took 1.4 and 2.0 us of a 16 us call."""
+    import torch
+
+    i = x.get_device()
+    st = torch._C._cuda_getCurrentRawStream(i) if stream is None else stream.cuda_stream
+    if torch._C._cuda_getDevice() == i:
+        return raw(*ptrs, *sizes, st, *options)
+    with torch.cuda.device(i):
+        return raw(*ptrs, *sizes, st, *options)
 
 
 def forward(x, gain, out=None, plan: str | int = "auto", stream=None, events=None,
@@ -289,15 +321,12 @@ def forward(x, gain, out=None, plan: str | int = "auto", stream=None, events=Non
     N count as zeros) on the same device.  out: optional tensor like x (may
     be x itself for in-place).  stream: a torch.cuda.Stream (default: the
     current stream)."""
-    import torch
-
     xx, dt, out = _check(x, out)
     B, N, C = xx.shape
     _gain(gain, (padded_tokens(N), C), x, "gain")
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = forward_raw(xx.data_ptr(), gain.data_ptr(), out.data_ptr(), B, N, C, dt,
-                             st.cuda_stream, plan, events, spin_limit)
+    status = _on_device(x, stream, forward_raw,
+                        (xx.data_ptr(), gain.data_ptr(), out.data_ptr()), (B, N, C, dt), plan,
+                        events, spin_limit)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_forward")
     return out
@@ -307,17 +336,14 @@ def forward_separable(x, log_gain_tokens, log_gain_channels, out=None,
                       plan: str | int = "auto", stream=None, events=None):
     """The paper's parametrisation (eq. (2) then eq. (3)) with log-domain gains:
     log_gain_tokens float32 [N_pad], log_gain_channels float32 [C]."""
-    import torch
-
     xx, dt, out = _check(x, out)
     B, N, C = xx.shape
     _gain(log_gain_tokens, (padded_tokens(N),), x, "log_gain_tokens")
     _gain(log_gain_channels, (C,), x, "log_gain_channels")
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = forward_separable_raw(xx.data_ptr(), log_gain_tokens.data_ptr(),
-                                       log_gain_channels.data_ptr(), out.data_ptr(), B, N, C,
-                                       dt, st.cuda_stream, plan, events)
+    status = _on_device(x, stream, forward_separable_raw,
+                        (xx.data_ptr(), log_gain_tokens.data_ptr(),
+                         log_gain_channels.data_ptr(), out.data_ptr()), (B, N, C, dt), plan,
+                        events)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_forward_separable")
     return out
@@ -327,8 +353,8 @@ def module_forward_raw(x_ptr: int, w_in_ptr: int, gain_ptr: int, w_out_ptr: int,
                        B: int, N: int, C: int, dtype: int, stream: int,
                        plan: str | int = "auto", events=None) -> int:
     """Direct call of whtmix_module_forward; returns the status."""
-    return lib().whtmix_module_forward(x_ptr, w_in_ptr, gain_ptr, w_out_ptr, y_ptr, B, N, C,
-                                       dtype, stream, _opt_arg(plan, events))
+    return _call_entry("whtmix_module_forward", x_ptr, w_in_ptr, gain_ptr, w_out_ptr, y_ptr,
+                       B, N, C, dtype, stream, plan=plan, events=events)
 
 
 def module_forward_separable_raw(x_ptr: int, w_in_ptr: int, gt_ptr: int, gc_ptr: int,
@@ -336,15 +362,14 @@ def module_forward_separable_raw(x_ptr: int, w_in_ptr: int, gt_ptr: int, gc_ptr:
                                  dtype: int, stream: int, plan: str | int = "auto",
                                  events=None) -> int:
     """Direct call of whtmix_module_forward_separable; returns the status."""
-    return lib().whtmix_module_forward_separable(x_ptr, w_in_ptr, gt_ptr, gc_ptr, w_out_ptr,
-                                                 y_ptr, B, N, C, dtype, stream,
-                                                 _opt_arg(plan, events))
+    return _call_entry("whtmix_module_forward_separable", x_ptr, w_in_ptr, gt_ptr, gc_ptr,
+                       w_out_ptr, y_ptr, B, N, C, dtype, stream, plan=plan, events=events)
 
 
 def _weight(w, C, x, what):
-    if w.device != x.device or w.dtype != x.dtype or not w.is_contiguous():
+    if w.get_device() != x.get_device() or w.dtype is not x.dtype or not w.is_contiguous():
         raise ValueError(f"{what} must be a contiguous tensor of x's dtype on x's device")
-    if tuple(w.shape) != (C, C):
+    if w.shape != (C, C):
         raise ValueError(f"{what} shape {tuple(w.shape)} != {(C, C)}")
 
 
@@ -353,18 +378,14 @@ def module_forward(x, w_in, gain, w_out, out=None, plan: str | int = "auto", str
     """The whole block of section III-B, eqs. (1)-(4): Y = mixer(X W_in) W_out with
     the joint gain.  w_in, w_out: [C, C] tensors of x's dtype (Z[n][j] = sum_i
     X[n][i] W_in[i][j]); gain: float32 [N_pad, C]."""
-    import torch
-
     xx, dt, out = _check(x, out)
     B, N, C = xx.shape
     _weight(w_in, C, x, "w_in")
     _weight(w_out, C, x, "w_out")
     _gain(gain, (padded_tokens(N), C), x, "gain")
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = module_forward_raw(xx.data_ptr(), w_in.data_ptr(), gain.data_ptr(),
-                                    w_out.data_ptr(), out.data_ptr(), B, N, C, dt,
-                                    st.cuda_stream, plan, events)
+    status = _on_device(x, stream, module_forward_raw,
+                        (xx.data_ptr(), w_in.data_ptr(), gain.data_ptr(), w_out.data_ptr(),
+                         out.data_ptr()), (B, N, C, dt), plan, events)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_module_forward")
     return out
@@ -373,21 +394,16 @@ def module_forward(x, w_in, gain, w_out, out=None, plan: str | int = "auto", str
 def module_forward_separable(x, w_in, log_gain_tokens, log_gain_channels, w_out, out=None,
                              plan: str | int = "auto", stream=None, events=None):
     """The whole block with the paper's log-domain gains (eqs. (1)-(4))."""
-    import torch
-
     xx, dt, out = _check(x, out)
     B, N, C = xx.shape
     _weight(w_in, C, x, "w_in")
     _weight(w_out, C, x, "w_out")
     _gain(log_gain_tokens, (padded_tokens(N),), x, "log_gain_tokens")
     _gain(log_gain_channels, (C,), x, "log_gain_channels")
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = module_forward_separable_raw(xx.data_ptr(), w_in.data_ptr(),
-                                              log_gain_tokens.data_ptr(),
-                                              log_gain_channels.data_ptr(), w_out.data_ptr(),
-                                              out.data_ptr(), B, N, C, dt, st.cuda_stream,
-                                              plan, events)
+    status = _on_device(x, stream, module_forward_separable_raw,
+                        (xx.data_ptr(), w_in.data_ptr(), log_gain_tokens.data_ptr(),
+                         log_gain_channels.data_ptr(), w_out.data_ptr(), out.data_ptr()),
+                        (B, N, C, dt), plan, events)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_module_forward_separable")
     return out
@@ -396,15 +412,15 @@ def module_forward_separable(x, w_in, log_gain_tokens, log_gain_channels, w_out,
 def backward_raw(x_ptr, dy_ptr, gain_ptr, dx_ptr, dgain_ptr, B, N, C, dtype, stream,
                  plan: str | int = "auto", events=None) -> int:
     """Direct call of whtmix_backward (0 for a skipped output); returns the status."""
-    return lib().whtmix_backward(x_ptr, dy_ptr, gain_ptr, dx_ptr, dgain_ptr, B, N, C, dtype,
-                                 stream, _opt_arg(plan, events))
+    return _call_entry("whtmix_backward", x_ptr, dy_ptr, gain_ptr, dx_ptr, dgain_ptr, B, N, C,
+                       dtype, stream, plan=plan, events=events)
 
 
 def backward_separable_raw(x_ptr, dy_ptr, gt_ptr, gc_ptr, dx_ptr, dgt_ptr, dgc_ptr, B, N, C,
                            dtype, stream, plan: str | int = "auto", events=None) -> int:
     """Direct call of whtmix_backward_separable; returns the status."""
-    return lib().whtmix_backward_separable(x_ptr, dy_ptr, gt_ptr, gc_ptr, dx_ptr, dgt_ptr,
-                                           dgc_ptr, B, N, C, dtype, stream, _opt_arg(plan, events))
+    return _call_entry("whtmix_backward_separable", x_ptr, dy_ptr, gt_ptr, gc_ptr, dx_ptr,
+                       dgt_ptr, dgc_ptr, B, N, C, dtype, stream, plan=plan, events=events)
 
 
 def _same(a, x, what):
@@ -430,12 +446,10 @@ def backward(x, dy, gain, want_dx: bool = True, want_dgain: bool = True, dx=None
     dgain = torch.empty_like(gain) if want_dgain else None
     if dx is None and dgain is None:
         raise ValueError("nothing to compute")
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = backward_raw(xx.data_ptr(), dy.data_ptr(), gain.data_ptr(),
-                              dx.data_ptr() if dx is not None else 0,
-                              dgain.data_ptr() if dgain is not None else 0, B, N, C, dt,
-                              st.cuda_stream, plan)
+    status = _on_device(x, stream, backward_raw,
+                        (xx.data_ptr(), dy.data_ptr(), gain.data_ptr(),
+                         dx.data_ptr() if dx is not None else 0,
+                         dgain.data_ptr() if dgain is not None else 0), (B, N, C, dt), plan)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_backward")
     return dx, dgain
@@ -461,13 +475,11 @@ def backward_separable(x, dy, log_gain_tokens, log_gain_channels, want_dx: bool 
     dgc = torch.empty_like(log_gain_channels) if want_dgains else None
     if dx is None and dgt is None:
         raise ValueError("nothing to compute")
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = backward_separable_raw(
-            xx.data_ptr(), dy.data_ptr(), log_gain_tokens.data_ptr(),
-            log_gain_channels.data_ptr(), dx.data_ptr() if dx is not None else 0,
-            dgt.data_ptr() if dgt is not None else 0, dgc.data_ptr() if dgc is not None else 0,
-            B, N, C, dt, st.cuda_stream, plan)
+    status = _on_device(x, stream, backward_separable_raw,
+                        (xx.data_ptr(), dy.data_ptr(), log_gain_tokens.data_ptr(),
+                         log_gain_channels.data_ptr(), dx.data_ptr() if dx is not None else 0,
+                         dgt.data_ptr() if dgt is not None else 0,
+                         dgc.data_ptr() if dgc is not None else 0), (B, N, C, dt), plan)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_backward_separable")
     return dx, dgt, dgc
@@ -477,19 +489,18 @@ def module_backward_raw(x_ptr, w_in_ptr, gain_ptr, w_out_ptr, dy_ptr, dx_ptr, dw
                         dw_out_ptr, dgain_ptr, B, N, C, dtype, stream,
                         plan: str | int = "auto", events=None) -> int:
     """Direct call of whtmix_module_backward; returns the status."""
-    return lib().whtmix_module_backward(x_ptr, w_in_ptr, gain_ptr, w_out_ptr, dy_ptr, dx_ptr,
-                                        dw_in_ptr, dw_out_ptr, dgain_ptr, B, N, C, dtype, stream,
-                                        _opt_arg(plan, events))
+    return _call_entry("whtmix_module_backward", x_ptr, w_in_ptr, gain_ptr, w_out_ptr, dy_ptr,
+                       dx_ptr, dw_in_ptr, dw_out_ptr, dgain_ptr, B, N, C, dtype, stream,
+                       plan=plan, events=events)
 
 
 def module_backward_separable_raw(x_ptr, w_in_ptr, gt_ptr, gc_ptr, w_out_ptr, dy_ptr, dx_ptr,
                                   dw_in_ptr, dw_out_ptr, dgt_ptr, dgc_ptr, B, N, C, dtype,
                                   stream, plan: str | int = "auto", events=None) -> int:
     """Direct call of whtmix_module_backward_separable; returns the status."""
-    return lib().whtmix_module_backward_separable(x_ptr, w_in_ptr, gt_ptr, gc_ptr, w_out_ptr,
-                                                  dy_ptr, dx_ptr, dw_in_ptr, dw_out_ptr, dgt_ptr,
-                                                  dgc_ptr, B, N, C, dtype, stream,
-                                                  _opt_arg(plan, events))
+    return _call_entry("whtmix_module_backward_separable", x_ptr, w_in_ptr, gt_ptr, gc_ptr,
+                       w_out_ptr, dy_ptr, dx_ptr, dw_in_ptr, dw_out_ptr, dgt_ptr, dgc_ptr,
+                       B, N, C, dtype, stream, plan=plan, events=events)
 
 
 def module_backward(x, w_in, gain, w_out, dy, want_dgain: bool = True, dx=None,
@@ -511,13 +522,10 @@ def module_backward(x, w_in, gain, w_out, dy, want_dgain: bool = True, dx=None,
     f32 = dict(dtype=torch.float32, device=x.device)
     dw_in, dw_out = torch.empty((C, C), **f32), torch.empty((C, C), **f32)
     dgain = torch.empty_like(gain) if want_dgain else None
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = module_backward_raw(xx.data_ptr(), w_in.data_ptr(), gain.data_ptr(),
-                                     w_out.data_ptr(), dy.data_ptr(), dx.data_ptr(),
-                                     dw_in.data_ptr(), dw_out.data_ptr(),
-                                     dgain.data_ptr() if dgain is not None else 0, B, N, C, dt,
-                                     st.cuda_stream, plan)
+    status = _on_device(x, stream, module_backward_raw,
+                        (xx.data_ptr(), w_in.data_ptr(), gain.data_ptr(), w_out.data_ptr(),
+                         dy.data_ptr(), dx.data_ptr(), dw_in.data_ptr(), dw_out.data_ptr(),
+                         dgain.data_ptr() if dgain is not None else 0), (B, N, C, dt), plan)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_module_backward")
     return dx, dw_in, dw_out, dgain
@@ -544,13 +552,12 @@ def module_backward_separable(x, w_in, log_gain_tokens, log_gain_channels, w_out
     dw_in, dw_out = torch.empty((C, C), **f32), torch.empty((C, C), **f32)
     dgt = torch.empty_like(log_gain_tokens) if want_dgains else None
     dgc = torch.empty_like(log_gain_channels) if want_dgains else None
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        status = module_backward_separable_raw(
-            xx.data_ptr(), w_in.data_ptr(), log_gain_tokens.data_ptr(),
-            log_gain_channels.data_ptr(), w_out.data_ptr(), dy.data_ptr(), dx.data_ptr(),
-            dw_in.data_ptr(), dw_out.data_ptr(), dgt.data_ptr() if dgt is not None else 0,
-            dgc.data_ptr() if dgc is not None else 0, B, N, C, dt, st.cuda_stream, plan)
+    status = _on_device(x, stream, module_backward_separable_raw,
+                        (xx.data_ptr(), w_in.data_ptr(), log_gain_tokens.data_ptr(),
+                         log_gain_channels.data_ptr(), w_out.data_ptr(), dy.data_ptr(),
+                         dx.data_ptr(), dw_in.data_ptr(), dw_out.data_ptr(),
+                         dgt.data_ptr() if dgt is not None else 0,
+                         dgc.data_ptr() if dgc is not None else 0), (B, N, C, dt), plan)
     if status != SUCCESS:
         raise WhtmixError(status, "whtmix_module_backward_separable")
     return dx, dw_in, dw_out, dgt, dgc

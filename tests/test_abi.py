@@ -282,6 +282,29 @@ def test_call_module_marshals_only():
         m.forward_ex(0, 0, 0, 1, 64, 64, 1 << 40, 0, 0)
 
 
+def test_call_by_address_marshals_only():
+    """The other entry points go through call(): the status of each is the
+    library's own for the same arguments, whatever the number of pointers."""
+    m, L = whtmix._call(), whtmix.lib()
+    for name, n in [("whtmix_backward", 5), ("whtmix_backward_separable", 7),
+                    ("whtmix_module_forward", 5), ("whtmix_module_forward_separable", 6),
+                    ("whtmix_module_backward", 9), ("whtmix_module_backward_separable", 11)]:
+        f = getattr(L, name)
+        addr = ctypes.cast(f, ctypes.c_void_p).value
+        far = [ALIGNED + (i << 32) for i in range(n)]
+        for ptrs in ([0] * n, far[:-1] + [far[-1] + 4], [far[0] + 4] + far[1:]):
+            for sizes in [(1, 64, 64, 0), (1, 64, 12, 0), (1, 64, 64, 9), (-1, 64, 64, 1)]:
+                st = m.call(addr, *ptrs, *sizes, 0, 0)
+                assert st == f(*ptrs, *sizes, 0, None) and st != 0
+                assert whtmix._call_entry(name, *ptrs, *sizes, 0) == st
+        with pytest.raises(TypeError):
+            m.call(addr, *([0] * 8), 0, 64, 64, 0, 0, 0)     # no entry point takes 8
+    with pytest.raises(ValueError):
+        m.call(0, *([0] * 5), 1, 64, 64, 0, 0, 0)
+    with pytest.raises(TypeError):
+        m.call(1)
+
+
 def test_plan_table():
     d = whtmix.plan_describe(1, 1, 1)
     assert d["plan"] == "small" and d["kernels"] == 1 and d["workspace_bytes"] == 0
