@@ -41,6 +41,15 @@ inline int module_outer_bits(int path, int cbits, int K)
     return three_pass_split(K).A;   // UNFUSED: the mixer's own plan
 }
 
+// Bytes of one repacked weight matrix: the float32 products of 32 <= C <= 128
+// inside the mixer's kernels take three bf16 planes, the others the matrix.
+inline int64_t module_packed_bytes(int cbits, int dtype)
+{
+    const int64_t cc = int64_t(1) << (2 * cbits);
+    if (dtype == DTYPE_BF16) return 2 * cc;
+    return cbits >= 5 && cbits <= kModuleMfmaMaxCbits ? 6 * cc : 4 * cc;
+}
+
 // A validated call of the block.  Workspace: the THREE_PASS workspace `ws`
 // (B * 2^K floats, else none), then for UNFUSED `z` (B * N * C floats), then
 // `wpack` (the two repacked weight matrices; not SMALL).

@@ -9,7 +9,9 @@
 //     Z' W_out has an fp32 left operand: it is split as Z' = hi + lo (two
 //     bf16, hi = RNE(Z'), lo = RNE(Z' - hi), which leaves a residual below
 //     2^-17 |Z'|) and multiplied in two MFMAs.
-//   * fp32: v_mfma_f32_16x16x4_f32.
+//   * fp32: the same instruction on three-term bf16 splits of both operands, the
+//     six products down to 2^-25 of the largest (v_mfma_f32_16x16x4_f32 for
+//     C = 16).
 //   The contraction order over k is free, so each lane's k values are chosen
 //   to make its loads of X 16-byte pieces and its register reads contiguous.
 //
@@ -191,7 +193,14 @@ struct Proj {
     // (fp32) instructions: 16 or 4 k values per MFMA
     static constexpr int KS = BF ? C / 16 : C / 4;
     // A-fragment registers per lane and row block (X: C/4 values)
-    static constexpr uint32_t WBYTES = (uint32_t)C * C * sizeof(T);
+    // float32 from C = 32: three-term bf16 splits of both operands on the same
+    // instruction, the weights as three planes of bf16, in W_ROUNDS column
+    // parts (C = 128: 96 KiB of planes would leave one workgroup per CU)
+    static constexpr bool X3 = !BF && C >= 32;
+    static constexpr int W_ROUNDS = X3 && C == 128 ? 2 : 1;
+    // elements of T a packed matrix takes, and the bytes staged at a time
+    static constexpr uint32_t PACKED = (uint32_t)C * C * (X3 ? 3u : 2u) / 2u;
+    static constexpr uint32_t WBYTES = PACKED * (uint32_t)sizeof(T) / W_ROUNDS;
 };
 
 // k value order of the 16x16x16 bf16 and 16x16x4 fp32 products (the fused
@@ -333,6 +342,77 @@ pack_std_kernel(PackJobs<T> jobs, int cb)
             jobs.p[i][idx] = jobs.w[i][pack_std_source<T>(idx, C, jobs.mode[i])];
 }
 
+// Three-term bf16 split of two floats, v = hi + mid + lo + d, each term the
+// nearest bf16 of what the previous ones leave: |mid| <= 2^-8 |v|, |lo| <= 2^-17
+// |v|, |d| <= 2^-26 |v|.
+__device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, uint32_t &mid,
+                                            uint32_t &lo)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const auto cvt = [](float a, float b) {
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
+    };
+    const auto f32 = [](uint32_t u) { return __builtin_bit_cast(float, u); };
+    hi = cvt(z0, z1);
+    const float r0 = z0 - f32(hi << 16), r1 = z1 - f32(hi & 0xffff0000u);
+    mid = cvt(r0, r1);
+    lo = cvt(r0 - f32(mid << 16), r1 - f32(mid & 0xffff0000u));
+}
+
+// float32 weights from C = 32: the order of pack_x32_kernel (but the epilogue's
+// column m of block nb is 16 nb + m) in three bf16 planes per column part:
+// part r holds column blocks [r NNB / ROUNDS, ...), plane by plane.
+__global__ void __launch_bounds__(256)
+pack_x3_kernel(PackJobs<float> jobs, int cb, uint32_t rounds)
+{
+    const uint32_t C = 1u << cb;
+    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    if (idx >= C * C) return;
+    const uint32_t e = idx & 7u, lane = (idx >> 3) & 63u;
+    const uint32_t j = lane & 15u, g = lane >> 4;
+    const uint32_t ks = C / 32u;
+    const uint32_t kk = (idx >> 9) % ks, nb = (idx >> 9) / ks;
+    const uint32_t col = 16u * nb + j;
+    const uint32_t part = C * C / rounds, r = idx / part;
+    const uint32_t dst = idx + 2u * part * r;   // 3 part r + (idx - part r)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        if (!jobs.p[i]) continue;
+        const int mode = jobs.mode[i];
+        const bool pro = mode == PACK_PROLOGUE || mode == PACK_PROLOGUE_T;
+        const uint32_t k = pro ? 32u * kk + 8u * g + e : (C / 4u) * g + 8u * kk + e;
+        const float w = jobs.w[i][mode >= PACK_PROLOGUE_T ? col * C + k : k * C + col];
+        uint32_t hi, mid, lo;
+        split3_pair(w, 0.0f, hi, mid, lo);
+        unsigned short *d = reinterpret_cast<unsigned short *>(jobs.p[i]) + dst;
+        d[0] = (unsigned short)hi;
+        d[part] = (unsigned short)mid;
+        d[2u * part] = (unsigned short)lo;
+    }
+}
+
+// acc = a b over ks k steps, both in three terms: the six products down to
+// 2^-25 of the largest, below float32's own rounding; the leading products
+// apart, so that the sum is rounded once per step at its own size.
+template <int KS2>
+__device__ __forceinline__ f32x4 mul_x3(const bf16x8 (&a0)[KS2], const bf16x8 (&a1)[KS2],
+                                        const bf16x8 (&a2)[KS2], const bf16x8 *b0,
+                                        const bf16x8 *b1, const bf16x8 *b2)
+{
+    f32x4 lead = {0.0f, 0.0f, 0.0f, 0.0f}, rest = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int kk = 0; kk < KS2; ++kk) {
+        rest = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2[kk], b0[kk], rest, 0, 0, 0);
+        rest = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[kk], b2[kk], rest, 0, 0, 0);
+        rest = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[kk], b1[kk], rest, 0, 0, 0);
+        rest = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[kk], b0[kk], rest, 0, 0, 0);
+        rest = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[kk], b1[kk], rest, 0, 0, 0);
+        lead = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[kk], b0[kk], lead, 0, 0, 0);
+    }
+    return lead + rest;
+}
+
 // X fragments of the prologue: per row block, the lane's C/4 channels of its
 // token, as bf16x4 per k step (bf16) or floats (fp32).
 template <typename T, int CB>
@@ -347,7 +427,7 @@ struct XFrag<__bf16, CB> {
 template <int CB>
 struct XFrag<float, CB> {
     using P = Proj<float, CB>;
-    float a[P::NRB][P::KS];
+    float a[P::NRB][P::KS];   // X3: k step kk's channels 32 kk + 8 q + e at 8 kk + e
 };
 
 // Token (tile row) of MFMA row m in row block rb for wave w: layout 4 puts
@@ -398,10 +478,12 @@ __device__ __forceinline__ void load_x_frags(XFrag<T, CB> &f, const T *tile, uin
 #pragma unroll
             for (int p = 0; p < P::C / 16; ++p) {
                 u32x4 d = {0u, 0u, 0u, 0u};
+                // X3: channels 32 (p / 2) + 8 q + 4 (p % 2) + [0, 4)
                 if (ok)
-                    d = __builtin_amdgcn_raw_buffer_load_b128(r, row + 16u * q,
-                                                              rb * rb_bytes + 64u * p,
-                                                              kStreaming);
+                    d = __builtin_amdgcn_raw_buffer_load_b128(
+                        r, row + (P::X3 ? 32u : 16u) * q,
+                        rb * rb_bytes + (P::X3 ? 128u * (p >> 1) + 16u * (p & 1) : 64u * p),
+                        kStreaming);
                 // Cast the whole vector: this compiler reads element 0 for a
                 // __builtin_bit_cast of a single ext-vector element (d.y etc.).
                 const f32x4 fv = __builtin_bit_cast(f32x4, d);
@@ -681,8 +763,10 @@ struct Lds {
     static constexpr uint32_t TILE = pad(1u << M) * 4u;
     static constexpr uint32_t W = Proj<T, CB>::WBYTES;
     static constexpr uint32_t CHUNKS = W / 16u;
+    // weights in parts: staged into the tile's space after the last exchange
+    static constexpr bool PARTS = Proj<T, CB>::W_ROUNDS > 1;
     static constexpr bool PREFETCH_OK = CHUNKS % NT == 0 && CHUNKS / NT <= 8;
-    static constexpr bool SEPARATE = TILE + W <= 80u * 1024u || !PREFETCH_OK;
+    static constexpr bool SEPARATE = !PARTS && (TILE + W <= 80u * 1024u || !PREFETCH_OK);
     static constexpr uint32_t PER = PREFETCH_OK ? CHUNKS / NT : 1;
     static constexpr uint32_t REGION0 = TILE > W ? TILE : W;   // tile, or weights first
     static constexpr uint32_t fwd_bytes() { return REGION0; }
@@ -723,7 +807,157 @@ __device__ __forceinline__ void stage_weights_dma(void *lds, const void *w, uint
             static_cast<char *>(lds) + 16u * (wave * 64u + i * NT), 16, 0, 0);
 }
 
+// The projections of float32 from C = 32.  Against the fp32 instruction the six
+// bf16 products take 3/8 of the matrix-unit cycles.
+template <int KS2>
+__device__ __forceinline__ void split_x3(bf16x8 (&a0)[KS2], bf16x8 (&a1)[KS2], bf16x8 (&a2)[KS2],
+                                         const float *z)
+{
+#pragma unroll
+    for (int kk = 0; kk < KS2; ++kk) {
+        u32x4 h, m, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t a, b, c;
+            split3_pair(z[8 * kk + 2 * e], z[8 * kk + 2 * e + 1], a, b, c);
+            h[e] = a;
+            m[e] = b;
+            l[e] = c;
+        }
+        a0[kk] = __builtin_bit_cast(bf16x8, h);
+        a1[kk] = __builtin_bit_cast(bf16x8, m);
+        a2[kk] = __builtin_bit_cast(bf16x8, l);
+    }
+}
+
+template <int CB, uint32_t NT>
+__device__ __forceinline__ void project_in_x3(float (&v)[V], const XFrag<float, CB> &f, float *lds,
+                                              const float *w, uint32_t tau)
+{
+    using P = Proj<float, CB>;
+    constexpr int KS2 = P::KS2, NPR = P::NNB / P::W_ROUNDS;   // column blocks of a part
+    constexpr uint32_t PLANE = NPR * KS2 * 64;                // 16-byte units
+    const uint32_t lane = tau & 63u;
+    bf16x8 a0[P::NRB][KS2], a1[P::NRB][KS2], a2[P::NRB][KS2];
+#pragma unroll
+    for (int r = 0; r < P::W_ROUNDS; ++r) {
+        if (r > 0)
+            __syncthreads();   // the previous part's readers
+        stage_weights<P::WBYTES / 16u, NT>(
+            lds, reinterpret_cast<const char *>(w) + (size_t)r * P::WBYTES, tau);
+        if (r == 0) {
+#pragma unroll
+            for (int rb = 0; rb < P::NRB; ++rb)
+                split_x3<KS2>(a0[rb], a1[rb], a2[rb], f.a[rb]);
+        }
+        __syncthreads();
+        const bf16x8 *wb = reinterpret_cast<const bf16x8 *>(lds) + lane;
+#pragma unroll
+        for (int n = 0; n < NPR; ++n) {
+            const int nb = r * NPR + n;
+            bf16x8 b0[KS2], b1[KS2], b2[KS2];
+#pragma unroll
+            for (int kk = 0; kk < KS2; ++kk) {
+                b0[kk] = wb[(n * KS2 + kk) * 64];
+                b1[kk] = wb[(n * KS2 + kk) * 64 + PLANE];
+                b2[kk] = wb[(n * KS2 + kk) * 64 + 2 * PLANE];
+            }
+#pragma unroll
+            for (int rb = 0; rb < P::NRB; ++rb) {
+                const f32x4 acc = mul_x3<KS2>(a0[rb], a1[rb], a2[rb], b0, b1, b2);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[nb | (e << (CB - 4)) | (rb << (CB - 2))] = acc[e];
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one block's operands at a time
+        }
+    }
+}
+
+// Y = Z' W_out as project_out, the weights either whole in LDS at wl, or (w not
+// null) staged into lds part by part.
+template <int CB, int M, uint32_t NT>
+__device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *wl, float *lds,
+                                               const float *w, float *tile, uint32_t valid,
+                                               uint32_t tau)
+{
+    using P = Proj<float, CB>;
+    constexpr int KS2 = P::KS2, NPR = P::NNB / P::W_ROUNDS;
+    constexpr uint32_t PLANE = NPR * KS2 * 64;
+    const uint32_t lane = tau & 63u, wv = tau >> 6;
+    const uint32_t j = lane & 15u, q = lane >> 4;
+    const __amdgpu_buffer_rsrc_t r = buffer(tile, valid * 4u);
+    const bool whole = valid >= (1u << M);
+    const uint32_t tok0 = j | (wv << 4);
+    const uint32_t row = tok0 * (uint32_t)(P::C * 4);
+    constexpr uint32_t rb_bytes = (1u << (M - 7)) * P::C * 4u;
+    bf16x8 z0[P::NRB][KS2], z1[P::NRB][KS2], z2[P::NRB][KS2];
+#pragma unroll
+    for (int rb = 0; rb < P::NRB; ++rb)
+        split_x3<KS2>(z0[rb], z1[rb], z2[rb], v + (rb << (CB - 2)));
+#pragma unroll
+    for (int part = 0; part < P::W_ROUNDS; ++part) {
+        if constexpr (P::W_ROUNDS > 1) {
+            __syncthreads();   // the last exchange's readers, or the previous part's
+            stage_weights<P::WBYTES / 16u, NT>(
+                lds, reinterpret_cast<const char *>(w) + (size_t)part * P::WBYTES, tau);
+            __syncthreads();
+            wl = lds;
+        }
+        const bf16x8 *wb = static_cast<const bf16x8 *>(wl) + lane;
+#pragma unroll
+        for (int n = 0; n < NPR; ++n) {
+            const int nb = part * NPR + n;
+            bf16x8 w0[KS2], w1[KS2], w2[KS2];
+#pragma unroll
+            for (int kk = 0; kk < KS2; ++kk) {
+                w0[kk] = wb[(n * KS2 + kk) * 64];
+                w1[kk] = wb[(n * KS2 + kk) * 64 + PLANE];
+                w2[kk] = wb[(n * KS2 + kk) * 64 + 2 * PLANE];
+            }
+#pragma unroll
+            for (int rb = 0; rb < P::NRB; ++rb) {
+                // channels 16 nb + 4 q + [0, 4)
+                const u32x4 d = __builtin_bit_cast(
+                    u32x4, mul_x3<KS2>(w0, w1, w2, z0[rb], z1[rb], z2[rb]));
+                const bool ok =
+                    whole || (tok0 + ((uint32_t)rb << (M - 7))) * (uint32_t)P::C < valid;
+                if (ok)
+                    __builtin_amdgcn_raw_buffer_store_b128(d, r, row + 16u * q,
+                                                           rb * rb_bytes + 64u * nb, kYPolicy);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- kernels
+// The end of the last kernel: the rest of W_out into LDS and Y = Z' W_out from
+// the epilogue layout.  wregion: W_out staged at kernel start (SEPARATE), else
+// wreg holds it (or, PARTS, it is staged from memory).
+template <typename T, int CB, int M, uint32_t PER>
+__device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const void *wregion,
+                                         [[maybe_unused]] const u32x4 (&wreg)[PER],
+                                         [[maybe_unused]] const T *w_out, T *tile, uint32_t valid,
+                                         uint32_t tau)
+{
+    using L = Lds<M, T, CB>;
+    const void *wl = wregion;
+    if constexpr (!L::SEPARATE && !L::PARTS) {
+        __syncthreads();   // every thread has read its epilogue-layout values
+#pragma unroll
+        for (uint32_t i = 0; i < L::PER; ++i)
+            reinterpret_cast<u32x4 *>(lds)[tau + i * L::NT] = wreg[i];
+        wl = lds;
+    }
+    if constexpr (!L::PARTS)
+        __syncthreads();
+    if constexpr (Proj<T, CB>::X3)
+        project_out_x3<CB, M, L::NT>(v, wl, lds, w_out, tile, valid, tau);
+    else
+        project_out<T, CB, M>(v, wl, tile, valid, tau);
+}
+
 // FUSED: one workgroup per slice (M = K).
 template <int K, typename T, class Gain, int CB>
 __global__ void __launch_bounds__(1 << (K - VB))
@@ -737,32 +971,28 @@ module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
     const size_t base = (size_t)blockIdx.x * nvalid;
     XFrag<T, CB> f;
     load_x_frags<T, CB>(f, x + base, nvalid, nvalid >= (1u << K), tau);
-    stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
-    u32x4 wreg[L::PER];
+    if constexpr (!Proj<T, CB>::X3)
+        stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
+    [[maybe_unused]] u32x4 wreg[L::PER];
     if constexpr (L::SEPARATE) {
         stage_weights<L::CHUNKS, L::NT>(region1, w_out, tau);
-    } else {
+    } else if constexpr (!L::PARTS) {
 #pragma unroll
         for (uint32_t i = 0; i < L::PER; ++i)
             wreg[i] = static_cast<const u32x4 *>(static_cast<const void *>(w_out))[tau + i * L::NT];
     }
     float v[V], gv[V];
     gain.template load<K - 5, ContigMap>(gv, 0, tau);
-    __syncthreads();
-    project_in<T, CB>(v, f, lds, tau);
+    if constexpr (Proj<T, CB>::X3) {
+        project_in_x3<CB, L::NT>(v, f, lds, w_in, tau);
+    } else {
+        __syncthreads();
+        project_in<T, CB>(v, f, lds, tau);
+    }
     forward_from_prologue<K>(lds, v, tau);
     apply_gain<K>(v, gv);
     inverse_to_epilogue<K, CB, true>(lds, v, tau);
-    const void *wl = region1;
-    if constexpr (!L::SEPARATE) {
-        __syncthreads();   // every thread has read its epilogue-layout values
-#pragma unroll
-        for (uint32_t i = 0; i < L::PER; ++i)
-            reinterpret_cast<u32x4 *>(lds)[tau + i * L::NT] = wreg[i];
-        wl = lds;
-    }
-    __syncthreads();
-    project_out<T, CB, K>(v, wl, y + base, nvalid, tau);
+    epilogue<T, CB, K>(v, lds, region1, wreg, w_out, y + base, nvalid, tau);
 }
 
 // THREE_PASS first pass: prologue, forward over the A low bits, workspace.
@@ -782,10 +1012,14 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds, const T *__res
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     XFrag<T, CB> f;
     load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, valid >= (1u << A), tau);
-    stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
-    __syncthreads();
     float v[V];
-    project_in<T, CB>(v, f, lds, tau);
+    if constexpr (Proj<T, CB>::X3) {
+        project_in_x3<CB, L::NT>(v, f, lds, w_in, tau);
+    } else {
+        stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
+        __syncthreads();
+        project_in<T, CB>(v, f, lds, tau);
+    }
     forward_from_prologue<A>(lds, v, tau);
     store_layout<A - 5, Run, float>(
         v, buffer(ws + (b << (A + HB)) + ((size_t)hi << R), extent_bytes<Run, A, float>()), tau);
@@ -836,10 +1070,10 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
     const uint32_t valid = tile_valid<A>(nvalid, hi);
     if (valid == 0)
         return;   // wholly padding: nothing to store (uniform per workgroup)
-    u32x4 wreg[L::PER];
+    [[maybe_unused]] u32x4 wreg[L::PER];
     if constexpr (L::SEPARATE) {
         stage_weights<L::CHUNKS, L::NT>(wregion, w_out, tau);
-    } else {
+    } else if constexpr (!L::PARTS) {
 #pragma unroll
         for (uint32_t i = 0; i < L::PER; ++i)
             wreg[i] = static_cast<const u32x4 *>(static_cast<const void *>(w_out))[tau + i * L::NT];
@@ -850,16 +1084,8 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
     inverse_to_epilogue<A, CB, false>(lds, v, tau);
     if constexpr (ZOUT)
         store_epilogue_f32<A, CB>(lds, v, z + b * nvalid + ((size_t)hi << A), valid, tau);
-    const void *wl = wregion;
-    if constexpr (!L::SEPARATE) {
-        __syncthreads();
-#pragma unroll
-        for (uint32_t i = 0; i < L::PER; ++i)
-            reinterpret_cast<u32x4 *>(lds)[tau + i * L::NT] = wreg[i];
-        wl = lds;
-    }
-    __syncthreads();
-    project_out<T, CB, A>(v, wl, y + b * nvalid + ((size_t)hi << A), valid, tau);
+    epilogue<T, CB, A>(v, lds, wregion, wreg, w_out, y + b * nvalid + ((size_t)hi << A), valid,
+                       tau);
 }
 
 // ---------------------------------------------------------------- C = 256 (bf16)
@@ -1469,7 +1695,7 @@ hipError_t launch_pack(const ModuleArgs &m, bool out_as_in)
 template <int K, typename T, class Gain, int CB>
 hipError_t launch_module_fused(const ModuleArgs &m, Gain gain)
 {
-    const uint32_t n = 1u << (2 * CB);
+    const uint32_t n = Proj<T, CB>::PACKED;
     const T *pin = static_cast<const T *>(m.wpack);
     hipError_t e = record(m.events[0], m.stream);
     if (e != hipSuccess) return e;
@@ -1504,7 +1730,7 @@ hipError_t launch_module_three_pass(const ModuleArgs &m, Gain gain)
 {
     constexpr Split sp = module_split(K);
     constexpr int A = sp.A, HB = sp.HB, R = sp.R;
-    const uint32_t n = 1u << (2 * CB);
+    const uint32_t n = Proj<T, CB>::PACKED;
     const T *pin = static_cast<const T *>(m.wpack);
     const hipStream_t st = m.stream;
     hipError_t e = record(m.events[0], st);
@@ -1602,6 +1828,16 @@ hipError_t dispatch_fused_module(const ModuleArgs &m, Gain gain)
                                {PACK_PROLOGUE, PACK_EPILOGUE, 0}};
         hipLaunchKernelGGL(pack_x32_kernel, dim3((n + 255u) / 256u), dim3(256), 0, m.stream, jobs,
                            m.cbits);
+        e = hipGetLastError();
+    } else if (std::is_same<T, float>::value && m.cbits >= 5) {
+        const uint32_t n = 1u << (2 * m.cbits);
+        const PackJobs<float> jobs{{static_cast<const float *>(m.w_in),
+                                    static_cast<const float *>(m.w_out), nullptr},
+                                   {static_cast<float *>(m.wpack),
+                                    static_cast<float *>(m.wpack) + n / 2u * 3u, nullptr},
+                                   {PACK_PROLOGUE, PACK_EPILOGUE, 0}};
+        hipLaunchKernelGGL(pack_x3_kernel, dim3((n + 255u) / 256u), dim3(256), 0, m.stream, jobs,
+                           m.cbits, m.cbits == 7 ? 2u : 1u);
         e = hipGetLastError();
     } else {
         e = launch_pack<T>(m, false);
@@ -2154,12 +2390,16 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
     const T *dy = static_cast<const T *>(m.dy);
     const T *w_in = static_cast<const T *>(m.w_in);
     T *pk = static_cast<T *>(m.wpack);
-    T *p_in = pk, *p_out_t = pk + CC, *p_in_te = pk + 2 * CC;
+    constexpr uint32_t PK = Proj<T, CB>::PACKED;
+    T *p_in = pk, *p_out_t = pk + PK, *p_in_te = pk + 2 * PK;
     const PackJobs<T> jobs{{w_in, static_cast<const T *>(m.w_out), w_in},
                            {p_in, p_out_t, p_in_te},
                            {PACK_PROLOGUE, PACK_PROLOGUE_T, PACK_EPILOGUE_T}};
     if constexpr (Proj<T, CB>::X32)
         hipLaunchKernelGGL(pack_x32_kernel, dim3((CC + 255u) / 256u), dim3(256), 0, st, jobs, CB);
+    else if constexpr (Proj<T, CB>::X3)
+        hipLaunchKernelGGL(pack_x3_kernel, dim3((CC + 255u) / 256u), dim3(256), 0, st, jobs, CB,
+                           (uint32_t)Proj<T, CB>::W_ROUNDS);
     else
         hipLaunchKernelGGL((pack_std_kernel<T>), dim3((CC + 255u) / 256u), dim3(256), 0, st, jobs,
                            CB);

@@ -942,3 +942,43 @@ def test_weight_gradient_model(rows, cb, kinds):
     assert np.max(np.abs(got - ref)) <= tol * np.max(np.abs(a).sum(0)[:, None] * np.abs(b).max(0))
     chunks, rpc = wgrad_plan(rows, cb)
     assert chunks * rpc >= rows and (chunks - 1) * rpc < rows and rpc % 4 == 0
+
+
+@pytest.mark.parametrize("C,rounds", [(32, 1), (64, 1), (128, 2)])
+def test_float32_split_planes(C, rounds):
+    """pack_x3_kernel and the reads of project_in_x3 / project_out_x3: every
+    element of the matrix lands once in each plane of its column part, and the
+    operand of (column block, k step, lane) holds the eight k values the other
+    operand pairs with (prologue: channels 32 kk + 8 q + e, as the X fragments
+    load them; epilogue: channels q C/4 + 8 kk + e of the epilogue layout)."""
+    ks, nnb, part = C // 32, C // 16, C * C // rounds
+    idx = np.arange(C * C)
+    e, lane = idx & 7, (idx >> 3) & 63
+    j, g = lane & 15, lane >> 4
+    kk, nb = (idx >> 9) % ks, (idx >> 9) // ks
+    col = 16 * nb + j
+    r = idx // part
+    dst = idx + 2 * part * r
+    for k in (32 * kk + 8 * g + e, (C // 4) * g + 8 * kk + e):
+        assert len(np.unique(k * C + col)) == C * C
+        where = np.full((3, 3 * C * C), -1)
+        for plane in range(3):
+            where[plane, dst + plane * part] = k * C + col
+        assert (np.sum(where >= 0, axis=0) == 1).all()     # planes disjoint, no gap
+        npr = nnb // rounds
+        for b in range(nnb):
+            rr, n = b // npr, b % npr
+            for s in range(ks):
+                for ln in range(64):
+                    q, i = ln >> 4, ln & 15
+                    unit = (n * ks + s) * 64 + ln
+                    want_k = (32 * s + 8 * q if k is not None and (k == 32 * kk + 8 * g + e).all()
+                              else (C // 4) * q + 8 * s) + np.arange(8)
+                    for plane in range(3):
+                        at = 3 * part * rr + 8 * (unit + plane * npr * ks * 64) + np.arange(8)
+                        assert np.array_equal(where[plane, at], want_k * C + 16 * b + i)
+    # the X fragment: piece p of group q covers channels 32 (p/2) + 8 q + 4 (p%2) + [0, 4),
+    # so value 8 kk + e of a lane is channel 32 kk + 8 q + e
+    for q in range(4):
+        ch = [32 * (p >> 1) + 8 * q + 4 * (p & 1) + t for p in range(C // 16) for t in range(4)]
+        assert ch == [32 * s + 8 * q + t for s in range(ks) for t in range(8)]
