@@ -878,7 +878,7 @@ outer_fwd_kernel2(const T *__restrict__ x, float *__restrict__ ws, uint32_t nval
 // and stored, since one 1024-thread workgroup per CU leaves no other
 // workgroup to cover the load latency.  With two operands (x1, ws1 not
 // null) tiles ntiles.. 2 ntiles - 1 are those of x1, as in outer_fwd2_kernel2.
-template <int HB, int R>
+template <int HB, int R, bool LIVE>
 __global__ void __launch_bounds__(1 << (15 - VB))
 outer_fwd_kernel2_pf(const __bf16 *__restrict__ x0, float *__restrict__ ws0,
                      const __bf16 *__restrict__ x1, float *__restrict__ ws1, uint32_t nvalid,
@@ -931,9 +931,11 @@ outer_fwd_kernel2_pf(const __bf16 *__restrict__ x0, float *__restrict__ ws0,
         const uint32_t hi = blk & ((1u << HB) - 1u);
         const __bf16 *x = second ? x1 : x0;
         float *ws = second ? ws1 : ws0;
-        if (tile_valid<A>(nvalid, hi) == 0) {   // wholly padding (uniform per workgroup)
-            have = t + gridDim.x < total && issue(t + gridDim.x);
-            continue;
+        if constexpr (LIVE) {
+            if (tile_valid<A>(nvalid, hi) == 0) {   // wholly padding (uniform per workgroup)
+                have = t + gridDim.x < total && issue(t + gridDim.x);
+                continue;
+            }
         }
         float v0[V], v1[V];
         if (have) {
@@ -1054,10 +1056,12 @@ hipError_t launch_outer_fwd(const T *x, float *ws, int64_t B, uint32_t nvalid, h
         if constexpr (sizeof(T) == 2 && VW == 3) {
             if (vec) {
                 const uint32_t ntiles = (uint32_t)(B << sp.HB);
-                hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R>),
-                                   dim3(ntiles < 256u ? ntiles : 256u), block, 0, st, x, ws,
-                                   (const __bf16 *)nullptr, (float *)nullptr, nvalid, ntiles);
-                return hipGetLastError();
+                return with_live(live_tiles(nvalid, sp.A), sp.HB, [&](auto l) {
+                    hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R, decltype(l)::value>),
+                                       dim3(ntiles < 256u ? ntiles : 256u), block, 0, st, x, ws,
+                                       (const __bf16 *)nullptr, (float *)nullptr, nvalid, ntiles);
+                    return hipGetLastError();
+                });
             }
         }
         if (vec)
@@ -1091,10 +1095,12 @@ hipError_t launch_outer_fwd2(const T *x, const T *dy, float *wsx, float *wsd, in
         if constexpr (sizeof(T) == 2 && VW == 3) {
             if (vec) {
                 const uint32_t ntiles = (uint32_t)(B << sp.HB);
-                hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R>),
-                                   dim3(2u * ntiles < 256u ? 2u * ntiles : 256u), block, 0, st, x,
-                                   wsx, dy, wsd, nvalid, ntiles);
-                return hipGetLastError();
+                return with_live(live_tiles(nvalid, sp.A), sp.HB, [&](auto l) {
+                    hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R, decltype(l)::value>),
+                                       dim3(2u * ntiles < 256u ? 2u * ntiles : 256u), block, 0, st,
+                                       x, wsx, dy, wsd, nvalid, ntiles);
+                    return hipGetLastError();
+                });
             }
         }
         if (vec)
