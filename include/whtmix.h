@@ -287,10 +287,11 @@ WHTMIX_API int whtmix_backward_separable(const void *x, const void *dy,
  * residual below 2^-17), and y is rounded to nearest even once.  For
  * 16 <= C <= 128, and for bf16 C = 256 from N_pad*C = 2^17, the projections
  * run on the matrix cores inside the mixer's first and last kernels (three
- * kernels plus a small weight-repacking kernel for N_pad*C > 2^15;
+ * kernels for N_pad*C > 2^15, plus a small weight-repacking kernel for C = 256;
  * whtmix_plan_describe's module_path says which); other shapes run separate
  * projection kernels around the float32 mixer.  Workspace: the mixer's, plus
- * 2*C*C elements of packed weights or B*N*C floats of Z.  Other conventions, plans and options as
+ * 2*C*C elements of packed weights (C = 256, and the separate kernels) and
+ * B*N*C floats of Z (the separate kernels).  Other conventions, plans and options as
  * whtmix_forward_ex (events: for the three-pass plan around each of its
  * three passes, otherwise [0] before and [1] after the call's kernels).
  */
@@ -333,10 +334,10 @@ WHTMIX_API int whtmix_module_forward_separable(const void *x, const void *w_in,
  * No output may overlap an input or another output (except dx == dy); B*N <
  * 2^31.  Weight gradients are summed over row chunks in a fixed order, so
  * results are bitwise reproducible.  Workspace: the mixer's backward
- * workspace, 3*C*C packed weight elements and the weight-gradient partial
- * sums; where the projections or the weight gradients run apart from the
+ * workspace and the weight-gradient partial sums; where the projections or the weight gradients run apart from the
  * mixer's passes (any other shape, C = 16 on 2^24 and 2^25 elements, C = 128 on
- * 2^16 and 2^17, and C = 256) 3*B*N*C floats and the forward workspace besides.  Other conventions as
+ * 2^16 and 2^17, and C = 256) 3*B*N*C floats and the forward workspace besides,
+ * and 3*C*C packed weight elements.  Other conventions as
  * whtmix_module_forward (events: [0] before, then after each phase: [1]
  * dW_out, [2] the mixer's gradients, [3] dX and dW_in; with the projections
  * inside the mixer's passes [1] the gain gradient, [2] dW_out (and dW_in

@@ -532,9 +532,12 @@ int module_impl(const void *x, const void *w_in, int gain_kind, const float *gai
     const int path = whtmix::module_path(c.plan, cbits, dtype, c.K);
     // workspace: mixer (THREE_PASS), then packed weights or Z, 256-byte aligned
     const int64_t mix = path == whtmix::MODULE_SMALL ? 0 : c.ws_bytes;
-    // FUSED_MFMA: the packed weights; UNFUSED: Z, then the packed weights
+    // FUSED_MFMA with C = 256: the packed weights; UNFUSED: Z, then the packed weights
     const int64_t zbytes = path == whtmix::MODULE_UNFUSED ? (B * N * C * 4 + 255) / 256 * 256 : 0;
-    const int64_t extra = path == whtmix::MODULE_SMALL ? 0 : zbytes + 2 * whtmix::module_packed_bytes(cbits, dtype);
+    const int64_t extra =
+        zbytes + (whtmix::module_packs_weights(path, cbits)
+                      ? 2 * whtmix::module_packed_bytes(cbits, dtype)
+                      : 0);
     const int64_t off = (mix + 255) / 256 * 256;
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     float *ws = nullptr;
@@ -636,10 +639,13 @@ int module_backward_impl(const void *x, const void *w_in, int gain_kind, const f
     // (with the weight gradients inside the fused backward's last pass, no Z,
     // Z', dZ' and no forward workspace)
     const int64_t rows = B * N;
-    m.tiles = whtmix::module_backward_fused_call(m) && c.K <= 25 &&
+    const bool fused = whtmix::module_backward_fused_call(m);
+    m.tiles = fused && c.K <= 25 &&
               whtmix::wgrad_tiles_shape(whtmix::module_split(c.K).A, cbits);
     const int64_t zb = m.tiles ? 0 : align256(rows * C * 4);
-    const int64_t pk = align256(3 * whtmix::module_packed_bytes(cbits, dtype));
+    const int64_t pk = fused && cbits <= whtmix::kModuleMfmaMaxCbits
+                           ? 0
+                           : align256(3 * whtmix::module_packed_bytes(cbits, dtype));
     const whtmix::WgradPlan wp = whtmix::wgrad_plan((uint64_t)rows, cbits);
     const int64_t part =
         m.tiles ? align256(2 * (int64_t)whtmix::wgrad_tiles_parts(c.K, cbits, dtype, B, m.nvalid) * C * C * 4)

@@ -41,18 +41,20 @@ inline int module_outer_bits(int path, int cbits, int K)
     return three_pass_split(K).A;   // UNFUSED: the mixer's own plan
 }
 
-// Bytes of one repacked weight matrix: the float32 products of 32 <= C <= 128
-// inside the mixer's kernels take three bf16 planes, the others the matrix.
+// Bytes of one repacked weight matrix.  The projections inside the mixer's
+// kernels up to C = 128 read the weights as they lie in memory.
 inline int64_t module_packed_bytes(int cbits, int dtype)
 {
-    const int64_t cc = int64_t(1) << (2 * cbits);
-    if (dtype == DTYPE_BF16) return 2 * cc;
-    return cbits >= 5 && cbits <= kModuleMfmaMaxCbits ? 6 * cc : 4 * cc;
+    return int64_t(dtype == DTYPE_BF16 ? 2 : 4) << (2 * cbits);
+}
+inline bool module_packs_weights(int path, int cbits)
+{
+    return path == MODULE_UNFUSED || (path == MODULE_FUSED_MFMA && cbits > kModuleMfmaMaxCbits);
 }
 
 // A validated call of the block.  Workspace: the THREE_PASS workspace `ws`
 // (B * 2^K floats, else none), then for UNFUSED `z` (B * N * C floats), then
-// `wpack` (the two repacked weight matrices; not SMALL).
+// `wpack` (the two repacked weight matrices, where module_packs_weights).
 struct ModuleArgs {
     const void *x;
     const void *w_in;       // [C][C], dtype of x
@@ -207,7 +209,8 @@ hipError_t launch_wgrad_tiles(const WgradTilesArgs &a);
 // A validated backward call of the block.  Workspace pieces (floats unless
 // noted): z, zp, dzp [B*N*C] (Z = X W_in, Z' = mixer(Z), dZ' then dZ; unused
 // and absent with `tiles`);
-// wpack: W_in, W_out^T and W_in^T packed (3*C*C elements of the dtype);
+// wpack: W_in, W_out^T and W_in^T packed (3*C*C elements of the dtype; absent
+// where the fused backward runs with C <= 128);
 // wpart: the weight gradients' partial sums (wgrad_plan, or
 // wgrad_tiles_parts with `tiles`); mix_ws: the
 // THREE_PASS workspace (B * 2^K, else none); bwd_ws: the mixer backward's

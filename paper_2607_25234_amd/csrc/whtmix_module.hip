@@ -23,9 +23,9 @@
 // no extra LDS pass.  The epilogue computes Y^T = W_out^T Z'^T, whose right
 // operand wants lane j on a token and lanes q on channel groups; the last
 // inverse exchange delivers that "epilogue layout" directly (Epi below).
-// The weights are repacked once per call into the MFMA operand order, staged
-// whole into LDS by each workgroup and read as one 8- or 16-byte LDS load per
-// lane per MFMA.
+// Each workgroup repacks the weights into the MFMA operand order on their way to
+// LDS (RawWeights; the pair kernels of C = 256 read a matrix repacked once per
+// call), and an MFMA operand is one 8- or 16-byte LDS load per lane.
 //
 // Plans (the mixer's, whtmix_plan.h):
 //   FUSED       K <= 15: one workgroup per slice, prologue + mixer + epilogue.
@@ -36,7 +36,7 @@
 //   UNFUSED     any other shape: projection kernels around the fp32 mixer (on
 //               the matrix cores from C = 256 where a weight slice fits LDS).
 // The block's backward fuses its projections into the mixer backward's
-// passes for bf16 32 <= C <= 128 (module_backward_fused_k).
+// passes (module_backward_fused_k).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -268,8 +268,9 @@ pack_weights_kernel(const T *__restrict__ w_in, const T *__restrict__ w_out, T *
 // group g is channels 32 kk + 8 g + [0, 8) of x, one 16-byte load) and
 // W_out[(C/4) g + 8 kk + e][oc_bf16(C, nb, j)] (A operand of Y^T = W_out^T Z'^T:
 // lane group g holds channels [g C/4, (g+1) C/4) of Z').  The block's backward
-// packs transposed matrices in the same orders (dZ' = dY W_out^T through the
-// prologue, dX = dZ W_in^T through the epilogue).
+// takes transposed matrices in the same orders (dZ' = dY W_out^T through the
+// prologue, dX = dZ W_in^T through the epilogue).  The kernel packs for the pair
+// kernels of C = 256; up to C = 128 RawWeights puts them in the same order.
 enum PackMode { PACK_PROLOGUE = 0, PACK_EPILOGUE = 1, PACK_PROLOGUE_T = 2, PACK_EPILOGUE_T = 3 };
 
 __device__ __forceinline__ uint32_t pack_x32_source(uint32_t idx, uint32_t C, int mode)
@@ -287,13 +288,11 @@ __device__ __forceinline__ uint32_t pack_x32_source(uint32_t idx, uint32_t C, in
 
 // Up to three packings in one launch: p[i] = w[i] packed in mode[i] for the
 // entries whose p[i] is not null.
-template <typename T>
-struct PackJobs {
-    const T *w[3];
-    T *p[3];
+struct PackX32Jobs {
+    const __bf16 *w[3];
+    __bf16 *p[3];
     int mode[3];
 };
-using PackX32Jobs = PackJobs<__bf16>;
 
 __global__ void __launch_bounds__(256)
 pack_x32_kernel(PackX32Jobs jobs, int cb)
@@ -329,19 +328,6 @@ __device__ __forceinline__ uint32_t pack_std_source(uint32_t idx, uint32_t C, in
     return mode >= PACK_PROLOGUE_T ? col * C + k : k * C + col;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256)
-pack_std_kernel(PackJobs<T> jobs, int cb)
-{
-    const uint32_t C = 1u << cb;
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-    if (idx >= C * C) return;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        if (jobs.p[i])
-            jobs.p[i][idx] = jobs.w[i][pack_std_source<T>(idx, C, jobs.mode[i])];
-}
-
 // Three-term bf16 split of two floats, v = hi + mid + lo + d, each term the
 // nearest bf16 of what the previous ones leave: |mid| <= 2^-8 |v|, |lo| <= 2^-17
 // |v|, |d| <= 2^-26 |v|.
@@ -360,37 +346,9 @@ __device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, ui
     lo = cvt(r0 - f32(mid << 16), r1 - f32(mid & 0xffff0000u));
 }
 
-// float32 weights from C = 32: the order of pack_x32_kernel (but the epilogue's
-// column m of block nb is 16 nb + m) in three bf16 planes per column part:
-// part r holds column blocks [r NNB / ROUNDS, ...), plane by plane.
-__global__ void __launch_bounds__(256)
-pack_x3_kernel(PackJobs<float> jobs, int cb, uint32_t rounds)
-{
-    const uint32_t C = 1u << cb;
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-    if (idx >= C * C) return;
-    const uint32_t e = idx & 7u, lane = (idx >> 3) & 63u;
-    const uint32_t j = lane & 15u, g = lane >> 4;
-    const uint32_t ks = C / 32u;
-    const uint32_t kk = (idx >> 9) % ks, nb = (idx >> 9) / ks;
-    const uint32_t col = 16u * nb + j;
-    const uint32_t part = C * C / rounds, r = idx / part;
-    const uint32_t dst = idx + 2u * part * r;   // 3 part r + (idx - part r)
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        if (!jobs.p[i]) continue;
-        const int mode = jobs.mode[i];
-        const bool pro = mode == PACK_PROLOGUE || mode == PACK_PROLOGUE_T;
-        const uint32_t k = pro ? 32u * kk + 8u * g + e : (C / 4u) * g + 8u * kk + e;
-        const float w = jobs.w[i][mode >= PACK_PROLOGUE_T ? col * C + k : k * C + col];
-        uint32_t hi, mid, lo;
-        split3_pair(w, 0.0f, hi, mid, lo);
-        unsigned short *d = reinterpret_cast<unsigned short *>(jobs.p[i]) + dst;
-        d[0] = (unsigned short)hi;
-        d[part] = (unsigned short)mid;
-        d[2u * part] = (unsigned short)lo;
-    }
-}
+// float32 weights from C = 32 are in the order of pack_x32_kernel (but the
+// epilogue's column m of block nb is 16 nb + m), in three bf16 planes per column
+// part: part r holds column blocks [r NNB / ROUNDS, ...), plane by plane.
 
 // acc = a b over ks k steps, both in three terms: the six products down to
 // 2^-25 of the largest, below float32's own rounding; the leading products
@@ -440,50 +398,43 @@ __device__ __forceinline__ uint32_t prologue_token(uint32_t rb, uint32_t m, uint
 }
 
 // Loads the lane's X fragments from a tile of `valid` elements (a multiple of
-// C); rows past it read as zero.  Rows are masked explicitly (the range check
-// of a buffer access is not relied on: part of each offset is in soffset).
+// C); rows past it read as zero.  The whole offset is in the vector operand, for
+// the bounds check leaves out the scalar one.  No load sits in a branch: the
+// compiler would count it as perhaps not issued, and a wait for the weights'
+// loads ahead of it would wait for x too.
 template <typename T, int CB>
 __device__ __forceinline__ void load_x_frags(XFrag<T, CB> &f, const T *tile, uint32_t valid,
-                                             bool whole, uint32_t tau)
+                                             uint32_t tau)
 {
     using P = Proj<T, CB>;
     const uint32_t lane = tau & 63u, w = tau >> 6;
     const uint32_t i = lane & 15u, q = lane >> 4;
     const __amdgpu_buffer_rsrc_t r = buffer(tile, valid * (uint32_t)sizeof(T));
-    const uint32_t tok0 = prologue_token<CB>(0, i, w);
-    const uint32_t row = tok0 * (uint32_t)(P::C * sizeof(T));
+    const uint32_t row = prologue_token<CB>(0, i, w) * (uint32_t)(P::C * sizeof(T));
     constexpr uint32_t rb_bytes = 4u * P::C * sizeof(T);
 #pragma unroll
     for (int rb = 0; rb < P::NRB; ++rb) {
-        const bool ok = whole || (tok0 + 4u * rb) * (uint32_t)P::C < valid;
         if constexpr (P::BF) {
             if constexpr (P::C >= 32) {
 #pragma unroll
-                for (int p = 0; p < P::C / 32; ++p) {   // channels 32 p + 8 q + [0, 8)
-                    u32x4 d = {0u, 0u, 0u, 0u};
-                    if (ok)
-                        d = __builtin_amdgcn_raw_buffer_load_b128(r, row + 16u * q,
-                                                                  rb * rb_bytes + 64u * p,
-                                                                  kStreaming);
-                    f.a[rb][p] = __builtin_bit_cast(bf16x8, d);
-                }
+                for (int p = 0; p < P::C / 32; ++p)   // channels 32 p + 8 q + [0, 8)
+                    f.a[rb][p] = __builtin_bit_cast(
+                        bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                    r, row + 16u * q + (rb * rb_bytes + 64u * p), 0, kStreaming));
             } else {
-                u32x2 d = {0u, 0u};
-                if (ok)
-                    d = __builtin_amdgcn_raw_buffer_load_b64(r, row + 8u * q, rb * rb_bytes,
-                                                             kStreaming);
-                f.a[rb][0] = __builtin_bit_cast(bf16x4, d);
+                f.a[rb][0] = __builtin_bit_cast(
+                    bf16x4, __builtin_amdgcn_raw_buffer_load_b64(r, row + 8u * q + rb * rb_bytes,
+                                                                 0, kStreaming));
             }
         } else {
 #pragma unroll
             for (int p = 0; p < P::C / 16; ++p) {
-                u32x4 d = {0u, 0u, 0u, 0u};
                 // X3: channels 32 (p / 2) + 8 q + 4 (p % 2) + [0, 4)
-                if (ok)
-                    d = __builtin_amdgcn_raw_buffer_load_b128(
-                        r, row + (P::X3 ? 32u : 16u) * q,
-                        rb * rb_bytes + (P::X3 ? 128u * (p >> 1) + 16u * (p & 1) : 64u * p),
-                        kStreaming);
+                const u32x4 d = __builtin_amdgcn_raw_buffer_load_b128(
+                    r,
+                    row + (P::X3 ? 32u : 16u) * q +
+                        (rb * rb_bytes + (P::X3 ? 128u * (p >> 1) + 16u * (p & 1) : 64u * p)),
+                    0, kStreaming);
                 // Cast the whole vector: this compiler reads element 0 for a
                 // __builtin_bit_cast of a single ext-vector element (d.y etc.).
                 const f32x4 fv = __builtin_bit_cast(f32x4, d);
@@ -505,23 +456,33 @@ __device__ __forceinline__ void project_in(float (&v)[V], const XFrag<T, CB> &f,
     using P = Proj<T, CB>;
     const uint32_t lane = tau & 63u;
     if constexpr (P::X32) {
-        const bf16x8 *wb = static_cast<const bf16x8 *>(wl);
+        // the next column block's operands are read while this one's products
+        // run (left to itself the compiler waits for each pair of reads)
+        const bf16x8 *wb = static_cast<const bf16x8 *>(wl) + lane;
+        bf16x8 b[2][P::KS2];
+#pragma unroll
+        for (int kk = 0; kk < P::KS2; ++kk)
+            b[0][kk] = wb[kk * 64];
 #pragma unroll
         for (int nb = 0; nb < P::NNB; ++nb) {
-            bf16x8 b[P::KS2];
+            if (nb + 1 < P::NNB) {
 #pragma unroll
-            for (int kk = 0; kk < P::KS2; ++kk)
-                b[kk] = wb[(nb * P::KS2 + kk) * 64 + lane];
+                for (int kk = 0; kk < P::KS2; ++kk)
+                    b[(nb + 1) & 1][kk] = wb[((nb + 1) * P::KS2 + kk) * 64];
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int rb = 0; rb < P::NRB; ++rb) {
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int kk = 0; kk < P::KS2; ++kk)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[rb][kk], b[kk], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[rb][kk], b[nb & 1][kk], acc,
+                                                                  0, 0, 0);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     v[nb | (r << (CB - 4)) | (rb << (CB - 2))] = acc[r];
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
     } else if constexpr (P::BF) {
         const bf16x4 *wb = static_cast<const bf16x4 *>(wl);
@@ -623,16 +584,29 @@ __device__ __forceinline__ void project_out(const float (&v)[V], const void *wl,
                 hi[kk] = __builtin_bit_cast(bf16x8, h2);
                 lo[kk] = __builtin_bit_cast(bf16x8, l2);
             }
+            // reads ahead of the products, as in project_in
             f32x4 acc[P::NNB];
+            bf16x8 a[2][P::KS2];
+#pragma unroll
+            for (int kk = 0; kk < P::KS2; ++kk)
+                a[0][kk] = wb[kk * 64 + lane];
 #pragma unroll
             for (int nb = 0; nb < P::NNB; ++nb) {
+                if (nb + 1 < P::NNB) {
+#pragma unroll
+                    for (int kk = 0; kk < P::KS2; ++kk)
+                        a[(nb + 1) & 1][kk] = wb[((nb + 1) * P::KS2 + kk) * 64 + lane];
+                }
+                __builtin_amdgcn_sched_barrier(0);
                 acc[nb] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int kk = 0; kk < P::KS2; ++kk) {
-                    const bf16x8 a = wb[(nb * P::KS2 + kk) * 64 + lane];
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi[kk], acc[nb], 0, 0, 0);
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo[kk], acc[nb], 0, 0, 0);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nb & 1][kk], hi[kk],
+                                                                      acc[nb], 0, 0, 0);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nb & 1][kk], lo[kk],
+                                                                      acc[nb], 0, 0, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
             // the row block's token; MFMAs above run with every lane active
             const bool ok = whole || (tok0 + ((uint32_t)rb << (M - 7))) * (uint32_t)P::C < valid;
@@ -767,7 +741,6 @@ struct Lds {
     static constexpr bool PARTS = Proj<T, CB>::W_ROUNDS > 1;
     static constexpr bool PREFETCH_OK = CHUNKS % NT == 0 && CHUNKS / NT <= 8;
     static constexpr bool SEPARATE = !PARTS && (TILE + W <= 80u * 1024u || !PREFETCH_OK);
-    static constexpr uint32_t PER = PREFETCH_OK ? CHUNKS / NT : 1;
     static constexpr uint32_t REGION0 = TILE > W ? TILE : W;   // tile, or weights first
     static constexpr uint32_t fwd_bytes() { return REGION0; }
     static constexpr uint32_t inv_bytes() { return SEPARATE ? TILE + W : REGION0; }
@@ -807,6 +780,170 @@ __device__ __forceinline__ void stage_weights_dma(void *lds, const void *w, uint
             static_cast<char *>(lds) + 16u * (wave * 64u + i * NT), 16, 0, 0);
 }
 
+// W as it lies in memory, into LDS in operand order: the fused kernels
+// repack the weights themselves.  A packing launch ahead of them cost 3 to 5 us
+// of every call, twice per training step (block of 1 x 50176 x 64 bf16 34.4 -> 31.7
+// us, training step of 2 x 36864 x 64 float32 140.1 -> 133.4 us).
+// A unit is what a thread loads and repacks at a time, always 16 or 32 bytes:
+//   * the operand's k runs along W's rows (MODE *_T): one 16-byte piece of 8
+//     bf16 (two of 4 floats), units in packed order;
+//   * k runs down W's columns: 8 rows of one dword (two bf16 columns, or one
+//     float column), consecutive lanes on consecutive columns, so that a load
+//     covers whole lines; the rows are put together in registers.
+// float32 values (C >= 32) are split into the three planes on the way.  UNITS
+// of a part are dealt to threads tau, tau + NT, ...; load() and write() are
+// apart so that an epilogue can hold the words until its LDS is free.
+template <typename T, int CB, PackMode MODE, uint32_t NT>
+struct RawWeights {
+    using P = Proj<T, CB>;
+    static constexpr uint32_t C = 1u << CB, KS2 = P::KS2;
+    static constexpr bool TR = MODE >= PACK_PROLOGUE_T;
+    static constexpr bool PRO = MODE == PACK_PROLOGUE || MODE == PACK_PROLOGUE_T;
+    static constexpr bool STD = C < 32;                // element order of pack_std_source
+    static constexpr uint32_t COLS = C / P::W_ROUNDS;  // columns of a part
+    static constexpr uint32_t UNITS =
+        STD ? C * C : (!TR && P::BF ? C * C / 16u : COLS * C / 8u);
+    static constexpr uint32_t WORDS = STD ? 1u : (TR && P::BF ? 4u : 8u);
+    static constexpr uint32_t PER = (UNITS + NT - 1u) / NT;
+    uint32_t raw[PER][WORDS];
+
+    // Octet o of k values: where it starts, and its step kk and lane group g.
+    static __device__ uint32_t octet_kk(uint32_t o) { return PRO ? o / 4u : o % KS2; }
+    static __device__ uint32_t octet_g(uint32_t o) { return PRO ? o % 4u : o / KS2; }
+    // Row m of column block nb -> column of the operand, and back.  Only the
+    // bf16 epilogue permutes.
+    static constexpr bool PERM = P::BF && !PRO;
+    static __device__ uint32_t column(uint32_t nb, uint32_t m)
+    {
+        return PERM ? oc_bf16(C, nb, m) : 16u * nb + m;
+    }
+    static __device__ void locate(uint32_t col, uint32_t &nb, uint32_t &m)
+    {
+        nb = PERM ? 2u * (col / 32u) + ((col >> 2) & 1u) : col / 16u;
+        m = PERM ? ((col >> 3) & 3u) * 4u + (col & 3u) : col % 16u;
+    }
+    // 16-byte chunk of (nb, kk, lane 16 g + m)
+    static __device__ uint32_t chunk(uint32_t nb, uint32_t kk, uint32_t g, uint32_t m)
+    {
+        return (nb * KS2 + kk) * 64u + 16u * g + m;
+    }
+
+    __device__ __forceinline__ void load(const T *w, uint32_t tau, uint32_t part = 0)
+    {
+#pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            const uint32_t u = tau + i * NT;
+            if (UNITS % NT != 0 && u >= UNITS) break;
+            if constexpr (STD) {
+                const T e = w[pack_std_source<T>(u, C, MODE)];
+                if constexpr (P::BF)
+                    raw[i][0] = __builtin_bit_cast(unsigned short, e);
+                else
+                    raw[i][0] = __builtin_bit_cast(uint32_t, e);
+            } else if constexpr (TR) {
+                const uint32_t lane = u & 63u, kk = (u >> 6) % KS2;
+                const uint32_t nb = (u >> 6) / KS2 + part * (COLS / 16u);
+                const uint32_t g = lane >> 4;
+                const uint32_t k0 = PRO ? 32u * kk + 8u * g : (C / 4u) * g + 8u * kk;
+                const u32x4 *src =
+                    reinterpret_cast<const u32x4 *>(w + column(nb, lane & 15u) * C + k0);
+#pragma unroll
+                for (uint32_t e = 0; e < WORDS / 4u; ++e) {
+                    const u32x4 d = src[e];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k)
+                        raw[i][4u * e + k] = d[k];
+                }
+            } else {
+                constexpr uint32_t PW = P::BF ? 2u : 1u;   // columns per dword
+                const uint32_t o = u / (COLS / PW), cp = u % (COLS / PW);
+                const uint32_t *src = reinterpret_cast<const uint32_t *>(
+                    w + 8u * o * C + part * COLS + PW * cp);
+#pragma unroll
+                for (uint32_t e = 0; e < 8u; ++e)
+                    raw[i][e] = src[e * (C / PW)];
+            }
+        }
+    }
+
+    __device__ __forceinline__ void write(void *lds, uint32_t tau)
+    {
+        u32x4 *d = static_cast<u32x4 *>(lds);
+#pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            const uint32_t u = tau + i * NT;
+            if (UNITS % NT != 0 && u >= UNITS) break;
+            const uint32_t *r = raw[i];
+            if constexpr (STD) {
+                if constexpr (P::BF)
+                    static_cast<unsigned short *>(lds)[u] = (unsigned short)r[0];
+                else
+                    static_cast<uint32_t *>(lds)[u] = r[0];
+            } else if constexpr (P::BF && TR) {
+                d[u] = (u32x4){r[0], r[1], r[2], r[3]};
+            } else if constexpr (P::BF) {
+                const uint32_t o = u / (C / 2u), cp = u % (C / 2u);
+                uint32_t nb, m;
+                locate(2u * cp, nb, m);
+                u32x4 a, b;
+#pragma unroll
+                for (uint32_t e = 0; e < 4u; ++e) {
+                    a[e] = (r[2u * e] & 0xffffu) | (r[2u * e + 1u] << 16);
+                    b[e] = (r[2u * e] >> 16) | (r[2u * e + 1u] & 0xffff0000u);
+                }
+                const uint32_t c = chunk(nb, octet_kk(o), octet_g(o), m);
+                // half of each 8 lanes write their second column first, so that
+                // the 8 pieces of an LDS cycle fall on different banks
+                const bool swap = cp & (PRO ? 4u : 2u);
+                d[c + (swap ? 1u : 0u)] = swap ? b : a;
+                d[c + (swap ? 0u : 1u)] = swap ? a : b;
+            } else {
+                u32x4 h, m, l;
+#pragma unroll
+                for (uint32_t e = 0; e < 4u; ++e) {
+                    uint32_t x, y, z;
+                    split3_pair(__builtin_bit_cast(float, r[2u * e]),
+                                __builtin_bit_cast(float, r[2u * e + 1u]), x, y, z);
+                    h[e] = x;
+                    m[e] = y;
+                    l[e] = z;
+                }
+                uint32_t c = u;
+                if constexpr (!TR) {
+                    const uint32_t o = u / COLS, col = u % COLS;   // within the part
+                    c = chunk(col / 16u, octet_kk(o), octet_g(o), col % 16u);
+                }
+                constexpr uint32_t PLANE = COLS * C / 8u;
+                d[c] = h;
+                d[c + PLANE] = m;
+                d[c + 2u * PLANE] = l;
+            }
+        }
+    }
+};
+
+// Part `part` of W (of W^T with `trans`, uniform) into LDS; `then` issues loads
+// behind the weights'.
+struct Nothing {
+    __device__ void operator()() const {}
+};
+template <typename T, int CB, bool PRO, uint32_t NT, class F = Nothing>
+__device__ __forceinline__ void stage_raw(void *lds, const T *w, bool trans, uint32_t tau,
+                                          uint32_t part = 0, F &&then = F{})
+{
+    if (trans) {
+        RawWeights<T, CB, PRO ? PACK_PROLOGUE_T : PACK_EPILOGUE_T, NT> r;
+        r.load(w, tau, part);
+        then();
+        r.write(lds, tau);
+    } else {
+        RawWeights<T, CB, PRO ? PACK_PROLOGUE : PACK_EPILOGUE, NT> r;
+        r.load(w, tau, part);
+        then();
+        r.write(lds, tau);
+    }
+}
+
 // The projections of float32 from C = 32.  Against the fp32 instruction the six
 // bf16 products take 3/8 of the matrix-unit cycles.
 template <int KS2>
@@ -832,7 +969,7 @@ __device__ __forceinline__ void split_x3(bf16x8 (&a0)[KS2], bf16x8 (&a1)[KS2], b
 
 template <int CB, uint32_t NT>
 __device__ __forceinline__ void project_in_x3(float (&v)[V], const XFrag<float, CB> &f, float *lds,
-                                              const float *w, uint32_t tau)
+                                              const float *w, bool trans, uint32_t tau)
 {
     using P = Proj<float, CB>;
     constexpr int KS2 = P::KS2, NPR = P::NNB / P::W_ROUNDS;   // column blocks of a part
@@ -841,11 +978,10 @@ __device__ __forceinline__ void project_in_x3(float (&v)[V], const XFrag<float, 
     bf16x8 a0[P::NRB][KS2], a1[P::NRB][KS2], a2[P::NRB][KS2];
 #pragma unroll
     for (int r = 0; r < P::W_ROUNDS; ++r) {
-        if (r > 0)
+        if (r > 0) {   // the caller staged the first part
             __syncthreads();   // the previous part's readers
-        stage_weights<P::WBYTES / 16u, NT>(
-            lds, reinterpret_cast<const char *>(w) + (size_t)r * P::WBYTES, tau);
-        if (r == 0) {
+            stage_raw<float, CB, true, NT>(lds, w, trans, tau, r);
+        } else {
 #pragma unroll
             for (int rb = 0; rb < P::NRB; ++rb)
                 split_x3<KS2>(a0[rb], a1[rb], a2[rb], f.a[rb]);
@@ -874,9 +1010,9 @@ __device__ __forceinline__ void project_in_x3(float (&v)[V], const XFrag<float, 
     }
 }
 
-// Y = Z' W_out as project_out, the weights either whole in LDS at wl, or (w not
-// null) staged into lds part by part.
-template <int CB, int M, uint32_t NT>
+// Y = Z' W_out as project_out, the weights either whole in LDS at wl, or
+// (W_ROUNDS > 1) staged into lds part by part.
+template <int CB, int M, uint32_t NT, bool TRANS>
 __device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *wl, float *lds,
                                                const float *w, float *tile, uint32_t valid,
                                                uint32_t tau)
@@ -899,8 +1035,7 @@ __device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *
     for (int part = 0; part < P::W_ROUNDS; ++part) {
         if constexpr (P::W_ROUNDS > 1) {
             __syncthreads();   // the last exchange's readers, or the previous part's
-            stage_weights<P::WBYTES / 16u, NT>(
-                lds, reinterpret_cast<const char *>(w) + (size_t)part * P::WBYTES, tau);
+            stage_raw<float, CB, false, NT>(lds, w, TRANS, tau, part);
             __syncthreads();
             wl = lds;
         }
@@ -935,9 +1070,9 @@ __device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *
 // The end of the last kernel: the rest of W_out into LDS and Y = Z' W_out from
 // the epilogue layout.  wregion: W_out staged at kernel start (SEPARATE), else
 // wreg holds it (or, PARTS, it is staged from memory).
-template <typename T, int CB, int M, uint32_t PER>
+template <typename T, int CB, int M, bool TRANS, class WReg>
 __device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const void *wregion,
-                                         [[maybe_unused]] const u32x4 (&wreg)[PER],
+                                         [[maybe_unused]] WReg &wreg,
                                          [[maybe_unused]] const T *w_out, T *tile, uint32_t valid,
                                          uint32_t tau)
 {
@@ -945,15 +1080,13 @@ __device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const 
     const void *wl = wregion;
     if constexpr (!L::SEPARATE && !L::PARTS) {
         __syncthreads();   // every thread has read its epilogue-layout values
-#pragma unroll
-        for (uint32_t i = 0; i < L::PER; ++i)
-            reinterpret_cast<u32x4 *>(lds)[tau + i * L::NT] = wreg[i];
+        wreg.write(lds, tau);
         wl = lds;
     }
     if constexpr (!L::PARTS)
         __syncthreads();
     if constexpr (Proj<T, CB>::X3)
-        project_out_x3<CB, M, L::NT>(v, wl, lds, w_out, tile, valid, tau);
+        project_out_x3<CB, M, L::NT, TRANS>(v, wl, lds, w_out, tile, valid, tau);
     else
         project_out<T, CB, M>(v, wl, tile, valid, tau);
 }
@@ -970,21 +1103,18 @@ module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
     const uint32_t tau = threadIdx.x;
     const size_t base = (size_t)blockIdx.x * nvalid;
     XFrag<T, CB> f;
-    load_x_frags<T, CB>(f, x + base, nvalid, nvalid >= (1u << K), tau);
-    if constexpr (!Proj<T, CB>::X3)
-        stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
-    [[maybe_unused]] u32x4 wreg[L::PER];
-    if constexpr (L::SEPARATE) {
-        stage_weights<L::CHUNKS, L::NT>(region1, w_out, tau);
-    } else if constexpr (!L::PARTS) {
-#pragma unroll
-        for (uint32_t i = 0; i < L::PER; ++i)
-            wreg[i] = static_cast<const u32x4 *>(static_cast<const void *>(w_out))[tau + i * L::NT];
-    }
+    stage_raw<T, CB, true, L::NT>(lds, w_in, false, tau, 0, [&] {
+        load_x_frags<T, CB>(f, x + base, nvalid, tau);
+    });
+    [[maybe_unused]] RawWeights<T, CB, PACK_EPILOGUE, L::NT> wreg;
+    if constexpr (L::SEPARATE)
+        stage_raw<T, CB, false, L::NT>(region1, w_out, false, tau);
+    else if constexpr (!L::PARTS)
+        wreg.load(w_out, tau);
     float v[V], gv[V];
     gain.template load<K - 5, ContigMap>(gv, 0, tau);
     if constexpr (Proj<T, CB>::X3) {
-        project_in_x3<CB, L::NT>(v, f, lds, w_in, tau);
+        project_in_x3<CB, L::NT>(v, f, lds, w_in, false, tau);
     } else {
         __syncthreads();
         project_in<T, CB>(v, f, lds, tau);
@@ -992,15 +1122,16 @@ module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
     forward_from_prologue<K>(lds, v, tau);
     apply_gain<K>(v, gv);
     inverse_to_epilogue<K, CB, true>(lds, v, tau);
-    epilogue<T, CB, K>(v, lds, region1, wreg, w_out, y + base, nvalid, tau);
+    epilogue<T, CB, K, false>(v, lds, region1, wreg, w_out, y + base, nvalid, tau);
 }
 
-// THREE_PASS first pass: prologue, forward over the A low bits, workspace.
+// THREE_PASS first pass: prologue (x W_in, or x W_in^T with trans), forward over
+// the A low bits, workspace.
 template <int A, int HB, int R, typename T, int CB>
 __device__ __forceinline__ void module_outer_fwd_tile(float *lds, const T *__restrict__ x,
                                                       const T *__restrict__ w_in,
-                                                      float *__restrict__ ws, uint32_t nvalid,
-                                                      uint32_t blk)
+                                                      bool trans, float *__restrict__ ws,
+                                                      uint32_t nvalid, uint32_t blk)
 {
     using L = Lds<A, T, CB>;
     using Run = RunMap<HB, R>;
@@ -1011,12 +1142,16 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds, const T *__res
     if (valid == 0)
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     XFrag<T, CB> f;
-    load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, valid >= (1u << A), tau);
+    // The weights come from L2, x from memory: issued first, they are in LDS
+    // by the time x arrives (with project_in's reads ahead, this kernel on 4 x
+    // 65536 x 128 bf16: 48.1 -> 41.9 us).
+    stage_raw<T, CB, true, L::NT>(lds, w_in, trans, tau, 0, [&] {
+        load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, tau);
+    });
     float v[V];
     if constexpr (Proj<T, CB>::X3) {
-        project_in_x3<CB, L::NT>(v, f, lds, w_in, tau);
+        project_in_x3<CB, L::NT>(v, f, lds, w_in, trans, tau);
     } else {
-        stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
         __syncthreads();
         project_in<T, CB>(v, f, lds, tau);
     }
@@ -1031,13 +1166,13 @@ module_outer_fwd_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
                         float *__restrict__ ws, uint32_t nvalid)
 {
     __shared__ __attribute__((aligned(16))) float lds[Lds<A, T, CB>::fwd_bytes() / 4];
-    module_outer_fwd_tile<A, HB, R, T, CB>(lds, x, w_in, ws, nvalid,
+    module_outer_fwd_tile<A, HB, R, T, CB>(lds, x, w_in, false, ws, nvalid,
                                            outer_block<R>(blockIdx.x, gridDim.x));
 }
 
 // Two operands in one launch (the block's backward: Z = X W_in and
-// dZ' = dY W_out^T): the first half of the grid takes (x, wa) into wsx, the
-// second (dy, wb) into wsd, each half numbered as a grid of its own.
+// dZ' = dY W_out^T): the first half of the grid takes x wa into wsx, the
+// second dy wb^T into wsd, each half numbered as a grid of its own.
 template <int A, int HB, int R, typename T, int CB>
 __global__ void __launch_bounds__(1 << (A - VB))
 module_outer_fwd2_kernel(const T *__restrict__ x, const T *__restrict__ wa,
@@ -1048,13 +1183,13 @@ module_outer_fwd2_kernel(const T *__restrict__ x, const T *__restrict__ wa,
     const uint32_t half = gridDim.x >> 1;
     const bool second = blockIdx.x >= half;
     const uint32_t blk = outer_block<R>(blockIdx.x - (second ? half : 0u), half);
-    module_outer_fwd_tile<A, HB, R, T, CB>(lds, second ? dy : x, second ? wb : wa,
+    module_outer_fwd_tile<A, HB, R, T, CB>(lds, second ? dy : x, second ? wb : wa, second,
                                            second ? wsd : wsx, nvalid, blk);
 }
 
-// THREE_PASS last pass: inverse over the A low bits, epilogue, y.  ZOUT: also
-// store the inverse-transformed tile itself (float32) to z.
-template <int A, int HB, int R, typename T, int CB, bool ZOUT = false>
+// THREE_PASS last pass: inverse over the A low bits, epilogue, y.  TRANS: by
+// w_out^T.  ZOUT: also store the inverse-transformed tile itself (float32) to z.
+template <int A, int HB, int R, typename T, int CB, bool TRANS, bool ZOUT = false>
 __global__ void __launch_bounds__(1 << (A - VB))
 module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_out,
                         T *__restrict__ y, float *__restrict__ z, uint32_t nvalid)
@@ -1070,22 +1205,19 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
     const uint32_t valid = tile_valid<A>(nvalid, hi);
     if (valid == 0)
         return;   // wholly padding: nothing to store (uniform per workgroup)
-    [[maybe_unused]] u32x4 wreg[L::PER];
-    if constexpr (L::SEPARATE) {
-        stage_weights<L::CHUNKS, L::NT>(wregion, w_out, tau);
-    } else if constexpr (!L::PARTS) {
-#pragma unroll
-        for (uint32_t i = 0; i < L::PER; ++i)
-            wreg[i] = static_cast<const u32x4 *>(static_cast<const void *>(w_out))[tau + i * L::NT];
-    }
+    [[maybe_unused]] RawWeights<T, CB, TRANS ? PACK_EPILOGUE_T : PACK_EPILOGUE, L::NT> wreg;
+    if constexpr (L::SEPARATE)
+        stage_raw<T, CB, false, L::NT>(wregion, w_out, TRANS, tau);
+    else if constexpr (!L::PARTS)
+        wreg.load(w_out, tau);
     float v[V];
     load_layout<A - 5, Run, float>(
         v, buffer(ws + (b << (A + HB)) + ((size_t)hi << R), extent_bytes<Run, A, float>()), tau);
     inverse_to_epilogue<A, CB, false>(lds, v, tau);
     if constexpr (ZOUT)
         store_epilogue_f32<A, CB>(lds, v, z + b * nvalid + ((size_t)hi << A), valid, tau);
-    epilogue<T, CB, A>(v, lds, wregion, wreg, w_out, y + b * nvalid + ((size_t)hi << A), valid,
-                       tau);
+    epilogue<T, CB, A, TRANS>(v, lds, wregion, wreg, w_out, y + b * nvalid + ((size_t)hi << A),
+                              valid, tau);
 }
 
 // ---------------------------------------------------------------- C = 256 (bf16)
@@ -1695,13 +1827,12 @@ hipError_t launch_pack(const ModuleArgs &m, bool out_as_in)
 template <int K, typename T, class Gain, int CB>
 hipError_t launch_module_fused(const ModuleArgs &m, Gain gain)
 {
-    const uint32_t n = Proj<T, CB>::PACKED;
-    const T *pin = static_cast<const T *>(m.wpack);
     hipError_t e = record(m.events[0], m.stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((module_fused_kernel<K, T, Gain, CB>), dim3((uint32_t)m.B),
-                       dim3(1u << (K - VB)), 0, m.stream, static_cast<const T *>(m.x), pin,
-                       pin + n, static_cast<T *>(m.y), gain, m.nvalid);
+                       dim3(1u << (K - VB)), 0, m.stream, static_cast<const T *>(m.x),
+                       static_cast<const T *>(m.w_in), static_cast<const T *>(m.w_out),
+                       static_cast<T *>(m.y), gain, m.nvalid);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return record(m.events[1], m.stream);
 }
@@ -1730,21 +1861,19 @@ hipError_t launch_module_three_pass(const ModuleArgs &m, Gain gain)
 {
     constexpr Split sp = module_split(K);
     constexpr int A = sp.A, HB = sp.HB, R = sp.R;
-    const uint32_t n = Proj<T, CB>::PACKED;
-    const T *pin = static_cast<const T *>(m.wpack);
     const hipStream_t st = m.stream;
     hipError_t e = record(m.events[0], st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((module_outer_fwd_kernel<A, HB, R, T, CB>), dim3((uint32_t)(m.B << HB)),
-                       dim3(1u << (A - VB)), 0, st, static_cast<const T *>(m.x), pin, m.ws,
-                       m.nvalid);
+                       dim3(1u << (A - VB)), 0, st, static_cast<const T *>(m.x),
+                       static_cast<const T *>(m.w_in), m.ws, m.nvalid);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = record(m.events[1], st)) != hipSuccess) return e;
     if ((e = launch_middle(middle_args(m, false))) != hipSuccess) return e;
     if ((e = record(m.events[2], st)) != hipSuccess) return e;
-    hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB>), dim3((uint32_t)(m.B << HB)),
-                       dim3(1u << (A - VB)), 0, st, m.ws, pin + n, static_cast<T *>(m.y),
-                       nullptr, m.nvalid);
+    hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, false>),
+                       dim3((uint32_t)(m.B << HB)), dim3(1u << (A - VB)), 0, st, m.ws,
+                       static_cast<const T *>(m.w_out), static_cast<T *>(m.y), nullptr, m.nvalid);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return record(m.events[3], st);
 }
@@ -1756,11 +1885,18 @@ hipError_t launch_module_pair(const ModuleArgs &m)
     constexpr Split sp = pair_split(K);
     constexpr int HB = sp.HB, R = sp.R;
     static_assert(sp.A == 16 && HB >= 1, "pair split");
-    const __bf16 *pin = static_cast<const __bf16 *>(m.wpack);
+    __bf16 *pin = static_cast<__bf16 *>(m.wpack);
     const hipStream_t st = m.stream;
     const dim3 grid((uint32_t)(m.B << HB)), block(kPairThreads);
-    hipError_t e = record(m.events[0], st);
+    const PackX32Jobs jobs{{static_cast<const __bf16 *>(m.w_in),
+                            static_cast<const __bf16 *>(m.w_out), nullptr},
+                           {pin, pin + kPairC * kPairC, nullptr},
+                           {PACK_PROLOGUE, PACK_EPILOGUE, 0}};
+    hipLaunchKernelGGL(pack_x32_kernel, dim3(kPairC * kPairC / 256u), dim3(256), 0, st, jobs,
+                       kPairCB);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if ((e = record(m.events[0], st)) != hipSuccess) return e;
     hipLaunchKernelGGL((module_outer_fwd_pair_kernel<HB, R>), grid, block, 0, st,
                        static_cast<const __bf16 *>(m.x), pin, m.ws, m.nvalid);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1818,31 +1954,6 @@ hipError_t dispatch_k(const ModuleArgs &m, Gain gain)
 template <typename T, class Gain>
 hipError_t dispatch_fused_module(const ModuleArgs &m, Gain gain)
 {
-    hipError_t e;
-    if (std::is_same<T, __bf16>::value && m.cbits >= 5) {
-        const uint32_t n = 1u << (2 * m.cbits);
-        const PackX32Jobs jobs{{static_cast<const __bf16 *>(m.w_in),
-                                static_cast<const __bf16 *>(m.w_out), nullptr},
-                               {static_cast<__bf16 *>(m.wpack),
-                                static_cast<__bf16 *>(m.wpack) + n, nullptr},
-                               {PACK_PROLOGUE, PACK_EPILOGUE, 0}};
-        hipLaunchKernelGGL(pack_x32_kernel, dim3((n + 255u) / 256u), dim3(256), 0, m.stream, jobs,
-                           m.cbits);
-        e = hipGetLastError();
-    } else if (std::is_same<T, float>::value && m.cbits >= 5) {
-        const uint32_t n = 1u << (2 * m.cbits);
-        const PackJobs<float> jobs{{static_cast<const float *>(m.w_in),
-                                    static_cast<const float *>(m.w_out), nullptr},
-                                   {static_cast<float *>(m.wpack),
-                                    static_cast<float *>(m.wpack) + n / 2u * 3u, nullptr},
-                                   {PACK_PROLOGUE, PACK_EPILOGUE, 0}};
-        hipLaunchKernelGGL(pack_x3_kernel, dim3((n + 255u) / 256u), dim3(256), 0, m.stream, jobs,
-                           m.cbits, m.cbits == 7 ? 2u : 1u);
-        e = hipGetLastError();
-    } else {
-        e = launch_pack<T>(m, false);
-    }
-    if (e != hipSuccess) return e;
     switch (m.cbits) {
     case 4: return dispatch_k<T, Gain, 4>(m, gain);
     case 5: return dispatch_k<T, Gain, 5>(m, gain);
@@ -2385,26 +2496,11 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
                   "the backward's middle phase runs the mixer's split");
     const hipStream_t st = m.stream;
     [[maybe_unused]] const uint32_t rows = (uint32_t)(((uint64_t)m.B * m.nvalid) >> CB);
-    const uint32_t CC = 1u << (2 * CB);
     const T *x = static_cast<const T *>(m.x);
     const T *dy = static_cast<const T *>(m.dy);
     const T *w_in = static_cast<const T *>(m.w_in);
-    T *pk = static_cast<T *>(m.wpack);
-    constexpr uint32_t PK = Proj<T, CB>::PACKED;
-    T *p_in = pk, *p_out_t = pk + PK, *p_in_te = pk + 2 * PK;
-    const PackJobs<T> jobs{{w_in, static_cast<const T *>(m.w_out), w_in},
-                           {p_in, p_out_t, p_in_te},
-                           {PACK_PROLOGUE, PACK_PROLOGUE_T, PACK_EPILOGUE_T}};
-    if constexpr (Proj<T, CB>::X32)
-        hipLaunchKernelGGL(pack_x32_kernel, dim3((CC + 255u) / 256u), dim3(256), 0, st, jobs, CB);
-    else if constexpr (Proj<T, CB>::X3)
-        hipLaunchKernelGGL(pack_x3_kernel, dim3((CC + 255u) / 256u), dim3(256), 0, st, jobs, CB,
-                           (uint32_t)Proj<T, CB>::W_ROUNDS);
-    else
-        hipLaunchKernelGGL((pack_std_kernel<T>), dim3((CC + 255u) / 256u), dim3(256), 0, st, jobs,
-                           CB);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const T *w_out = static_cast<const T *>(m.w_out);
+    hipError_t e;
     if ((e = record(m.events[0], st)) != hipSuccess) return e;
     const bool separable = m.gain_kind == GAIN_LOG_SEPARABLE;
     const BackwardLayout lay =
@@ -2412,8 +2508,8 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
     float *wsx = m.bwd_ws + lay.wsx;
     float *wsd = m.bwd_ws + lay.wsd;
     hipLaunchKernelGGL((module_outer_fwd2_kernel<A, HB, R, T, CB>),
-                       dim3((uint32_t)(2 * (m.B << HB))), dim3(1u << (A - VB)), 0, st, x, p_in,
-                       dy, p_out_t, wsx, wsd, m.nvalid);
+                       dim3((uint32_t)(2 * (m.B << HB))), dim3(1u << (A - VB)), 0, st, x, w_in,
+                       dy, w_out, wsx, wsd, m.nvalid);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     BackwardArgs g{};
     g.gain_kind = m.gain_kind;
@@ -2453,8 +2549,8 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
         if ((e = launch_wgrad_tiles(w)) != hipSuccess) return e;
         if ((e = record(m.events[2], st)) != hipSuccess) return e;
         // dX = dZ W_in^T last: dX may be dY itself
-        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB>), grid, block, 0, st, wsd,
-                           p_in_te, dx, nullptr, m.nvalid);
+        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true>), grid, block, 0, st,
+                           wsd, w_in, dx, nullptr, m.nvalid);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         if ((e = launch_outer_inv<K, float>(wsx, m.zp, m.B, m.nvalid, st)) != hipSuccess) return e;
@@ -2462,8 +2558,8 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
             return e;
         if ((e = record(m.events[2], st)) != hipSuccess) return e;
         // dZ (float32, for dW_in) and dX = dZ W_in^T from one pass over wsd
-        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true>), grid, block, 0, st,
-                           wsd, p_in_te, dx, m.dzp, m.nvalid);
+        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true, true>), grid, block, 0,
+                           st, wsd, w_in, dx, m.dzp, m.nvalid);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = wgrad<T, float>(x, m.dzp, m.wpart, m.dw_in, rows, CB, st)) != hipSuccess)
             return e;

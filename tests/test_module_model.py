@@ -946,7 +946,7 @@ def test_weight_gradient_model(rows, cb, kinds):
 
 @pytest.mark.parametrize("C,rounds", [(32, 1), (64, 1), (128, 2)])
 def test_float32_split_planes(C, rounds):
-    """pack_x3_kernel and the reads of project_in_x3 / project_out_x3: every
+    """The float32 weight planes and the reads of project_in_x3 / project_out_x3: every
     element of the matrix lands once in each plane of its column part, and the
     operand of (column block, k step, lane) holds the eight k values the other
     operand pairs with (prologue: channels 32 kk + 8 q + e, as the X fragments
@@ -982,3 +982,88 @@ def test_float32_split_planes(C, rounds):
     for q in range(4):
         ch = [32 * (p >> 1) + 8 * q + 4 * (p & 1) + t for p in range(C // 16) for t in range(4)]
         assert ch == [32 * s + 8 * q + t for s in range(ks) for t in range(8)]
+
+
+def stage_raw_model(C, bf, pro, trans, NT):
+    """RawWeights::load and write: LDS contents (per column part) as flat indices
+    into W, one per packed element, from the units' own index arithmetic."""
+    ks = max(C // 32, 1)
+    rounds = 2 if not bf and C == 128 else 1
+    cols = C // rounds
+    perm = bf and not pro
+    parts = []
+    for part in range(rounds):
+        lds = np.full(cols * C, -1)
+        if C < 32:
+            units = C * C
+        elif not trans and bf:
+            units = C * C // 16
+        else:
+            units = cols * C // 8
+        seen = []
+        for i in range((units + NT - 1) // NT):
+            for tau in range(NT):
+                u = tau + i * NT
+                if u < units:
+                    seen.append(u)
+        assert sorted(seen) == list(range(units))
+        for u in range(units):
+            if C < 32:   # pack_std_source
+                e, lane, rest = u & 3, (u >> 2) & 63, u >> 8
+                j, q = lane & 15, lane >> 4
+                if bf:
+                    k = k_in_bf16(C, rest % (C // 16), q, e) if pro else q * (C // 4) + e
+                    col = j
+                else:
+                    s = 4 * rest + e
+                    k = k_in_f32(s, q) if pro else q * (C // 4) + s
+                    col = j
+                lds[u] = col * C + k if trans else k * C + col
+                continue
+            if trans:
+                lane, kk = u & 63, (u >> 6) % ks
+                nb, g = (u >> 6) // ks + part * (cols // 16), lane >> 4
+                col = oc_bf16(C, nb, lane & 15) if perm else 16 * nb + (lane & 15)
+                k0 = 32 * kk + 8 * g if pro else (C // 4) * g + 8 * kk
+                assert (col * C + k0) % 8 == 0          # 16-byte pieces (32 of floats)
+                chunks = [(u, [col * C + k0 + e for e in range(8)])]
+            else:
+                pw = 2 if bf else 1
+                o, cp = u // (cols // pw), u % (cols // pw)
+                kk, g = (o // 4, o % 4) if pro else (o % ks, o // ks)
+                col0 = pw * cp
+                if perm:
+                    nb, m = 2 * (col0 // 32) + ((col0 >> 2) & 1), ((col0 >> 3) & 3) * 4 + (col0 & 3)
+                else:
+                    nb, m = col0 // 16, col0 % 16
+                base = 8 * o * C + part * cols + col0
+                assert base % pw == 0                   # aligned dwords
+                c = (nb * ks + kk) * 64 + 16 * g + m
+                chunks = [(c + h, [base + h + e * C for e in range(8)]) for h in range(pw)]
+            for c, src in chunks:
+                assert (lds[8 * c:8 * c + 8] == -1).all()
+                lds[8 * c:8 * c + 8] = src
+        parts.append(lds)
+    return np.concatenate(parts)
+
+
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("pro", [True, False])
+@pytest.mark.parametrize("C,bf", [(16, True), (16, False), (32, True), (32, False), (64, True),
+                                  (64, False), (128, True), (128, False)])
+def test_weights_staged_as_they_lie(C, bf, pro, trans):
+    """The fused kernels' own repacking puts every element of W (or W^T) where the
+    packed order has it, for the smallest and largest workgroups."""
+    w = np.arange(C * C, dtype=np.float64).reshape(C, C)
+    wt = w.T if trans else w
+    if bf or C < 32:
+        p_in, p_out = pack_fused(wt, wt, bf)
+        want = p_in if pro else p_out
+    else:   # one plane per column part, the epilogue's columns in order
+        idx = np.arange(C * C)
+        e, j, g = idx & 7, (idx >> 3) & 15, (idx >> 7) & 3
+        kk, nb = (idx >> 9) % (C // 32), (idx >> 9) // (C // 32)
+        k = 32 * kk + 8 * g + e if pro else (C // 4) * g + 8 * kk + e
+        want = wt[k, 16 * nb + j]
+    for NT in (64, 1024):
+        assert np.array_equal(stage_raw_model(C, bf, pro, trans, NT), want)
