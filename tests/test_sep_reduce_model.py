@@ -85,6 +85,27 @@ def test_layout_rule_blocks(C, P):
     np.testing.assert_allclose(part.sum(axis=0), (dG * G).sum(axis=0), rtol=1e-12, atol=1e-12)
 
 
+@pytest.mark.parametrize("C,P,chunks", [(1, 3, 2), (16, 100, 5), (64, 1024, 16), (256, 9000, 3)])
+def test_single_pass_sums_of_chunks(C, P, chunks):
+    """The CHUNKS form: one row step per iteration, dG added up from partial sums
+    P * C apart in order, each read once and in range."""
+    rng = np.random.default_rng(P + chunks)
+    part = rng.standard_normal(chunks * P * C)
+    at = np.arange(P * C)
+    dG = part[at].copy()
+    for _ in range(1, chunks):
+        at = at + P * C
+        dG += part[at]
+    assert at[-1] == part.size - 1
+    dG = dG.reshape(P, C)
+    G = rng.uniform(0.5, 1.5, (P, C))
+    dgt, cols, seen = sep_rows_cols_model(dG, G, rows_per_block(P, C), U=1)
+    want = part.reshape(chunks, P, C).sum(axis=0) * G
+    assert np.all(seen == 1)
+    np.testing.assert_allclose(dgt, want.sum(axis=1), rtol=1e-12, atol=1e-12)
+    np.testing.assert_allclose(cols.sum(axis=0), want.sum(axis=0), rtol=1e-12, atol=1e-12)
+
+
 # ---------------------------------------------------------------- fused sums
 def sep_tile_sums_model(p, tau_count, run, chunk, nchunks, A, HB, cbits, rowpart, colpart,
                         writes):
