@@ -119,8 +119,8 @@ OPS = ("forward", "separable", "backward", "backward_separable", "module", "modu
 
 
 def module_kernels(plan: str, path: str) -> list[str]:
-    """Kernels between the events of a whtmix_module_forward call (the weight
-    repacking kernel runs before the first event); path: the library's
+    """Kernels between the events of a whtmix_module_forward call (where a weight
+    repacking kernel runs, C = 256, it is before the first event); path: the library's
     module_path for the shape ("small", "mfma" or "unfused")."""
     if plan == "small" or path == "small":
         return ["module_small"]
