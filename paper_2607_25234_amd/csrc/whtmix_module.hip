@@ -10,8 +10,8 @@
 //     bf16, hi = RNE(Z'), lo = RNE(Z' - hi), which leaves a residual below
 //     2^-17 |Z'|) and multiplied in two MFMAs.
 //   * fp32: the same instruction on three-term bf16 splits of both operands, the
-//     six products down to 2^-25 of the largest (v_mfma_f32_16x16x4_f32 for
-//     C = 16).
+//     six products down to 2^-25 of the largest; v_mfma_f32_16x16x4_f32 for C = 16
+//     and for waves with operands that the terms do not hold (SplitRange).
 //   The contraction order over k is free, so each lane's k values are chosen
 //   to make its loads of X 16-byte pieces and its register reads contiguous.
 //
@@ -204,8 +204,8 @@ struct Proj {
 };
 
 // k value order of the 16x16x16 bf16 and 16x16x4 fp32 products (the fused
-// kernels' float32 and C = 16 forms, and the projection kernel; the fused bf16
-// forms from C = 32 use pack_x32_kernel's order).  bf16: lane group q, step
+// kernels' C = 16 forms, and the projection kernel; the fused forms from C = 32
+// use pack_x32_kernel's order).  bf16: lane group q, step
 // kk, element r: channel 32(kk/2) + 8q + 4(kk%2) + r (C >= 32; each lane reads
 // its channels as 16-byte pieces of 8), or 4q + r (C = 16).  fp32: step s:
 // channel 16(s/4) + 4q + s%4 (16-byte pieces of 4).
@@ -330,7 +330,7 @@ __device__ __forceinline__ uint32_t pack_std_source(uint32_t idx, uint32_t C, in
 
 // Three-term bf16 split of two floats, v = hi + mid + lo + d, each term the
 // nearest bf16 of what the previous ones leave: |mid| <= 2^-8 |v|, |lo| <= 2^-17
-// |v|, |d| <= 2^-26 |v|.
+// |v|, |d| <= 2^-26 |v|.  For |v| >= 2^-100 each term is a normal bf16 and d = 0.
 __device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, uint32_t &mid,
                                             uint32_t &lo)
 {
@@ -346,12 +346,42 @@ __device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, ui
     lo = cvt(r0 - f32(mid << 16), r1 - f32(mid & 0xffff0000u));
 }
 
+// Whether three bf16 terms hold the floats seen, each add() a lane's share of one
+// row or column of an operand: none that rounds to an infinite bf16 (its terms, as
+// those of Inf, are Inf and NaN), and, unless the share is zero throughout, one
+// of 2^-95 or more, against which the bits that terms lose below 2^-126 are
+// nothing.  A wave that meets another operand takes the float32 instruction
+// (project_in_f32, project_out_f32), which is what these products mean.  With the
+// checks the backward's first pass on 2 slices of 36864 x 64 takes 25.3 us (24.1
+// without), its last 13.2 (12.4); the float32 block over 12 <= K <= 24 takes 2, 3 and 5%
+// longer at C = 32, 64 and 128, 12% at most (2^11 tiles of C = 128).
+struct SplitRange {
+    uint32_t least = 0xffffffffu;   // of 2 |or-ed| - 1 (zero: the top)
+    float most = 0.0f;              // NaN passes: its products are NaN either way
+    template <int N>
+    __device__ __forceinline__ void add(const float *v)
+    {
+        uint32_t any = 0u;
+#pragma unroll
+        for (int k = 0; k < N; k += 2) {
+            asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[k]), "v"(v[k + 1]));
+            any |= __builtin_bit_cast(uint32_t, v[k]) | __builtin_bit_cast(uint32_t, v[k + 1]);
+        }
+        least = min(least, (any << 1) - 1u);
+    }
+    __device__ __forceinline__ bool outside() const
+    {
+        return least < (32u << 24) - 1u || most >= 0x1.ffp127f;
+    }
+};
+__device__ __forceinline__ bool any_lane(bool b) { return __builtin_amdgcn_ballot_w64(b) != 0u; }
+
 // float32 weights from C = 32 are in the order of pack_x32_kernel (but the
 // epilogue's column m of block nb is 16 nb + m), in three bf16 planes per column
 // part: part r holds column blocks [r NNB / ROUNDS, ...), plane by plane.
 
 // acc = a b over ks k steps, both in three terms: the six products down to
-// 2^-25 of the largest, below float32's own rounding; the leading products
+// 2^-25 of the largest (the three left out come to 2^-24 of it at most); the leading products
 // apart, so that the sum is rounded once per step at its own size.
 template <int KS2>
 __device__ __forceinline__ f32x4 mul_x3(const bf16x8 (&a0)[KS2], const bf16x8 (&a1)[KS2],
@@ -866,6 +896,22 @@ struct RawWeights {
         }
     }
 
+    // X3: whether a loaded weight of this thread is outside SplitRange.
+    __device__ __forceinline__ bool outside(uint32_t tau) const
+    {
+        SplitRange range;
+#pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            if (UNITS % NT != 0 && tau + i * NT >= UNITS) break;
+            float w[WORDS];   // of one column
+#pragma unroll
+            for (uint32_t e = 0; e < WORDS; ++e)
+                w[e] = __builtin_bit_cast(float, raw[i][e]);
+            range.add<WORDS>(w);
+        }
+        return range.outside();
+    }
+
     __device__ __forceinline__ void write(void *lds, uint32_t tau)
     {
         u32x4 *d = static_cast<u32x4 *>(lds);
@@ -922,26 +968,61 @@ struct RawWeights {
     }
 };
 
+// Per wave, whether its share of the staged weights is outside SplitRange (X3),
+// read by every wave after the barrier they are staged behind.  The prologue asks
+// part by part; the epilogue, which gives up Z' for its terms before the second
+// part, asks for all of W with the first.
+template <typename T, int CB, uint32_t NT>
+struct WeightFlags {
+    static constexpr bool USED = Proj<T, CB>::X3;
+    static constexpr uint32_t WAVES = USED ? NT / 64u : 1u;
+    uint32_t wave[WAVES];
+    template <PackMode MODE>
+    __device__ __forceinline__ void set(const RawWeights<T, CB, MODE, NT> &staged, const T *w,
+                                        uint32_t tau, uint32_t part)
+    {
+        using R = RawWeights<T, CB, MODE, NT>;
+        if constexpr (USED) {
+            bool outside = staged.outside(tau);
+            if constexpr (!R::PRO) {
+                if (part > 0)
+                    return;
+#pragma unroll
+                for (int p = 1; p < Proj<T, CB>::W_ROUNDS; ++p) {
+                    R r;
+                    r.load(w, tau, p);
+                    outside |= r.outside(tau);
+                }
+            }
+            wave[tau >> 6] = any_lane(outside);
+        }
+    }
+    __device__ __forceinline__ bool any(uint32_t tau) const
+    {
+        return any_lane(wave[tau & (WAVES - 1u)] != 0u);
+    }
+};
+
 // Part `part` of W (of W^T with `trans`, uniform) into LDS; `then` issues loads
 // behind the weights'.
 struct Nothing {
     __device__ void operator()() const {}
 };
 template <typename T, int CB, bool PRO, uint32_t NT, class F = Nothing>
-__device__ __forceinline__ void stage_raw(void *lds, const T *w, bool trans, uint32_t tau,
-                                          uint32_t part = 0, F &&then = F{})
+__device__ __forceinline__ void stage_raw(void *lds, WeightFlags<T, CB, NT> &flags, const T *w,
+                                          bool trans, uint32_t tau, uint32_t part = 0,
+                                          F &&then = F{})
 {
-    if (trans) {
-        RawWeights<T, CB, PRO ? PACK_PROLOGUE_T : PACK_EPILOGUE_T, NT> r;
+    const auto stage = [&](auto r) {
         r.load(w, tau, part);
         then();
         r.write(lds, tau);
-    } else {
-        RawWeights<T, CB, PRO ? PACK_PROLOGUE : PACK_EPILOGUE, NT> r;
-        r.load(w, tau, part);
-        then();
-        r.write(lds, tau);
-    }
+        flags.set(r, w, tau, part);
+    };
+    if (trans)
+        stage(RawWeights<T, CB, PRO ? PACK_PROLOGUE_T : PACK_EPILOGUE_T, NT>{});
+    else
+        stage(RawWeights<T, CB, PRO ? PACK_PROLOGUE : PACK_EPILOGUE, NT>{});
 }
 
 // The projections of float32 from C = 32.  Against the fp32 instruction the six
@@ -967,26 +1048,72 @@ __device__ __forceinline__ void split_x3(bf16x8 (&a0)[KS2], bf16x8 (&a1)[KS2], b
     }
 }
 
+// acc = X W for column block nb on the float32 instruction, both operands from
+// memory (k step s: channel 4 s + q): for the rare wave whose operands the split
+// does not hold, so in few registers rather than fast.
+template <int CB, int NRB>
+__device__ __forceinline__ void project_in_f32(f32x4 (&acc)[NRB], const float *tile,
+                                               uint32_t valid, const float *w, bool trans,
+                                               uint32_t nb, uint32_t tau)
+{
+    constexpr uint32_t C = 1u << CB;
+    const uint32_t lane = tau & 63u, i = lane & 15u, q = lane >> 4;
+    const __amdgpu_buffer_rsrc_t r = buffer(tile, valid * 4u);
+    uint32_t x = (prologue_token<CB>(0, i, tau >> 6) * C + q) * 4u;
+    const float *src = w + (trans ? (16u * nb + i) * C + q : q * C + 16u * nb + i);
+    const uint32_t step = trans ? 4u : 4u * C;
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+        acc[rb] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (uint32_t s = 0; s < C / 4u; ++s, x += 16u, src += step) {
+        const float b = *src;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+            acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                Elt<float>::load(r, x + rb * (16u * C), 0), b, acc[rb], 0, 0, 0);
+    }
+}
+
+// tile, valid: where f was loaded from.
 template <int CB, uint32_t NT>
 __device__ __forceinline__ void project_in_x3(float (&v)[V], const XFrag<float, CB> &f, float *lds,
-                                              const float *w, bool trans, uint32_t tau)
+                                              WeightFlags<float, CB, NT> &flags, const float *w,
+                                              bool trans, const float *tile, uint32_t valid,
+                                              uint32_t tau)
 {
     using P = Proj<float, CB>;
     constexpr int KS2 = P::KS2, NPR = P::NNB / P::W_ROUNDS;   // column blocks of a part
     constexpr uint32_t PLANE = NPR * KS2 * 64;                // 16-byte units
     const uint32_t lane = tau & 63u;
+    SplitRange range;
     bf16x8 a0[P::NRB][KS2], a1[P::NRB][KS2], a2[P::NRB][KS2];
+#pragma unroll
+    for (int rb = 0; rb < P::NRB; ++rb) {
+        range.add<P::KS>(f.a[rb]);
+        split_x3<KS2>(a0[rb], a1[rb], a2[rb], f.a[rb]);
+    }
+    const bool outside = any_lane(range.outside());
 #pragma unroll
     for (int r = 0; r < P::W_ROUNDS; ++r) {
         if (r > 0) {   // the caller staged the first part
             __syncthreads();   // the previous part's readers
-            stage_raw<float, CB, true, NT>(lds, w, trans, tau, r);
-        } else {
-#pragma unroll
-            for (int rb = 0; rb < P::NRB; ++rb)
-                split_x3<KS2>(a0[rb], a1[rb], a2[rb], f.a[rb]);
+            stage_raw<float, CB, true, NT>(lds, flags, w, trans, tau, r);
         }
         __syncthreads();
+        if (__builtin_expect(outside || flags.any(tau), 0)) {   // uniform over the wave
+#pragma unroll
+            for (int n = 0; n < NPR; ++n) {
+                f32x4 acc[P::NRB];
+                project_in_f32<CB>(acc, tile, valid, w, trans, r * NPR + n, tau);
+#pragma unroll
+                for (int rb = 0; rb < P::NRB; ++rb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        v[(r * NPR + n) | (e << (CB - 4)) | (rb << (CB - 2))] = acc[rb][e];
+            }
+            continue;
+        }
         const bf16x8 *wb = reinterpret_cast<const bf16x8 *>(lds) + lane;
 #pragma unroll
         for (int n = 0; n < NPR; ++n) {
@@ -1010,12 +1137,55 @@ __device__ __forceinline__ void project_in_x3(float (&v)[V], const XFrag<float, 
     }
 }
 
+// Y = Z' W for the wave's rows on the float32 instruction, for the rare wave whose
+// operands the split does not hold.  The wave's rows of y hold Z' (its own stores):
+// read back in a loop, it takes no registers from the common path.
+template <int CB, int M, bool TRANS>
+__device__ __forceinline__ void project_out_f32(const float *w, float *tile, uint32_t valid,
+                                                uint32_t tau)
+{
+    using P = Proj<float, CB>;
+    constexpr uint32_t C = P::C, ROWS = (1u << (M - 7)) * C * 4u;   // bytes between row blocks
+    const uint32_t lane = tau & 63u, j = lane & 15u, q = lane >> 4;
+    const __amdgpu_buffer_rsrc_t r = buffer(tile, valid * 4u);
+    const uint32_t row = (j | ((tau >> 6) << 4)) * C * 4u;
+    const float *src = w + (TRANS ? j * C + q : q * C + j);
+    f32x4 acc[P::NRB][P::NNB];
+#pragma unroll
+    for (int rb = 0; rb < P::NRB; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < P::NNB; ++nb)
+            acc[rb][nb] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    __threadfence();
+#pragma unroll 1
+    for (uint32_t s = 0; s < C / 4u; ++s, src += TRANS ? 4u : 4u * C) {   // channel 4 s + q
+        float z[P::NRB];
+#pragma unroll
+        for (int rb = 0; rb < P::NRB; ++rb)
+            z[rb] = Elt<float>::load(r, row + 16u * s + 4u * q + rb * ROWS, 0);
+#pragma unroll
+        for (int nb = 0; nb < P::NNB; ++nb) {
+            const float a = src[nb * (TRANS ? 16u * C : 16u)];
+#pragma unroll
+            for (int rb = 0; rb < P::NRB; ++rb)
+                acc[rb][nb] =
+                    __builtin_amdgcn_mfma_f32_16x16x4f32(a, z[rb], acc[rb][nb], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int rb = 0; rb < P::NRB; ++rb)
+#pragma unroll
+        for (int nb = 0; nb < P::NNB; ++nb)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[rb][nb]), r,
+                                                   row + 16u * q + rb * ROWS + 64u * nb, 0, 0);
+}
+
 // Y = Z' W_out as project_out, the weights either whole in LDS at wl, or
 // (W_ROUNDS > 1) staged into lds part by part.
 template <int CB, int M, uint32_t NT, bool TRANS>
 __device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *wl, float *lds,
-                                               const float *w, float *tile, uint32_t valid,
-                                               uint32_t tau)
+                                               WeightFlags<float, CB, NT> &flags, const float *w,
+                                               float *tile, uint32_t valid, uint32_t tau)
 {
     using P = Proj<float, CB>;
     constexpr int KS2 = P::KS2, NPR = P::NNB / P::W_ROUNDS;
@@ -1027,18 +1197,44 @@ __device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *
     const uint32_t tok0 = j | (wv << 4);
     const uint32_t row = tok0 * (uint32_t)(P::C * 4);
     constexpr uint32_t rb_bytes = (1u << (M - 7)) * P::C * 4u;
-    bf16x8 z0[P::NRB][KS2], z1[P::NRB][KS2], z2[P::NRB][KS2];
+    SplitRange range;
 #pragma unroll
     for (int rb = 0; rb < P::NRB; ++rb)
-        split_x3<KS2>(z0[rb], z1[rb], z2[rb], v + (rb << (CB - 2)));
+        range.add<P::C / 4>(v + (rb << (CB - 2)));
+    const bool outside = any_lane(range.outside());
+    if constexpr (P::W_ROUNDS > 1) {
+        __syncthreads();   // the last exchange's readers
+        stage_raw<float, CB, false, NT>(lds, flags, w, TRANS, tau, 0);
+        __syncthreads();
+        wl = lds;
+    }
+    const bool plain = !outside && !flags.any(tau);   // uniform over the wave
+    bf16x8 z0[P::NRB][KS2], z1[P::NRB][KS2], z2[P::NRB][KS2];
+    if (__builtin_expect(plain, 1)) {
+#pragma unroll
+        for (int rb = 0; rb < P::NRB; ++rb)
+            split_x3<KS2>(z0[rb], z1[rb], z2[rb], v + (rb << (CB - 2)));
+    } else {
+#pragma unroll
+        for (int rb = 0; rb < P::NRB; ++rb)
+#pragma unroll
+            for (int p = 0; p < P::C / 16; ++p) {   // channels q C/4 + 4 p + [0, 4)
+                const float *z = v + (rb << (CB - 2)) + 4 * p;
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    __builtin_bit_cast(u32x4, (f32x4){z[0], z[1], z[2], z[3]}), r,
+                    row + q * P::C + (rb * rb_bytes + 16u * p), 0, 0);
+            }
+        project_out_f32<CB, M, TRANS>(w, tile, valid, tau);
+    }
 #pragma unroll
     for (int part = 0; part < P::W_ROUNDS; ++part) {
-        if constexpr (P::W_ROUNDS > 1) {
-            __syncthreads();   // the last exchange's readers, or the previous part's
-            stage_raw<float, CB, false, NT>(lds, w, TRANS, tau, part);
+        if (part > 0) {
+            __syncthreads();   // the previous part's readers
+            stage_raw<float, CB, false, NT>(lds, flags, w, TRANS, tau, part);
             __syncthreads();
-            wl = lds;
         }
+        if (!plain)
+            continue;
         const bf16x8 *wb = static_cast<const bf16x8 *>(wl) + lane;
 #pragma unroll
         for (int n = 0; n < NPR; ++n) {
@@ -1072,6 +1268,7 @@ __device__ __forceinline__ void project_out_x3(const float (&v)[V], const void *
 // wreg holds it (or, PARTS, it is staged from memory).
 template <typename T, int CB, int M, bool TRANS, class WReg>
 __device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const void *wregion,
+                                         WeightFlags<T, CB, Lds<M, T, CB>::NT> &flags,
                                          [[maybe_unused]] WReg &wreg,
                                          [[maybe_unused]] const T *w_out, T *tile, uint32_t valid,
                                          uint32_t tau)
@@ -1081,12 +1278,13 @@ __device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const 
     if constexpr (!L::SEPARATE && !L::PARTS) {
         __syncthreads();   // every thread has read its epilogue-layout values
         wreg.write(lds, tau);
+        flags.set(wreg, w_out, tau, 0);
         wl = lds;
     }
     if constexpr (!L::PARTS)
         __syncthreads();
     if constexpr (Proj<T, CB>::X3)
-        project_out_x3<CB, M, L::NT, TRANS>(v, wl, lds, w_out, tile, valid, tau);
+        project_out_x3<CB, M, L::NT, TRANS>(v, wl, lds, flags, w_out, tile, valid, tau);
     else
         project_out<T, CB, M>(v, wl, tile, valid, tau);
 }
@@ -1102,19 +1300,20 @@ module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
     unsigned char *const region1 = reinterpret_cast<unsigned char *>(lds) + L::REGION0;
     const uint32_t tau = threadIdx.x;
     const size_t base = (size_t)blockIdx.x * nvalid;
+    __shared__ WeightFlags<T, CB, L::NT> in_flags, out_flags;
     XFrag<T, CB> f;
-    stage_raw<T, CB, true, L::NT>(lds, w_in, false, tau, 0, [&] {
+    stage_raw<T, CB, true, L::NT>(lds, in_flags, w_in, false, tau, 0, [&] {
         load_x_frags<T, CB>(f, x + base, nvalid, tau);
     });
     [[maybe_unused]] RawWeights<T, CB, PACK_EPILOGUE, L::NT> wreg;
     if constexpr (L::SEPARATE)
-        stage_raw<T, CB, false, L::NT>(region1, w_out, false, tau);
+        stage_raw<T, CB, false, L::NT>(region1, out_flags, w_out, false, tau);
     else if constexpr (!L::PARTS)
         wreg.load(w_out, tau);
     float v[V], gv[V];
     gain.template load<K - 5, ContigMap>(gv, 0, tau);
     if constexpr (Proj<T, CB>::X3) {
-        project_in_x3<CB, L::NT>(v, f, lds, w_in, false, tau);
+        project_in_x3<CB, L::NT>(v, f, lds, in_flags, w_in, false, x + base, nvalid, tau);
     } else {
         __syncthreads();
         project_in<T, CB>(v, f, lds, tau);
@@ -1122,13 +1321,15 @@ module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
     forward_from_prologue<K>(lds, v, tau);
     apply_gain<K>(v, gv);
     inverse_to_epilogue<K, CB, true>(lds, v, tau);
-    epilogue<T, CB, K, false>(v, lds, region1, wreg, w_out, y + base, nvalid, tau);
+    epilogue<T, CB, K, false>(v, lds, region1, out_flags, wreg, w_out, y + base, nvalid, tau);
 }
 
 // THREE_PASS first pass: prologue (x W_in, or x W_in^T with trans), forward over
 // the A low bits, workspace.
 template <int A, int HB, int R, typename T, int CB>
-__device__ __forceinline__ void module_outer_fwd_tile(float *lds, const T *__restrict__ x,
+__device__ __forceinline__ void module_outer_fwd_tile(float *lds,
+                                                      WeightFlags<T, CB, Lds<A, T, CB>::NT> &flags,
+                                                      const T *__restrict__ x,
                                                       const T *__restrict__ w_in,
                                                       bool trans, float *__restrict__ ws,
                                                       uint32_t nvalid, uint32_t blk)
@@ -1141,16 +1342,17 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds, const T *__res
     const uint32_t valid = tile_valid<A>(nvalid, hi);
     if (valid == 0)
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
+    const T *const tile = x + b * nvalid + ((size_t)hi << A);
     XFrag<T, CB> f;
     // The weights come from L2, x from memory: issued first, they are in LDS
     // by the time x arrives (with project_in's reads ahead, this kernel on 4 x
     // 65536 x 128 bf16: 48.1 -> 41.9 us).
-    stage_raw<T, CB, true, L::NT>(lds, w_in, trans, tau, 0, [&] {
-        load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, tau);
+    stage_raw<T, CB, true, L::NT>(lds, flags, w_in, trans, tau, 0, [&] {
+        load_x_frags<T, CB>(f, tile, valid, tau);
     });
     float v[V];
     if constexpr (Proj<T, CB>::X3) {
-        project_in_x3<CB, L::NT>(v, f, lds, w_in, trans, tau);
+        project_in_x3<CB, L::NT>(v, f, lds, flags, w_in, trans, tile, valid, tau);
     } else {
         __syncthreads();
         project_in<T, CB>(v, f, lds, tau);
@@ -1166,7 +1368,8 @@ module_outer_fwd_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
                         float *__restrict__ ws, uint32_t nvalid)
 {
     __shared__ __attribute__((aligned(16))) float lds[Lds<A, T, CB>::fwd_bytes() / 4];
-    module_outer_fwd_tile<A, HB, R, T, CB>(lds, x, w_in, false, ws, nvalid,
+    __shared__ WeightFlags<T, CB, Lds<A, T, CB>::NT> flags;
+    module_outer_fwd_tile<A, HB, R, T, CB>(lds, flags, x, w_in, false, ws, nvalid,
                                            outer_block<R>(blockIdx.x, gridDim.x));
 }
 
@@ -1180,10 +1383,11 @@ module_outer_fwd2_kernel(const T *__restrict__ x, const T *__restrict__ wa,
                          float *__restrict__ wsx, float *__restrict__ wsd, uint32_t nvalid)
 {
     __shared__ __attribute__((aligned(16))) float lds[Lds<A, T, CB>::fwd_bytes() / 4];
+    __shared__ WeightFlags<T, CB, Lds<A, T, CB>::NT> flags;
     const uint32_t half = gridDim.x >> 1;
     const bool second = blockIdx.x >= half;
     const uint32_t blk = outer_block<R>(blockIdx.x - (second ? half : 0u), half);
-    module_outer_fwd_tile<A, HB, R, T, CB>(lds, second ? dy : x, second ? wb : wa, second,
+    module_outer_fwd_tile<A, HB, R, T, CB>(lds, flags, second ? dy : x, second ? wb : wa, second,
                                            second ? wsd : wsx, nvalid, blk);
 }
 
@@ -1198,6 +1402,7 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
     using Run = RunMap<HB, R>;
     __shared__ __attribute__((aligned(16))) float lds[L::inv_bytes() / 4];
     unsigned char *const wregion = reinterpret_cast<unsigned char *>(lds) + L::TILE;
+    __shared__ WeightFlags<T, CB, L::NT> flags;
     const uint32_t tau = threadIdx.x;
     const uint32_t blk = outer_block<R>(blockIdx.x, gridDim.x);
     const size_t b = blk >> HB;
@@ -1207,7 +1412,7 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
         return;   // wholly padding: nothing to store (uniform per workgroup)
     [[maybe_unused]] RawWeights<T, CB, TRANS ? PACK_EPILOGUE_T : PACK_EPILOGUE, L::NT> wreg;
     if constexpr (L::SEPARATE)
-        stage_raw<T, CB, false, L::NT>(wregion, w_out, TRANS, tau);
+        stage_raw<T, CB, false, L::NT>(wregion, flags, w_out, TRANS, tau);
     else if constexpr (!L::PARTS)
         wreg.load(w_out, tau);
     float v[V];
@@ -1216,7 +1421,7 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
     inverse_to_epilogue<A, CB, false>(lds, v, tau);
     if constexpr (ZOUT)
         store_epilogue_f32<A, CB>(lds, v, z + b * nvalid + ((size_t)hi << A), valid, tau);
-    epilogue<T, CB, A, TRANS>(v, lds, wregion, wreg, w_out, y + b * nvalid + ((size_t)hi << A),
+    epilogue<T, CB, A, TRANS>(v, lds, wregion, flags, wreg, w_out, y + b * nvalid + ((size_t)hi << A),
                               valid, tau);
 }
 

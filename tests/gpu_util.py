@@ -92,3 +92,17 @@ def random_cases(n: int, seed: int, max_elems: int = 1 << 21) -> list[tuple]:
 
 def case_ids(cases) -> list[str]:
     return [f"r{i:02d}-{b}x{n}x{c}-{d}" for i, (b, n, c, d) in enumerate(cases)]
+
+
+def check_with_infinities(name, y, ref, tol):
+    """y against a float64 reference that holds infinities: the same elements
+    are +Inf, -Inf and NaN, and the finite ones agree normwise to tol."""
+    r = np.asarray(ref).astype(np.float32)
+    assert y.shape == r.shape
+    finite = np.isfinite(r)
+    assert np.array_equal(np.isfinite(y), finite), (name, "finite")
+    assert np.array_equal(np.isnan(y), np.isnan(r)), (name, "NaN")
+    assert np.array_equal(y[np.isinf(r)], r[np.isinf(r)]), (name, "Inf")
+    err = errors(y[finite], np.asarray(ref)[finite])[0]
+    say(f"  {name}: normwise-max {err:.3e} (tol {tol:g}), {np.sum(~finite)} not finite")
+    assert err <= tol, (name, err)

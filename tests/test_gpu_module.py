@@ -15,7 +15,8 @@ import pytest
 
 from oracle import oracle as oracle_mod
 from paper_2607_25234_amd import whtmix, workloads
-from tests.gpu_util import device, errors, say, to_device, to_host
+from tests.gpu_util import (check_with_infinities, device, errors, say, to_device,
+                            to_host)
 
 pytestmark = pytest.mark.gpu
 
@@ -221,3 +222,49 @@ def test_module_deterministic(dev):
     a = run_module(x, wi, wo, "bf16", dev, g=g)
     b = run_module(x, wi, wo, "bf16", dev, g=g)
     assert np.array_equal(a, b)
+
+
+# Both float32 plans of each C whose projections are bf16 products of split
+# operands: one workgroup per slice; three passes on 2^11, 2^12 and 2^13 tiles,
+# ragged token counts
+RANGE_SHAPES = [(2, 100, 32), (2, 200, 64), (2, 100, 128), (2, 3000, 32), (2, 3000, 64),
+                (2, 1000, 128), (1, 9216, 128)]
+HUGE = np.float32(3.4e38)   # finite, but the nearest bf16 is infinite
+
+
+@pytest.mark.parametrize("case", ["inf_w_out", "nan_x", "huge_x", "huge_w_in", "huge_w_out",
+                                  "tiny_x", "tiny_w_in", "tiny_w_out"])
+@pytest.mark.parametrize("shape", RANGE_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_module_float32_range(shape, case, dev, orc):
+    """Operands the three bf16 terms do not hold give what float32 products give:
+    infinite weights give infinities of the right sign in their own column, the
+    largest finite floats finite results, and operands near the smallest normal
+    float32 (2^-121 here) keep the float32 bar.  Powers of two and 1e-10 keep
+    every product and sum inside the normal range."""
+    B, N, C = shape
+    x, g, wi, wo = inputs(B, N, C, "f32", seed=40 + N + C)
+    small = np.float32(1e-10)
+    if case == "inf_w_out":
+        wo[3, 5], wo[7, C - 1] = np.inf, -np.inf
+    elif case == "nan_x":
+        x[0, N - 1, 2] = np.nan
+    elif case == "huge_x":
+        x[0, 1, 2], wi = HUGE, wi * small
+    elif case == "huge_w_in":
+        wi[C - 1, 3], x = HUGE, x * small
+    elif case == "huge_w_out":
+        wo[C - 1, 3], x = HUGE, x * small
+    else:
+        g = g * np.float32(2.0 ** 10)
+        tiny = np.float32(2.0 ** -121)
+        if case == "tiny_x":
+            x = x * tiny
+        elif case == "tiny_w_in":
+            wi = wi * tiny
+        else:
+            wo = wo * tiny
+    say(f"module range {shape} {case} {path(B, N, C, 'f32')}")
+    y = run_module(x, wi, wo, "f32", dev, g=g)
+    with np.errstate(all="ignore"):
+        ref = orc.whtmix_module(x, wi, g, wo)
+        check_with_infinities(case, y, ref, TOL["f32"])

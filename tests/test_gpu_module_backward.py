@@ -12,7 +12,8 @@ import pytest
 
 from oracle import oracle as oracle_mod
 from paper_2607_25234_amd import whtmix, workloads
-from tests.gpu_util import device, errors, say, to_device, to_host
+from tests.gpu_util import (check_with_infinities, device, errors, say, to_device,
+                            to_host)
 
 pytestmark = pytest.mark.gpu
 
@@ -206,6 +207,28 @@ def test_module_backward_by_composition(shape, dtype, dev):
     check("dx", to_host(dx), to_host(dx_ref), TOL[dtype])
     for name, a, r in [("dw_in", dwi, dwi_ref), ("dw_out", dwo, dwo_ref), ("dgain", dg, dg_ref)]:
         check(name, to_host(a), to_host(r), GRAD_TOL)
+
+
+@pytest.mark.parametrize("case", ["inf_w_in", "huge_dy", "tiny_dy"])
+@pytest.mark.parametrize("shape", [(2, 3000, 32), (2, 1000, 64), (2, 1000, 128), (1, 9216, 128)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_module_backward_float32_range(shape, case, dev, orc):
+    """dX = mixer(dY W_out^T) W_in^T through the transposed float32 projections, with
+    operands their bf16 terms do not hold (tests/test_gpu_module.py has the
+    forward's)."""
+    B, N, C = shape
+    x, dy, g, wi, wo = inputs(B, N, C, "f32", seed=60 + N + C)
+    if case == "inf_w_in":
+        wi[3, 5], wi[C - 1, 0] = np.inf, -np.inf
+    elif case == "huge_dy":
+        dy[0, 1, 2], wo = np.float32(3.4e38), wo * np.float32(1e-10)
+    else:
+        dy, g = dy * np.float32(2.0 ** -121), g * np.float32(2.0 ** 10)
+    say(f"module backward range {shape} {case}")
+    dx = run(x, dy, wi, wo, "f32", dev, g=g)[0]
+    with np.errstate(all="ignore"):
+        ref = orc.whtmix_module_grad(x, wi, g, wo, dy)[0]
+        check_with_infinities(case, dx, ref, TOL["f32"])
 
 
 def test_module_backward_empty_batch_zeroes_gradients(dev):
