@@ -648,7 +648,7 @@ int module_backward_impl(const void *x, const void *w_in, int gain_kind, const f
                            : align256(3 * whtmix::module_packed_bytes(cbits, dtype));
     const whtmix::WgradPlan wp = whtmix::wgrad_plan((uint64_t)rows, cbits);
     const int64_t part =
-        m.tiles ? align256(2 * (int64_t)whtmix::wgrad_tiles_parts(c.K, cbits, dtype, B, m.nvalid) * C * C * 4)
+        m.tiles ? align256(whtmix::wgrad_tiles_floats(c.K, cbits, dtype, B, m.nvalid) * 4)
                 : align256((int64_t)wp.partial_floats(cbits) * 4);
     const int64_t mix = m.tiles ? 0 : align256(c.ws_bytes);
     const whtmix::BackwardLayout lay = whtmix::backward_layout(c.plan, c.K, B, C, sep);

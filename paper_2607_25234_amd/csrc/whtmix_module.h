@@ -188,12 +188,21 @@ inline uint32_t wgrad_tiles_parts(int K, int cbits, int dtype, int64_t B, uint32
     return (uint32_t)(groups < most ? groups : most);
 }
 
+// Floats of `part`: the partial matrices, then (float32) a word per wave about its
+// operands.
+inline int64_t wgrad_tiles_floats(int K, int cbits, int dtype, int64_t B, uint32_t nvalid)
+{
+    const int64_t words = dtype == DTYPE_F32 ? 16 : 0;   // waves of a workgroup at most
+    return 2 * (int64_t)wgrad_tiles_parts(K, cbits, dtype, B, nvalid) *
+           ((int64_t(1) << (2 * cbits)) + words);
+}
+
 struct WgradTilesArgs {
     const float *wsx;       // middle pass's output of Z and of dZ'
     const float *wsd;
     const void *x;
     const void *dy;
-    float *part;            // 2 * wgrad_tiles_parts * C * C floats
+    float *part;            // wgrad_tiles_floats
     float *dw_in;
     float *dw_out;
     int cbits;
@@ -212,7 +221,7 @@ hipError_t launch_wgrad_tiles(const WgradTilesArgs &a);
 // wpack: W_in, W_out^T and W_in^T packed (3*C*C elements of the dtype; absent
 // where the fused backward runs with C <= 128);
 // wpart: the weight gradients' partial sums (wgrad_plan, or
-// wgrad_tiles_parts with `tiles`); mix_ws: the
+// wgrad_tiles_floats with `tiles`); mix_ws: the
 // THREE_PASS workspace (B * 2^K, else none); bwd_ws: the mixer backward's
 // workspace (backward_layout).
 struct ModuleBackwardArgs {

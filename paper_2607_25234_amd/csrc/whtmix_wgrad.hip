@@ -28,6 +28,11 @@
 //   against bf16 dY / X (both exact) or against the same split of float32 dY /
 //   X: the six products down to 2^-25 of the largest, below float32's own
 //   rounding, at 2.7 times the rate of the fp32 instruction.
+// The terms of Inf, of |v| past the largest bf16 (rounded) and, below 2^-110, of
+// the smallest floats are not v, and an infinite sum over channel frequencies says
+// nothing of the channels.  A column that comes out NaN or Inf, and both matrices of
+// float32 operands that are tiny throughout (Seen), are formed again in float32
+// by the final sum (exact_column).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -201,6 +206,42 @@ __device__ __forceinline__ void split3(const float (&z)[8], bf16x8 &hi, bf16x8 &
     mid = __builtin_bit_cast(bf16x8, m);
     lo = __builtin_bit_cast(bf16x8, l);
 }
+
+// The magnitudes of a float32 operand, or-ed: no bit from 2^28 up is set where all
+// are below 2^-95, whose splits may lose bits that matter.  (Against larger ones a
+// tiny value's loss, 2^-134 at most, is below the sum's own rounding.)
+struct Seen {
+    uint32_t x = 0u, z = 0u;
+    static constexpr uint32_t LARGE = 0x70000000u, ANY = 0x7fffffffu;
+    template <int N>
+    __device__ __forceinline__ void add_z(const float (&v)[N])
+    {
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            z |= as_u32(v[k]);
+        asm volatile("" : "+v"(z));   // here, before the values are split
+    }
+    template <int N>
+    __device__ __forceinline__ void add_x(const u32x4 (&v)[N])
+    {
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            x |= (v[k][0] | v[k][1]) | (v[k][2] | v[k][3]);
+        asm volatile("" : "+v"(x));
+    }
+    // bit 0, 1: a large x, any x; bit 2, 3: z.  One word per wave.
+    __device__ __forceinline__ void store(uint32_t *word) const
+    {
+        const auto some = [](uint32_t v) { return __builtin_amdgcn_ballot_w64(v != 0u) != 0u; };
+        *word = (some(x & LARGE) ? 1u : 0u) | (some(x & ANY) ? 2u : 0u) |
+                (some(z & LARGE) ? 4u : 0u) | (some(z & ANY) ? 8u : 0u);
+    }
+    // of all words or-ed
+    __device__ static bool tiny(uint32_t words)
+    {
+        return (words & 3u) == 2u || (words & 12u) == 8u;
+    }
+};
 
 // acc += a b over k steps [s0, s1) of a round (a: the lane's float operand, b:
 // the staged planes; rs0 the round's first step).  Steps go in groups whose
@@ -421,8 +462,8 @@ template <int A, int HB, int R, typename T, int CB>
 __global__ void __launch_bounds__((Wg<A, CB>::THREADS), (Wg<A, CB>::NS == 1 ? 4 : 2))
 wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                    const float *__restrict__ wsd, const T *__restrict__ x,
-                   float *__restrict__ part, uint32_t nvalid, uint32_t live, uint32_t ntiles,
-                   uint32_t nwg)
+                   float *__restrict__ part, uint32_t *__restrict__ seen_words, uint32_t nvalid,
+                   uint32_t live, uint32_t ntiles, uint32_t nwg)
 {
     using W = Wg<A, CB>;
     using Run = RunMap<HB, R>;
@@ -463,6 +504,7 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
     // its workspace registers after the products, ahead of the next exchange.
     constexpr int ROUNDS = W::template rounds<T>(), STEPS = 1 << (W::RT - 3);
     constexpr int NB = W::template chunk_bits<T>();
+    [[maybe_unused]] Seen seen;   // float32
     float v[V];
     u32x4 xr[V * sizeof(T) / 16];
     size_t b;
@@ -504,6 +546,10 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                 v[k] = region[pb + W::at(W::reg((uint32_t)k))];
         }
         butterflies<W::SR, W::SR + W::REM>(v);
+        if constexpr (sizeof(T) == 4) {
+            seen.add_z(v);
+            seen.add_x(xr);
+        }
         // opaque per group: the operand and staging addresses are cheap to form
         // and, hoisted out of the loop, would take some forty registers
         uint32_t ln = lane, tt = t;
@@ -533,6 +579,8 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
 
     store_sums<C, NS, NNB, W::SW, CB>(acc, lds, part, wave >> W::SW, W::TEAMS,
                                       wave & ((1u << W::SW) - 1u), lane);
+    if constexpr (sizeof(T) == 4)
+        seen.store(seen_words + (blockIdx.x << W::WB) + wave);
 }
 
 // ---------------------------------------------------------------- direct form
@@ -713,8 +761,8 @@ template <int A, int HB, int R, typename T, int CB>
 __global__ void __launch_bounds__((Wd<A, CB>::THREADS), (Wd<A, CB>::template waves<T>()))
 wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                     const float *__restrict__ wsd, const T *__restrict__ x,
-                    float *__restrict__ part, uint32_t nvalid, uint32_t live, uint32_t ntiles,
-                    uint32_t nwg)
+                    float *__restrict__ part, uint32_t *__restrict__ seen_words, uint32_t nvalid,
+                    uint32_t live, uint32_t ntiles, uint32_t nwg)
 {
     using W = Wd<A, CB>;
     using X = StageX<A, CB, T>;
@@ -752,6 +800,7 @@ wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
 
     constexpr int ROUNDS = X::ROUNDS, STEPS = 1 << (W::RT - 3);
     constexpr int NB = W::template chunk_bits<T>();
+    [[maybe_unused]] Seen seen;   // float32
     float v[VV];
     u32x4 xr[X::NP];
     size_t b;
@@ -779,6 +828,8 @@ wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
         const auto round = [&](auto H) {
             constexpr int h = decltype(H)::value;
             __syncthreads();   // the previous round's product reads are done
+            if constexpr (sizeof(T) == 4)
+                seen.add_x(xr);
             X::stage(region, xr, tt);
             // the next round's pieces, or the next group's
             if (h + 1 < ROUNDS) {
@@ -795,6 +846,8 @@ wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                 swap_lane_bit<16, W::SR>(v);
                 swap_lane_bit<32, W::SR + 1>(v);
                 bfly<W::SR, W::SR + 2>(v);
+                if constexpr (sizeof(T) == 4)
+                    seen.add_z(v);
             }
             __syncthreads();
             // k step s: tokens 8 s + [0, 8) of each group q
@@ -809,40 +862,136 @@ wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
             load_ws();
     }
     store_sums<C, NS, NNB, W::SW, CB>(acc, lds, part, team, W::TEAMS, strip0, lane);
+    if constexpr (sizeof(T) == 4)
+        seen.store(seen_words + (blockIdx.x << W::WB) + wave);
+}
+
+// Bits [J, S + 5) of the transform of the 2^A tile in LDS (pad(t)), J >= S.
+template <int A, int S, int J>
+__device__ __forceinline__ void transform_window(float *lds, uint32_t tau)
+{
+    for (uint32_t i = tau; i < (1u << (A - VB)); i += 256u) {
+        const uint32_t at = pad(layout_base<S>(i));
+        float v[V];
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+            v[k] = lds[at + pad((uint32_t)k << S)];
+        butterflies<J - S, VB>(v);
+#pragma unroll
+        for (int k = 0; k < V; ++k)
+            lds[at + pad((uint32_t)k << S)] = v[k];
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ bool not_finite(float v)
+{
+    return (as_u32(v) & 0x7f800000u) == 0x7f800000u;
+}
+
+// Column `col` of dW in float32 as the formulas have it: tiles inverse-transformed
+// whole, their rows times their elements of dY / X.  Returns element tau of the
+// column (tau < C).  z_finite: Z' (dZ) is finite throughout, so that a column that
+// is not has its infinities and NaN from dY / X, and only the tiles that hold them
+// are looked at; otherwise, or if there are none, every tile.  A column that is NaN
+// throughout ends the loop.  Rare, so simple rather than fast.
+template <int CB, int A, typename T>
+__device__ float exact_column(float *lds, float *xcol, const float *ws, const T *xs, uint32_t col,
+                              bool z_finite, uint32_t nvalid, uint32_t live, uint32_t nslices,
+                              int HB, int R, uint32_t tau)
+{
+    constexpr uint32_t C = 1u << CB, G = 256u / C, TOKENS = 1u << (A - CB);
+    const uint32_t a = tau & (C - 1u), g = tau >> CB;
+    float total = 0.0f;
+    bool found = false, ended = false;
+    for (uint32_t pass = z_finite ? 0u : 1u; pass < 2u && !found && !ended; ++pass) {
+        for (uint32_t i = 0; i < nslices * live && !ended; ++i) {   // uniform
+            const uint32_t b = i / live, hi = i - b * live;
+            const T *x = xs + (size_t)b * nvalid + ((size_t)hi << A) + col;
+            const uint32_t tokens = tile_valid<A>(nvalid, hi) >> CB;
+            bool bad = false;
+            __syncthreads();   // the previous tile's readers
+            for (uint32_t n = tau; n < TOKENS; n += 256u) {
+                const float v = n < tokens ? (float)x[(size_t)n << CB] : 0.0f;
+                xcol[n] = v;
+                bad |= not_finite(v);
+            }
+            const bool some = __syncthreads_or(bad);
+            if (pass == 0u && !some)
+                continue;
+            found |= some;
+            const float *src = ws + ((size_t)b << (A + HB)) + ((size_t)hi << R);
+#pragma unroll 8
+            for (uint32_t t = tau; t < (1u << A); t += 256u)
+                lds[pad(t)] = src[((size_t)(t >> R) << (HB + R)) | (t & ((1u << R) - 1u))];
+            __syncthreads();
+            transform_window<A, 0, 0>(lds, tau);
+            transform_window<A, 5, 5>(lds, tau);
+            transform_window<A, A - VB, 10>(lds, tau);
+            float s = 0.0f;
+            for (uint32_t n = g; n < tokens; n += G)
+                s = fmaf(lds[pad((n << CB) | a)], xcol[n], s);
+            total += s;
+            ended = __syncthreads_and(total != total);
+        }
+    }
+    __syncthreads();
+    lds[tau] = total;
+    __syncthreads();
+    float v = 0.0f;
+    for (uint32_t k = 0; k < G; ++k)
+        v += lds[k * C + a];
+    return v;
 }
 
 // Block b < C: column b of dW_out, block C + b: row b of dW_in.  Adds the
 // nwg partial vectors part[p][b][0 .. C) in a fixed order (each of the 1024/C
 // thread groups takes every (1024/C)-th, then the groups in order) and applies
 // the channel inverse the tiles left out, over a.
-template <int CB>
+template <int CB, int A, typename T>
 __global__ void __launch_bounds__(256)
-wgrad_final_kernel(const float *__restrict__ part, float *__restrict__ dw_out,
-                   float *__restrict__ dw_in, uint32_t nwg)
+wgrad_final_kernel(const float *__restrict__ part, const uint32_t *__restrict__ seen_words,
+                   float *__restrict__ dw_out, float *__restrict__ dw_in, uint32_t nwg,
+                   uint32_t nwords, const float *__restrict__ wsx, const T *__restrict__ dy,
+                   const float *__restrict__ wsd, const T *__restrict__ x, uint32_t nvalid,
+                   uint32_t live, uint32_t nslices, int HB, int R)
 {
     constexpr uint32_t C = 1u << CB, G = 1024u / C;
-    __shared__ __attribute__((aligned(16))) float red[1024];
+    static_assert(pad(1u << A) >= 1024u, "LDS holds either use");
+    __shared__ __attribute__((aligned(16))) float red[pad(1u << A)];
+    __shared__ uint32_t found[4];
+    __shared__ float xcol[1u << (A - CB)];
     const uint32_t tau = threadIdx.x;
     const bool second = blockIdx.x >= C;
     const uint32_t b = blockIdx.x & (C - 1u);
     const uint32_t a4 = tau & (C / 4u - 1u), pg = tau / (C / 4u);
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(
-                           part + (((size_t)(second ? nwg : 0u)) << (2 * CB)) + ((size_t)b << CB)) +
-                       a4;
-    constexpr uint32_t STRIDE = C * C / 4u;   // f32x4 per partial matrix
-    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
-    uint32_t p = pg;
-    for (; p + 7u * G < nwg; p += 8u * G) {
-        f32x4 u[8];
-#pragma unroll
-        for (uint32_t i = 0; i < 8; ++i)
-            u[i] = src[(size_t)(p + i * G) * STRIDE];
-#pragma unroll
-        for (uint32_t i = 0; i < 8; ++i)
-            s += u[i];
+    uint32_t words = 0u;
+    if constexpr (sizeof(T) == 4) {
+        for (uint32_t i = tau; i < nwords; i += 256u)
+            words |= seen_words[(second ? nwords : 0u) + i];
     }
-    for (; p < nwg; p += G)
-        s += src[(size_t)p * STRIDE];
+    const auto column_sums = [&](uint32_t col) {
+        const f32x4 *src = reinterpret_cast<const f32x4 *>(
+                               part + (((size_t)(second ? nwg : 0u)) << (2 * CB)) +
+                               ((size_t)col << CB)) +
+                           a4;
+        constexpr uint32_t STRIDE = C * C / 4u;   // f32x4 per partial matrix
+        f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+        uint32_t p = pg;
+        for (; p + 7u * G < nwg; p += 8u * G) {
+            f32x4 u[8];
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i)
+                u[i] = src[(size_t)(p + i * G) * STRIDE];
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i)
+                s += u[i];
+        }
+        for (; p < nwg; p += G)
+            s += src[(size_t)p * STRIDE];
+        return s;
+    };
+    const f32x4 s = column_sums(b);
     *reinterpret_cast<f32x4 *>(red + pg * C + 4u * a4) = s;
     __syncthreads();
     float v = 0.0f;
@@ -860,6 +1009,29 @@ wgrad_final_kernel(const float *__restrict__ part, float *__restrict__ dw_out,
             v = (tau & h) ? o - v : v + o;
         }
     }
+    // bits 0-3: Seen's; bit 4: NaN or Inf in the column
+    if (tau < C && not_finite(v))
+        words |= 16u;
+    uint32_t all = 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < 5u; ++i)
+        all |= __builtin_amdgcn_ballot_w64((words >> i) & 1u) != 0u ? 1u << i : 0u;
+    if ((tau & 63u) == 0u)
+        found[tau >> 6] = all;
+    __syncthreads();
+    all = (found[0] | found[1]) | (found[2] | found[3]);
+    const bool tiny = sizeof(T) == 4 && Seen::tiny(all);
+    if (__builtin_expect((all & 16u) || tiny, 0)) {
+        // A row of Z' (dZ) that is not finite leaves no column finite.
+        bool z_finite = false;
+        for (uint32_t k = 1; k < C && !z_finite && !tiny; ++k) {
+            const f32x4 u = column_sums((b + k) & (C - 1u));
+            z_finite = !__syncthreads_or(not_finite(u[0]) || not_finite(u[1]) ||
+                                         not_finite(u[2]) || not_finite(u[3]));
+        }
+        v = exact_column<CB, A, T>(red, xcol, second ? wsd : wsx, second ? x : dy, b, z_finite,
+                                   nvalid, live, nslices, HB, R, tau);
+    }
     if (tau < C) {
         if (second)
             dw_in[(b << CB) | tau] = v;
@@ -876,20 +1048,25 @@ hipError_t launch_k(const WgradTilesArgs &a)
         const uint32_t live = wgrad_live_tiles(K, a.nvalid);
         const uint32_t ntiles = (uint32_t)a.B * live;
         const uint32_t nwg = wgrad_tiles_parts(K, CB, a.dtype, a.B, a.nvalid);
-        if constexpr (wgrad_direct_shape(sp.A, CB))
+        const T *x = static_cast<const T *>(a.x), *dy = static_cast<const T *>(a.dy);
+        uint32_t *words = reinterpret_cast<uint32_t *>(a.part + 2 * ((size_t)nwg << (2 * CB)));
+        uint32_t wave_bits;
+        if constexpr (wgrad_direct_shape(sp.A, CB)) {
+            wave_bits = Wd<sp.A, CB>::WB;
             hipLaunchKernelGGL((wgrad_direct_kernel<sp.A, sp.HB, sp.R, T, CB>), dim3(2u * nwg),
-                               dim3(Wd<sp.A, CB>::THREADS), 0, a.stream, a.wsx,
-                               static_cast<const T *>(a.dy), a.wsd, static_cast<const T *>(a.x),
-                               a.part, a.nvalid, live, ntiles, nwg);
-        else
+                               dim3(Wd<sp.A, CB>::THREADS), 0, a.stream, a.wsx, dy, a.wsd, x,
+                               a.part, words, a.nvalid, live, ntiles, nwg);
+        } else {
+            wave_bits = Wg<sp.A, CB>::WB;
             hipLaunchKernelGGL((wgrad_tiles_kernel<sp.A, sp.HB, sp.R, T, CB>), dim3(2u * nwg),
-                               dim3(Wg<sp.A, CB>::THREADS), 0, a.stream, a.wsx,
-                               static_cast<const T *>(a.dy), a.wsd, static_cast<const T *>(a.x),
-                               a.part, a.nvalid, live, ntiles, nwg);
+                               dim3(Wg<sp.A, CB>::THREADS), 0, a.stream, a.wsx, dy, a.wsd, x,
+                               a.part, words, a.nvalid, live, ntiles, nwg);
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((wgrad_final_kernel<CB>), dim3(2u << CB), dim3(256), 0, a.stream,
-                           a.part, a.dw_out, a.dw_in, nwg);
+        hipLaunchKernelGGL((wgrad_final_kernel<CB, sp.A, T>), dim3(2u << CB), dim3(256), 0,
+                           a.stream, a.part, words, a.dw_out, a.dw_in, nwg, nwg << wave_bits,
+                           a.wsx, dy, a.wsd, x, a.nvalid, live, (uint32_t)a.B, sp.HB, sp.R);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;

@@ -231,6 +231,43 @@ def test_module_backward_float32_range(shape, case, dev, orc):
         check_with_infinities(case, dx, ref, TOL["f32"])
 
 
+@pytest.mark.parametrize("case,dtype", [("inf_dy", "f32"), ("inf_dy", "bf16"), ("inf_x", "f32"),
+                                        ("inf_x", "bf16"), ("nan_dy", "f32"), ("huge_dy", "f32"),
+                                        ("huge_x", "f32"), ("tiny_dy", "f32"), ("tiny_x", "f32")])
+@pytest.mark.parametrize("shape", [(2, 1000, 64), (2, 3000, 64), (1, 9216, 128), (1, 40000, 16)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_weight_gradients_range(shape, case, dtype, dev, orc):
+    """The weight gradients formed over channel frequencies, from operands their bf16
+    terms do not hold, are what the formulas give in float32: an infinity in dY or
+    X gives infinities of the right sign in its own column of dW_out or row of dW_in, the
+    largest finite floats finite sums, operands near the smallest normal float32
+    the float32 bar."""
+    B, N, C = shape
+    x, dy, g, wi, wo = inputs(B, N, C, dtype, seed=80 + N + C)
+    b = B - 1
+    which = ("dw_out",) if "dy" in case else ("dw_in",)   # the other one is all NaN
+    if case.startswith("inf"):
+        t = dy if case == "inf_dy" else x
+        t[0, 5, 3], t[b, N - 1, C - 1], t[b, 77, C - 1] = np.inf, -np.inf, -np.inf
+    elif case == "nan_dy":
+        dy[b, N - 2, 1] = np.nan
+    elif case == "huge_dy":
+        dy[0, 1, 2], x = np.float32(3.4e38), x * np.float32(1e-10)
+    elif case == "huge_x":
+        x[0, 1, 2], dy = np.float32(3.4e38), dy * np.float32(1e-10)
+    else:
+        g, which = g * np.float32(2.0 ** 10), ("dw_in", "dw_out")
+        tiny = np.float32(2.0 ** -121)
+        x, dy = (x, dy * tiny) if case == "tiny_dy" else (x * tiny, dy)
+    say(f"weight gradients {shape} {case} {dtype}")
+    got = run(x, dy, wi, wo, dtype, dev, g=g)
+    with np.errstate(all="ignore"):
+        ref = orc.whtmix_module_grad(x, wi, g, wo, dy)
+        for name in which:
+            i = ("dx", "dw_in", "dw_out").index(name)
+            check_with_infinities(f"{case} {name}", got[i], ref[i], GRAD_TOL)
+
+
 def test_module_backward_empty_batch_zeroes_gradients(dev):
     import torch
 
