@@ -30,9 +30,10 @@
 //   rounding, at 2.7 times the rate of the fp32 instruction.
 // The terms of Inf, of |v| past the largest bf16 (rounded) and, below 2^-110, of
 // the smallest floats are not v, and an infinite sum over channel frequencies says
-// nothing of the channels.  A column that comes out NaN or Inf, and both matrices of
-// float32 operands that are tiny throughout (Seen), are formed again in float32
-// by the final sum (exact_column).
+// nothing of the channels.  A column that comes out NaN or Inf, and the matrix of a
+// float32 operand that is tiny throughout (Seen), are formed again in float32 by the
+// final sum (exact_column).  For that the float32 kernels look at every operand:
+// 28.6 -> 30.6 us on 2 slices of 36864 x 64, and 4.8 -> 5.5 us for the sum.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -894,7 +895,9 @@ __device__ __forceinline__ bool not_finite(float v)
 // column (tau < C).  z_finite: Z' (dZ) is finite throughout, so that a column that
 // is not has its infinities and NaN from dY / X, and only the tiles that hold them
 // are looked at; otherwise, or if there are none, every tile.  A column that is NaN
-// throughout ends the loop.  Rare, so simple rather than fast.
+// throughout ends the loop.  Rare, so simple rather than fast: the backward of 4 x
+// 65536 x 128 bf16 takes 2.5 ms with one Inf in dY (0.4 without), of 2 x 36864 x 64
+// float32 0.4 ms; with operands that are tiny throughout, 6.8 ms.
 template <int CB, int A, typename T>
 __device__ float exact_column(float *lds, float *xcol, const float *ws, const T *xs, uint32_t col,
                               bool z_finite, uint32_t nvalid, uint32_t live, uint32_t nslices,
@@ -1022,9 +1025,10 @@ wgrad_final_kernel(const float *__restrict__ part, const uint32_t *__restrict__ 
     all = (found[0] | found[1]) | (found[2] | found[3]);
     const bool tiny = sizeof(T) == 4 && Seen::tiny(all);
     if (__builtin_expect((all & 16u) || tiny, 0)) {
-        // A row of Z' (dZ) that is not finite leaves no column finite.
+        // A row of Z' (dZ) that is not finite leaves no column finite: one finite
+        // neighbour shows that there is none.
         bool z_finite = false;
-        for (uint32_t k = 1; k < C && !z_finite && !tiny; ++k) {
+        for (uint32_t k = 1; k <= 8u && !z_finite && !tiny; ++k) {
             const f32x4 u = column_sums((b + k) & (C - 1u));
             z_finite = !__syncthreads_or(not_finite(u[0]) || not_finite(u[1]) ||
                                          not_finite(u[2]) || not_finite(u[3]));
