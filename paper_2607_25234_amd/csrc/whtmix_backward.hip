@@ -31,11 +31,11 @@ using namespace tile;
 // workgroup owns one workspace run (2^HB x 2^R elements) for a chunk of
 // slices: forward over the HB high bits for both operands, multiply,
 // accumulate; then 2^-K times the sum is stored at the run's positions of G.
-// LIVE: only the first `live` rows of the tiles exist (with_live).
-template <int A, int HB, int R, bool LIVE>
+// ROWS: registers of a tile whose rows exist (with_rows).
+template <int A, int HB, int R, int ROWS>
 __global__ void __launch_bounds__(1 << (HB + R - VB))
 grad_middle_kernel(const float *__restrict__ wsx, const float *__restrict__ wsd,
-                   float *__restrict__ out, uint32_t nslices, uint32_t per_chunk, uint32_t live)
+                   float *__restrict__ out, uint32_t nslices, uint32_t per_chunk)
 {
     constexpr int M = HB + R;
     using G = Groups<M, R>;
@@ -53,8 +53,8 @@ grad_middle_kernel(const float *__restrict__ wsx, const float *__restrict__ wsd,
     for (uint32_t b = b0; b < b1; ++b) {   // uniform over the workgroup
         const size_t off = ((size_t)b << (A + HB)) + ((size_t)run << M);
         float vx[V], vd[V];
-        load_middle<G::TOP, M, LIVE>(vx, wsx + off, live << R, tau);
-        load_middle<G::TOP, M, LIVE>(vd, wsd + off, live << R, tau);
+        load_middle<G::TOP, M, ROWS>(vx, wsx + off, tau);
+        load_middle<G::TOP, M, ROWS>(vd, wsd + off, tau);
         butterflies<G::JT, VB>(vx);
         butterflies<G::JT, VB>(vd);
         forward_groups<M, R, 0, G::TOP, true>(lds, vx, tau);
@@ -197,18 +197,17 @@ __device__ __forceinline__ void sep_tile_sums_single(
 // back to wsx (the forward mixer's middle pass on x, for the block's backward,
 // which needs Z' as well), after the product and before the next slice's load.
 //
-// LIVE: only the first `live` rows of the tiles exist (with_live).
+// ROWS: registers of a tile whose rows exist (with_rows).
 //
 // SEPSUM (separable gains, R = 5, HB >= 6, R <= log2 C <= A): instead of
 // storing dG the workgroup forms the two log-gain gradients' partial sums of
 // dG * G over its tile and writes them to rowpart / colpart (sep_tile_sums
 // with several slices per chunk, sep_tile_sums_single with one).
-template <int A, int HB, int R, class Gain, bool SINGLE, bool MIX_X, bool SEPSUM, bool LIVE>
+template <int A, int HB, int R, class Gain, bool SINGLE, bool MIX_X, bool SEPSUM, int ROWS>
 __global__ void __launch_bounds__(1 << (HB + R - VB))
 grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain gain,
                        float *__restrict__ out, uint32_t nslices, uint32_t per_chunk,
-                       float *__restrict__ rowpart, float *__restrict__ colpart, uint32_t cbits,
-                       uint32_t live)
+                       float *__restrict__ rowpart, float *__restrict__ colpart, uint32_t cbits)
 {
     constexpr int M = HB + R;
     using G = Groups<M, R>;
@@ -229,8 +228,8 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
                       : out + ((size_t)chunk << (A + HB)) + ((size_t)run << R) +
                             GM::at(layout_base<G::SL>(tau));
     float vx[V], vd[V];
-    load_middle<G::TOP, M, LIVE>(vx, tile(wsx, b0), live << R, tau);
-    load_middle<G::TOP, M, LIVE>(vd, tile(wsd, b0), live << R, tau);
+    load_middle<G::TOP, M, ROWS>(vx, tile(wsx, b0), tau);
+    load_middle<G::TOP, M, ROWS>(vd, tile(wsd, b0), tau);
     if constexpr (SINGLE) {
         butterflies<G::JT, VB>(vx);
         butterflies<G::JT, VB>(vd);
@@ -254,13 +253,13 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
             if constexpr (G::NBOT > 0)
                 inverse_groups<M, R, G::NBOT - 1>(lds, vx, tau);
             butterflies<G::JT, VB>(vx);
-            store_middle<G::TOP, M, LIVE>(vx, tile(wsx, b0), live << R, tau);
+            store_middle<G::TOP, M, ROWS>(vx, tile(wsx, b0), tau);
         }
         apply_gain<A + HB>(vd, gv);
         if constexpr (G::NBOT > 0)
             inverse_groups<M, R, G::NBOT - 1>(lds, vd, tau);
         butterflies<G::JT, VB>(vd);
-        store_middle<G::TOP, M, LIVE>(vd, tile(wsd, b0), live << R, tau);
+        store_middle<G::TOP, M, ROWS>(vd, tile(wsd, b0), tau);
     } else {
         float acc[V], gv[V];
 #pragma unroll
@@ -281,17 +280,17 @@ grad_mix_middle_kernel(float *__restrict__ wsx, float *__restrict__ wsd, Gain ga
                 if constexpr (G::NBOT > 0)
                     inverse_groups<M, R, G::NBOT - 1>(lds, vx, tau);
                 butterflies<G::JT, VB>(vx);
-                store_middle<G::TOP, M, LIVE>(vx, tile(wsx, b), live << R, tau);
+                store_middle<G::TOP, M, ROWS>(vx, tile(wsx, b), tau);
             }
             if (more)
-                load_middle<G::TOP, M, LIVE>(vx, tile(wsx, b + 1), live << R, tau);
+                load_middle<G::TOP, M, ROWS>(vx, tile(wsx, b + 1), tau);
             apply_gain<A + HB>(vd, gv);
             if constexpr (G::NBOT > 0)
                 inverse_groups<M, R, G::NBOT - 1>(lds, vd, tau);
             butterflies<G::JT, VB>(vd);
-            store_middle<G::TOP, M, LIVE>(vd, tile(wsd, b), live << R, tau);
+            store_middle<G::TOP, M, ROWS>(vd, tile(wsd, b), tau);
             if (more)
-                load_middle<G::TOP, M, LIVE>(vd, tile(wsd, b + 1), live << R, tau);
+                load_middle<G::TOP, M, ROWS>(vd, tile(wsd, b + 1), tau);
         }
         if constexpr (SEPSUM) {
             float p[V];
@@ -688,11 +687,10 @@ hipError_t grad_three_pass(const T *x, const T *dy, float *dst, const BackwardAr
     if ((e = launch_outer_fwd<K, T>(x, wsx, a.B, a.nvalid, st)) != hipSuccess) return e;
     if ((e = launch_outer_fwd<K, T>(dy, wsd, a.B, a.nvalid, st)) != hipSuccess) return e;
     float *o = lay.nchunks > 1 ? a.ws + lay.part : dst;
-    const uint32_t live = live_tiles(a.nvalid, A);
-    return with_live(live, HB, [&](auto l) {
-        hipLaunchKernelGGL((grad_middle_kernel<A, HB, R, decltype(l)::value>),
+    return with_rows(a.nvalid, A, HB, [&](auto n) {
+        hipLaunchKernelGGL((grad_middle_kernel<A, HB, R, decltype(n)::value>),
                            dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st, wsx,
-                           wsd, o, (uint32_t)a.B, lay.per_chunk, live);
+                           wsd, o, (uint32_t)a.B, lay.per_chunk);
         return hipGetLastError();
     });
 }
@@ -888,7 +886,6 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
     const hipStream_t st = a.stream;
     float *wsx = a.ws + lay.wsx;
     float *wsd = a.ws + lay.wsd;
-    const uint32_t live = live_tiles(a.nvalid, A);
     hipError_t e;
     if constexpr (std::is_same_v<Gain, LogSeparableGain> && R == VB && HB >= 6 &&
                   HB + R <= kMaxTile) {
@@ -898,13 +895,12 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
             // per chunk; the one-slice form for 2^15), then one small kernel
             // adds them up
             constexpr bool single = HB + R == kMaxTile;
-            e = with_live(live, HB, [&](auto l) {
+            e = with_rows(a.nvalid, A, HB, [&](auto n) {
                 hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, Gain, single, MIX_X, true,
-                                                           decltype(l)::value>),
+                                                           decltype(n)::value>),
                                    dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
                                    wsx, wsd, gain, nullptr, (uint32_t)a.B, lay.per_chunk,
-                                   a.ws + lay.rowpart, a.ws + lay.fcolpart, (uint32_t)a.cbits,
-                                   live);
+                                   a.ws + lay.rowpart, a.ws + lay.fcolpart, (uint32_t)a.cbits);
                 return hipGetLastError();
             });
             if (e != hipSuccess) return e;
@@ -921,11 +917,11 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
     float *o = lay.nchunks > 1 ? a.ws + lay.part : dst;
     if (lay.per_chunk == 1) {
         e = with_middle_gain(gain, a.B, [&](auto g) {
-            return with_live(live, HB, [&](auto l) {
+            return with_rows(a.nvalid, A, HB, [&](auto n) {
                 hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, decltype(g), true, MIX_X,
-                                                           false, decltype(l)::value>),
+                                                           false, decltype(n)::value>),
                                    dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
-                                   wsx, wsd, g, o, (uint32_t)a.B, 1u, nullptr, nullptr, 0u, live);
+                                   wsx, wsd, g, o, (uint32_t)a.B, 1u, nullptr, nullptr, 0u);
                 return hipGetLastError();
             });
         });
@@ -935,12 +931,12 @@ hipError_t grad_middle_phase(const BackwardArgs &a, const BackwardLayout &lay, f
         // slices: a joint gain streams (non-temporal), so it does not displace
         // the two workspaces
         e = with_streamed_gain(gain, [&](auto g) {
-            return with_live(live, HB, [&](auto l) {
+            return with_rows(a.nvalid, A, HB, [&](auto n) {
                 hipLaunchKernelGGL((grad_mix_middle_kernel<A, HB, R, decltype(g), false, MIX_X,
-                                                           false, decltype(l)::value>),
+                                                           false, decltype(n)::value>),
                                    dim3(lay.nchunks << (A - R)), dim3(1u << (HB + R - VB)), 0, st,
                                    wsx, wsd, g, o, (uint32_t)a.B, lay.per_chunk, nullptr, nullptr,
-                                   0u, live);
+                                   0u);
                 return hipGetLastError();
             });
         });

@@ -102,10 +102,10 @@ fused_pair_kernel(const T *__restrict__ x, T *__restrict__ y, Gain gain, uint32_
 // MIDDLE: logical tile = run * B + b (the B slices sharing a gain tile are
 // adjacent); workgroups are renumbered so adjacent logical tiles land on the
 // same XCD (blocks are dealt round-robin over the 8 XCDs) and share its L2.
-// LIVE: only the first `live` rows of the tile exist (with_live).
-template <int A, int HB, int R, class Gain, bool LIVE>
+// ROWS: registers of a tile whose rows exist (with_rows).
+template <int A, int HB, int R, class Gain, int ROWS>
 __global__ void __launch_bounds__(1 << (HB + R - VB))
-middle_kernel(float *__restrict__ ws, Gain gain, uint32_t nslices, uint32_t live)
+middle_kernel(float *__restrict__ ws, Gain gain, uint32_t nslices)
 {
     constexpr int M = HB + R;
     using G = Groups<M, R>;
@@ -119,7 +119,7 @@ middle_kernel(float *__restrict__ ws, Gain gain, uint32_t nslices, uint32_t live
     const size_t b = logical - run * nslices;
     float *const tile = ws + (b << (A + HB)) + ((size_t)run << M);
     float v[V], gv[V];
-    load_middle<G::TOP, M, LIVE>(v, tile, live << R, tau);
+    load_middle<G::TOP, M, ROWS>(v, tile, tau);
     gain.template load<G::SL, GainMap<A, R>, true>(gv, run << R, tau);
     butterflies<G::JT, VB>(v);
     forward_groups<M, R, 0, G::TOP>(lds, v, tau);
@@ -127,7 +127,7 @@ middle_kernel(float *__restrict__ ws, Gain gain, uint32_t nslices, uint32_t live
     if constexpr (G::NBOT > 0)
         inverse_groups<M, R, G::NBOT - 1>(lds, v, tau);
     butterflies<G::JT, VB>(v);
-    store_middle<G::TOP, M, LIVE>(v, tile, live << R, tau);
+    store_middle<G::TOP, M, ROWS>(v, tile, tau);
 }
 
 // MIDDLE over slice groups (nb > 1, middle_slices_per_group): workgroup w
@@ -140,9 +140,9 @@ middle_kernel(float *__restrict__ ws, Gain gain, uint32_t nslices, uint32_t live
 // middle_kernel measured 51.2 us here, and prefetching the next slice's tile
 // into registers 50.4 us.  The first tile's loads go out before the gain's
 // (49.0 against 50.0 us, averaged with cold calls).
-template <int A, int HB, int R, class Gain, bool LIVE>
+template <int A, int HB, int R, class Gain, int ROWS>
 __global__ void __launch_bounds__(1 << (HB + R - VB))
-middle_group_kernel(float *__restrict__ ws, Gain gain, uint32_t nb, uint32_t live)
+middle_group_kernel(float *__restrict__ ws, Gain gain, uint32_t nb)
 {
     constexpr int M = HB + R;
     using G = Groups<M, R>;
@@ -152,7 +152,7 @@ middle_group_kernel(float *__restrict__ ws, Gain gain, uint32_t nb, uint32_t liv
     float *const base = ws + (((size_t)(blockIdx.x >> (A - R)) * nb) << (A + HB)) +
                         ((size_t)run << M);
     float v[V], gv[V];
-    load_middle<G::TOP, M, LIVE>(v, base, live << R, tau);
+    load_middle<G::TOP, M, ROWS>(v, base, tau);
     gain.template load<G::SL, GainMap<A, R>, true>(gv, run << R, tau);   // needed later
 #pragma unroll 1
     for (uint32_t j = 0; j < nb; ++j) {
@@ -162,9 +162,9 @@ middle_group_kernel(float *__restrict__ ws, Gain gain, uint32_t nb, uint32_t liv
         if constexpr (G::NBOT > 0)
             inverse_groups<M, R, G::NBOT - 1>(lds, v, tau);
         butterflies<G::JT, VB>(v);
-        store_middle<G::TOP, M, LIVE>(v, base + ((size_t)j << (A + HB)), live << R, tau);
+        store_middle<G::TOP, M, ROWS>(v, base + ((size_t)j << (A + HB)), tau);
         if (j + 1 < nb)
-            load_middle<G::TOP, M, LIVE>(v, base + ((size_t)(j + 1) << (A + HB)), live << R, tau);
+            load_middle<G::TOP, M, ROWS>(v, base + ((size_t)(j + 1) << (A + HB)), tau);
     }
 }
 
@@ -237,19 +237,17 @@ hipError_t launch_middle_split(const LaunchArgs &a, Gain gain)
 {
     static_assert(HB >= 1 && HB + R >= kMinTile && HB + R <= kMaxTile, "middle tile size");
     const long long nb = middle_slices_per_group(a.B, A - R, HB + R - VB);
-    const uint32_t live = live_tiles(a.nvalid, A);
     return with_forward_middle_gain(gain, a.B, A + HB, [&](auto g) {
-        return with_live(live, HB, [&](auto l) {
-            constexpr bool LIVE = decltype(l)::value;
+        return with_rows(a.nvalid, A, HB, [&](auto n) {
+            constexpr int ROWS = decltype(n)::value;
             if (nb > 1)
-                hipLaunchKernelGGL((middle_group_kernel<A, HB, R, decltype(g), LIVE>),
+                hipLaunchKernelGGL((middle_group_kernel<A, HB, R, decltype(g), ROWS>),
                                    dim3((uint32_t)((a.B / nb) << (A - R))),
-                                   dim3(1u << (HB + R - VB)), 0, a.stream, a.ws, g, (uint32_t)nb,
-                                   live);
+                                   dim3(1u << (HB + R - VB)), 0, a.stream, a.ws, g, (uint32_t)nb);
             else
-                hipLaunchKernelGGL((middle_kernel<A, HB, R, decltype(g), LIVE>),
+                hipLaunchKernelGGL((middle_kernel<A, HB, R, decltype(g), ROWS>),
                                    dim3((uint32_t)(a.B << (A - R))), dim3(1u << (HB + R - VB)), 0,
-                                   a.stream, a.ws, g, (uint32_t)a.B, live);
+                                   a.stream, a.ws, g, (uint32_t)a.B);
             return hipGetLastError();
         });
     });

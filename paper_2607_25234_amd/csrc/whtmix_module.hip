@@ -1340,7 +1340,7 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds,
     const size_t b = blk >> HB;
     const uint32_t hi = blk & ((1u << HB) - 1u);
     const uint32_t valid = tile_valid<A>(nvalid, hi);
-    if (valid == 0)
+    if (hi >= middle_rows(nvalid, A, HB))
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     const T *const tile = x + b * nvalid + ((size_t)hi << A);
     XFrag<T, CB> f;
@@ -1576,7 +1576,7 @@ __device__ __forceinline__ void module_outer_fwd_pair_tile(float *lds, const __b
     const size_t b = blk >> HB;
     const uint32_t hi = blk & ((1u << HB) - 1u);
     const uint32_t valid = tile_valid<A>(nvalid, hi);
-    if (valid == 0)
+    if (hi >= middle_rows(nvalid, A, HB))
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     bf16x8 a[kPairKs];
     load_x_pair(a, x + b * nvalid + ((size_t)hi << A), valid, tau);

@@ -336,49 +336,32 @@ __device__ __forceinline__ void store_layout(const float (&v)[V], __amdgpu_buffe
                                    soff0 + Map::at((uint32_t)k << S) * Elt<T>::bytes);
 }
 
-// Loads and stores of a middle tile of which only the first rows exist (the
-// outer tiles of a zero-padded slice past its last real token are neither
-// transformed nor stored): r covers those rows only, so that loads past them
-// return 0 and stores past them are dropped.  The whole offset is in the
-// vector operand, since the bounds check leaves out the scalar one.
-template <int S, typename T>
-__device__ __forceinline__ void load_live(float (&v)[V], __amdgpu_buffer_rsrc_t r, uint32_t tau)
+// A middle tile of 2^M floats at base in layout S = M-5 (registers: the top five
+// tile bits), of which the first N registers' rows exist (N = 0: all; with_rows).
+// The others are zero in registers and not stored.  No access is out of range: a
+// buffer load or store past the resource's end costs as much as several that are
+// not (8 slices of 2^19 float32, 56% real, in the gradient's middle pass: 16.0 us
+// with checked accesses to whole tiles, 13.9 reading zeros).
+template <int S, int M, int N>
+__device__ __forceinline__ void load_middle(float (&v)[V], const float *base, uint32_t tau)
 {
-    const uint32_t voff = layout_base<S>(tau) * Elt<T>::bytes;
+    static_assert(S == M - VB, "registers hold the top tile bits");
+    const __amdgpu_buffer_rsrc_t r = buffer(base, (1u << M) * 4u);
+    const uint32_t voff = layout_base<S>(tau) * 4u;
 #pragma unroll
     for (int k = 0; k < V; ++k)
-        v[k] = Elt<T>::load(r, voff + ((uint32_t)k << S) * Elt<T>::bytes, 0);
+        v[k] = N == 0 || k < N ? Elt<float>::load(r, voff, ((uint32_t)k << S) * 4u) : 0.0f;
 }
 
-template <int S, typename T>
-__device__ __forceinline__ void store_live(const float (&v)[V], __amdgpu_buffer_rsrc_t r,
-                                           uint32_t tau)
+template <int S, int M, int N>
+__device__ __forceinline__ void store_middle(const float (&v)[V], float *base, uint32_t tau)
 {
-    const uint32_t voff = layout_base<S>(tau) * Elt<T>::bytes;
+    static_assert(S == M - VB, "registers hold the top tile bits");
+    const __amdgpu_buffer_rsrc_t r = buffer(base, (1u << M) * 4u);
+    const uint32_t voff = layout_base<S>(tau) * 4u;
 #pragma unroll
-    for (int k = 0; k < V; ++k)
-        Elt<T>::store(v[k], r, voff + ((uint32_t)k << S) * Elt<T>::bytes, 0);
-}
-
-// A middle tile of 2^M floats at base, its first `live` floats only with LIVE.
-template <int S, int M, bool LIVE>
-__device__ __forceinline__ void load_middle(float (&v)[V], const float *base, uint32_t live,
-                                            uint32_t tau)
-{
-    if constexpr (LIVE)
-        load_live<S, float>(v, buffer(base, live * 4u), tau);
-    else
-        load_layout<S, ContigMap, float>(v, buffer(base, (1u << M) * 4u), tau);
-}
-
-template <int S, int M, bool LIVE>
-__device__ __forceinline__ void store_middle(const float (&v)[V], float *base, uint32_t live,
-                                             uint32_t tau)
-{
-    if constexpr (LIVE)
-        store_live<S, float>(v, buffer(base, live * 4u), tau);
-    else
-        store_layout<S, ContigMap, float>(v, buffer(base, (1u << M) * 4u), tau);
+    for (int k = 0; k < (N == 0 ? V : N); ++k)
+        Elt<float>::store(v[k], r, voff, ((uint32_t)k << S) * 4u);
 }
 
 // Masked forms for the one tile of a zero-padded slice that straddles the
@@ -685,23 +668,30 @@ __device__ __forceinline__ uint32_t tile_valid(uint32_t nvalid, uint32_t hi)
     return nvalid <= start ? 0u : min(nvalid - start, 1u << A);
 }
 
-// Outer tiles of a slice that hold real elements.  The others, wholly zero
-// padding, are skipped by OUTER_FWD and OUTER_INV, and the middle pass neither
-// reads nor writes their workspace rows (with_live).  Of 2 slices of 36864 x 64
-// (of 65536) 44% of the workspace traffic was zeros: their middle pass 17.4 ->
-// 12.8 us, the backward's 26.3 -> 20.8 us.
-inline uint32_t live_tiles(uint32_t nvalid, int A)
+// Rows (outer tiles) of a slice that the workspace holds: those with real elements,
+// rounded up to an eighth of all, so that a middle tile's registers hold rows that
+// exist or rows that do not.  OUTER_FWD and the middle pass leave the others,
+// wholly zero padding, out (with_rows); OUTER_INV leaves out every padded tile.  Of 2
+// slices of 36864 x 64 (of 65536) 44% of the workspace traffic was zeros: their
+// middle pass 17.4 -> 12.8 us, the backward's 26.3 -> 20.8 us.
+__host__ __device__ inline uint32_t middle_rows(uint32_t nvalid, int A, int HB)
 {
-    return (uint32_t)(((uint64_t)nvalid + (uint64_t(1) << A) - 1) >> A);
+    const uint32_t unit = HB > 3 ? 1u << (HB - 3) : 1u;
+    const uint32_t rows = (uint32_t)(((uint64_t)nvalid + (uint64_t(1) << A) - 1) >> A);
+    return (rows + unit - 1u) & ~(unit - 1u);
 }
 
-// Calls f with a compile-time flag: whether a middle pass over slices of 2^HB
-// outer tiles has rows to leave out.  Slices without padding keep the plain
-// accesses, whose register offsets cost no vector arithmetic.
+// Calls f with the number of layout M-5 registers whose rows exist, a compile-time
+// constant, 0 for all of them.  (N_pad is the next power of two of N, so more than
+// half of the rows always do.)
 template <class F>
-inline hipError_t with_live(uint32_t live, int HB, F &&f)
+inline hipError_t with_rows(uint32_t nvalid, int A, int HB, F &&f)
 {
-    return live < (1u << HB) ? f(std::true_type{}) : f(std::false_type{});
+    const uint32_t n = (middle_rows(nvalid, A, HB) * (uint32_t)V) >> HB;
+    if (n <= 20u) return f(std::integral_constant<int, 20>{});
+    if (n <= 24u) return f(std::integral_constant<int, 24>{});
+    if (n <= 28u) return f(std::integral_constant<int, 28>{});
+    return f(std::integral_constant<int, 0>{});
 }
 
 // OUTER_FWD tile (forward pass and backward pass): block = b * 2^HB + hi;
@@ -720,7 +710,7 @@ __device__ __forceinline__ void outer_fwd_tile(float *lds, const T *__restrict__
     const size_t b = blk >> HB;
     const uint32_t hi = blk & ((1u << HB) - 1u);
     const uint32_t valid = tile_valid<A>(nvalid, hi);
-    if (valid == 0)
+    if (hi >= middle_rows(nvalid, A, HB))
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     const T *src = x + b * nvalid + ((size_t)hi << A);
     const __amdgpu_buffer_rsrc_t r =
@@ -830,7 +820,7 @@ __device__ __forceinline__ void outer_fwd_tile2(float *lds, const T *__restrict_
     const size_t b = blk >> HB;
     const uint32_t hi = blk & ((1u << HB) - 1u);
     const uint32_t valid = tile_valid<A>(nvalid, hi);
-    if (valid == 0)
+    if (hi >= middle_rows(nvalid, A, HB))
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
     const uint32_t valid0 = min(valid, 1u << M);
     const uint32_t valid1 = valid > (1u << M) ? valid - (1u << M) : 0u;
@@ -878,7 +868,7 @@ outer_fwd_kernel2(const T *__restrict__ x, float *__restrict__ ws, uint32_t nval
 // and stored, since one 1024-thread workgroup per CU leaves no other
 // workgroup to cover the load latency.  With two operands (x1, ws1 not
 // null) tiles ntiles.. 2 ntiles - 1 are those of x1, as in outer_fwd2_kernel2.
-template <int HB, int R, bool LIVE>
+template <int HB, int R, bool LEAVE_OUT>
 __global__ void __launch_bounds__(1 << (15 - VB))
 outer_fwd_kernel2_pf(const __bf16 *__restrict__ x0, float *__restrict__ ws0,
                      const __bf16 *__restrict__ x1, float *__restrict__ ws1, uint32_t nvalid,
@@ -931,8 +921,8 @@ outer_fwd_kernel2_pf(const __bf16 *__restrict__ x0, float *__restrict__ ws0,
         const uint32_t hi = blk & ((1u << HB) - 1u);
         const __bf16 *x = second ? x1 : x0;
         float *ws = second ? ws1 : ws0;
-        if constexpr (LIVE) {
-            if (tile_valid<A>(nvalid, hi) == 0) {   // wholly padding (uniform per workgroup)
+        if constexpr (LEAVE_OUT) {
+            if (hi >= middle_rows(nvalid, A, HB)) {   // uniform per workgroup
                 have = t + gridDim.x < total && issue(t + gridDim.x);
                 continue;
             }
@@ -1056,8 +1046,8 @@ hipError_t launch_outer_fwd(const T *x, float *ws, int64_t B, uint32_t nvalid, h
         if constexpr (sizeof(T) == 2 && VW == 3) {
             if (vec) {
                 const uint32_t ntiles = (uint32_t)(B << sp.HB);
-                return with_live(live_tiles(nvalid, sp.A), sp.HB, [&](auto l) {
-                    hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R, decltype(l)::value>),
+                return with_rows(nvalid, sp.A, sp.HB, [&](auto n) {
+                    hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R, decltype(n)::value != 0>),
                                        dim3(ntiles < 256u ? ntiles : 256u), block, 0, st, x, ws,
                                        (const __bf16 *)nullptr, (float *)nullptr, nvalid, ntiles);
                     return hipGetLastError();
@@ -1095,8 +1085,8 @@ hipError_t launch_outer_fwd2(const T *x, const T *dy, float *wsx, float *wsd, in
         if constexpr (sizeof(T) == 2 && VW == 3) {
             if (vec) {
                 const uint32_t ntiles = (uint32_t)(B << sp.HB);
-                return with_live(live_tiles(nvalid, sp.A), sp.HB, [&](auto l) {
-                    hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R, decltype(l)::value>),
+                return with_rows(nvalid, sp.A, sp.HB, [&](auto n) {
+                    hipLaunchKernelGGL((outer_fwd_kernel2_pf<sp.HB, sp.R, decltype(n)::value != 0>),
                                        dim3(2u * ntiles < 256u ? 2u * ntiles : 256u), block, 0, st,
                                        x, wsx, dy, wsd, nvalid, ntiles);
                     return hipGetLastError();

@@ -11,10 +11,11 @@ from tests.gpu_util import DERIVED, device, errors, say, to_device, to_host
 
 pytestmark = pytest.mark.gpu
 
-# (B, N, C): one real outer tile past half of them, one short of all, a
-# straddling tile, slice groups in the middle pass (B = 4 of 2^21), pair tiles
+# (B, N, C): five eighths of the rows kept (one real outer tile past half of them, a
+# straddling tile, slice groups in the middle pass with B = 4 of 2^21), six and
+# seven eighths, and all of them with one tile padded
 SHAPES = [(1, 9216, 64), (2, 4097, 64), (3, 2040, 128), (1, 36864, 64), (4, 9000, 128),
-          (1, 600, 128), (2, 25600, 32)]
+          (1, 600, 128), (2, 25600, 32), (1, 700, 128), (64, 700, 64)]
 
 
 @pytest.fixture(scope="module")

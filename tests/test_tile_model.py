@@ -829,3 +829,21 @@ def test_outer_renumbering(R):
             inv = {v: b for b, v in enumerate(m)}
             for hi0 in range(0, nblk, g):
                 assert len({inv[hi0 + j] % 8 for j in range(g)}) == 1
+
+
+@pytest.mark.parametrize("HB", range(1, 16))
+def test_rows_left_out_of_the_middle_pass(HB):
+    """middle_rows and with_rows: the kept rows cover every real outer tile, and a
+    middle tile's registers (layout M-5, register k: elements k << (M-5) on) below the
+    chosen count hold kept rows only, those from it on none of them."""
+    R = max(5, 11 - HB) if HB <= 10 else max(0, 15 - HB)
+    M = HB + R
+    unit = 1 << (HB - 3) if HB > 3 else 1
+    for real in range((1 << HB) // 2 + 1, (1 << HB) + 1):   # N > N_pad / 2
+        rows = (real + unit - 1) & ~(unit - 1)
+        assert real <= rows <= 1 << HB
+        n = (rows * 32) >> HB
+        assert (rows * 32) % (1 << HB) == 0 and 17 <= n <= 32
+        regs = 20 if n <= 20 else 24 if n <= 24 else 28 if n <= 28 else 32
+        # register k's rows: elements [k, k + 1) << (M - 5), rows of 2^R elements
+        assert regs << (M - 5) == rows << R
