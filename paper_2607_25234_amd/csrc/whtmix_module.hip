@@ -1289,9 +1289,12 @@ __device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const 
         project_out<T, CB, M>(v, wl, tile, valid, tau);
 }
 
-// FUSED: one workgroup per slice (M = K).
+// FUSED: one workgroup per slice (M = K).  2^14 tiles from C = 64 are held to 128
+// registers, so that two workgroups share a CU as their LDS allows (left alone
+// they took 130 to 152; 2048 slices of 128 x 128 bf16 95.6 -> 67.1 us, of 256 x 64
+// float32 137 -> 116 us; C = 32 takes 122 and is slower with the bound, 87 -> 91).
 template <int K, typename T, class Gain, int CB>
-__global__ void __launch_bounds__(1 << (K - VB))
+__global__ void __launch_bounds__((1 << (K - VB)), (K == 14 && CB >= 6 ? 4 : 1))
 module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
                     const T *__restrict__ w_out, T *__restrict__ y, Gain gain, uint32_t nvalid)
 {
