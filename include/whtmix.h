@@ -287,10 +287,11 @@ WHTMIX_API int whtmix_backward_separable(const void *x, const void *dy,
  * residual below 2^-17), and y is rounded to nearest even once.  For
  * 16 <= C <= 128, and for bf16 C = 256 from N_pad*C = 2^17, the projections
  * run on the matrix cores inside the mixer's first and last kernels (three
- * kernels for N_pad*C > 2^15, plus a small weight-repacking kernel for C = 256;
+ * kernels for N_pad*C > 2^15, plus a small weight-repacking kernel for C = 256 and
+ * for bf16 C = 128 on many slices of 2^16 or 2^17 elements;
  * whtmix_plan_describe's module_path says which); other shapes run separate
  * projection kernels around the float32 mixer.  Workspace: the mixer's, plus
- * 2*C*C elements of packed weights (C = 256, and the separate kernels) and
+ * 2*C*C elements of packed weights (where they are repacked, and the separate kernels) and
  * B*N*C floats of Z (the separate kernels).  Other conventions, plans and options as
  * whtmix_forward_ex (events: for the three-pass plan around each of its
  * three passes, otherwise [0] before and [1] after the call's kernels).

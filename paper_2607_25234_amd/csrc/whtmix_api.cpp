@@ -535,7 +535,10 @@ int module_impl(const void *x, const void *w_in, int gain_kind, const float *gai
     // FUSED_MFMA with C = 256: the packed weights; UNFUSED: Z, then the packed weights
     const int64_t zbytes = path == whtmix::MODULE_UNFUSED ? (B * N * C * 4 + 255) / 256 * 256 : 0;
     const int64_t extra =
-        zbytes + (whtmix::module_packs_weights(path, cbits)
+        zbytes + (whtmix::module_packs_weights(path, cbits) ||
+                          (path == whtmix::MODULE_FUSED_MFMA &&
+                           c.plan == whtmix::PLAN_THREE_PASS &&
+                           whtmix::module_packs_for_tiles(dtype, cbits, c.K, B))
                       ? 2 * whtmix::module_packed_bytes(cbits, dtype)
                       : 0);
     const int64_t off = (mix + 255) / 256 * 256;
@@ -643,7 +646,8 @@ int module_backward_impl(const void *x, const void *w_in, int gain_kind, const f
     m.tiles = fused && c.K <= 25 &&
               whtmix::wgrad_tiles_shape(whtmix::module_split(c.K).A, cbits);
     const int64_t zb = m.tiles ? 0 : align256(rows * C * 4);
-    const int64_t pk = fused && cbits <= whtmix::kModuleMfmaMaxCbits
+    const int64_t pk = fused && cbits <= whtmix::kModuleMfmaMaxCbits &&
+                               !whtmix::module_packs_for_tiles(dtype, cbits, c.K, B)
                            ? 0
                            : align256(3 * whtmix::module_packed_bytes(cbits, dtype));
     const whtmix::WgradPlan wp = whtmix::wgrad_plan((uint64_t)rows, cbits);

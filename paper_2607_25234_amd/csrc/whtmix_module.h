@@ -52,6 +52,21 @@ inline bool module_packs_weights(int path, int cbits)
     return path == MODULE_UNFUSED || (path == MODULE_FUSED_MFMA && cbits > kModuleMfmaMaxCbits);
 }
 
+// Except that a thousand one-wave workgroups and more, each with a matrix eight
+// times its tile, read a matrix repacked once per call: bf16, C = 128, 2^11 outer
+// tiles.  The packing launch takes 3 to 5 us; at 512 x 128 and 1024 x 128 tokens the
+// forward takes 17.9 us packed and 18.1 with the weights as they lie at 512 tiles,
+// 28.1 and 28.7 at 1024, 36.6 and 38.8 at 2048, 189 and 218 at 16384, the backward
+// 62.3 and 61.8, 78.8 and 80.5, 111 and 117, 532 and 553.
+constexpr int64_t kModulePackTiles = 1024;
+constexpr bool module_packs_shape(int A, int cbits) { return A == 11 && cbits == 7; }
+inline bool module_packs_for_tiles(int dtype, int cbits, int K, int64_t B)
+{
+    const Split sp = module_split(K);
+    return dtype == DTYPE_BF16 && module_packs_shape(sp.A, cbits) &&
+           (B << sp.HB) >= kModulePackTiles;
+}
+
 // A validated call of the block.  Workspace: the THREE_PASS workspace `ws`
 // (B * 2^K floats, else none), then for UNFUSED `z` (B * N * C floats), then
 // `wpack` (the two repacked weight matrices, where module_packs_weights).

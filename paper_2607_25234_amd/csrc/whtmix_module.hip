@@ -1328,8 +1328,9 @@ module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
 }
 
 // THREE_PASS first pass: prologue (x W_in, or x W_in^T with trans), forward over
-// the A low bits, workspace.
-template <int A, int HB, int R, typename T, int CB>
+// the A low bits, workspace.  PACKED: w_in is a matrix repacked once per call
+// (module_packs_for_tiles).
+template <int A, int HB, int R, typename T, int CB, bool PACKED>
 __device__ __forceinline__ void module_outer_fwd_tile(float *lds,
                                                       WeightFlags<T, CB, Lds<A, T, CB>::NT> &flags,
                                                       const T *__restrict__ x,
@@ -1350,9 +1351,14 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds,
     // The weights come from L2, x from memory: issued first, they are in LDS
     // by the time x arrives (with project_in's reads ahead, this kernel on 4 x
     // 65536 x 128 bf16: 48.1 -> 41.9 us).
-    stage_raw<T, CB, true, L::NT>(lds, flags, w_in, trans, tau, 0, [&] {
+    if constexpr (PACKED) {
         load_x_frags<T, CB>(f, tile, valid, tau);
-    });
+        stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
+    } else {
+        stage_raw<T, CB, true, L::NT>(lds, flags, w_in, trans, tau, 0, [&] {
+            load_x_frags<T, CB>(f, tile, valid, tau);
+        });
+    }
     float v[V];
     if constexpr (Proj<T, CB>::X3) {
         project_in_x3<CB, L::NT>(v, f, lds, flags, w_in, trans, tile, valid, tau);
@@ -1365,21 +1371,21 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds,
         v, buffer(ws + (b << (A + HB)) + ((size_t)hi << R), extent_bytes<Run, A, float>()), tau);
 }
 
-template <int A, int HB, int R, typename T, int CB>
+template <int A, int HB, int R, typename T, int CB, bool PACKED>
 __global__ void __launch_bounds__(1 << (A - VB))
 module_outer_fwd_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
                         float *__restrict__ ws, uint32_t nvalid)
 {
     __shared__ __attribute__((aligned(16))) float lds[Lds<A, T, CB>::fwd_bytes() / 4];
     __shared__ WeightFlags<T, CB, Lds<A, T, CB>::NT> flags;
-    module_outer_fwd_tile<A, HB, R, T, CB>(lds, flags, x, w_in, false, ws, nvalid,
+    module_outer_fwd_tile<A, HB, R, T, CB, PACKED>(lds, flags, x, w_in, false, ws, nvalid,
                                            outer_block<R>(blockIdx.x, gridDim.x));
 }
 
 // Two operands in one launch (the block's backward: Z = X W_in and
 // dZ' = dY W_out^T): the first half of the grid takes x wa into wsx, the
 // second dy wb^T into wsd, each half numbered as a grid of its own.
-template <int A, int HB, int R, typename T, int CB>
+template <int A, int HB, int R, typename T, int CB, bool PACKED>
 __global__ void __launch_bounds__(1 << (A - VB))
 module_outer_fwd2_kernel(const T *__restrict__ x, const T *__restrict__ wa,
                          const T *__restrict__ dy, const T *__restrict__ wb,
@@ -1390,13 +1396,13 @@ module_outer_fwd2_kernel(const T *__restrict__ x, const T *__restrict__ wa,
     const uint32_t half = gridDim.x >> 1;
     const bool second = blockIdx.x >= half;
     const uint32_t blk = outer_block<R>(blockIdx.x - (second ? half : 0u), half);
-    module_outer_fwd_tile<A, HB, R, T, CB>(lds, flags, second ? dy : x, second ? wb : wa, second,
+    module_outer_fwd_tile<A, HB, R, T, CB, PACKED>(lds, flags, second ? dy : x, second ? wb : wa, second,
                                            second ? wsd : wsx, nvalid, blk);
 }
 
 // THREE_PASS last pass: inverse over the A low bits, epilogue, y.  TRANS: by
 // w_out^T.  ZOUT: also store the inverse-transformed tile itself (float32) to z.
-template <int A, int HB, int R, typename T, int CB, bool TRANS, bool ZOUT = false>
+template <int A, int HB, int R, typename T, int CB, bool PACKED, bool TRANS, bool ZOUT = false>
 __global__ void __launch_bounds__(1 << (A - VB))
 module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_out,
                         T *__restrict__ y, float *__restrict__ z, uint32_t nvalid)
@@ -1414,7 +1420,10 @@ module_outer_inv_kernel(const float *__restrict__ ws, const T *__restrict__ w_ou
     if (valid == 0)
         return;   // wholly padding: nothing to store (uniform per workgroup)
     [[maybe_unused]] RawWeights<T, CB, TRANS ? PACK_EPILOGUE_T : PACK_EPILOGUE, L::NT> wreg;
-    if constexpr (L::SEPARATE)
+    static_assert(!PACKED || L::SEPARATE, "packed weights go to LDS at once");
+    if constexpr (PACKED)
+        stage_weights<L::CHUNKS, L::NT>(wregion, w_out, tau);
+    else if constexpr (L::SEPARATE)
         stage_raw<T, CB, false, L::NT>(wregion, flags, w_out, TRANS, tau);
     else if constexpr (!L::PARTS)
         wreg.load(w_out, tau);
@@ -2021,6 +2030,12 @@ inline hipError_t record(hipEvent_t ev, hipStream_t st)
     return ev ? hipEventRecord(ev, st) : hipSuccess;
 }
 
+inline hipError_t launch_pack_x32(const PackX32Jobs &jobs, int cb, hipStream_t st)
+{
+    hipLaunchKernelGGL(pack_x32_kernel, dim3((1u << (2 * cb)) / 256u), dim3(256), 0, st, jobs, cb);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_pack(const ModuleArgs &m, bool out_as_in)
 {
@@ -2070,20 +2085,36 @@ hipError_t launch_module_three_pass(const ModuleArgs &m, Gain gain)
     constexpr Split sp = module_split(K);
     constexpr int A = sp.A, HB = sp.HB, R = sp.R;
     const hipStream_t st = m.stream;
-    hipError_t e = record(m.events[0], st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((module_outer_fwd_kernel<A, HB, R, T, CB>), dim3((uint32_t)(m.B << HB)),
-                       dim3(1u << (A - VB)), 0, st, static_cast<const T *>(m.x),
-                       static_cast<const T *>(m.w_in), m.ws, m.nvalid);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = record(m.events[1], st)) != hipSuccess) return e;
-    if ((e = launch_middle(middle_args(m, false))) != hipSuccess) return e;
-    if ((e = record(m.events[2], st)) != hipSuccess) return e;
-    hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, false>),
-                       dim3((uint32_t)(m.B << HB)), dim3(1u << (A - VB)), 0, st, m.ws,
-                       static_cast<const T *>(m.w_out), static_cast<T *>(m.y), nullptr, m.nvalid);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return record(m.events[3], st);
+    const auto run = [&](auto packed, const T *w_in, const T *w_out) {
+        constexpr bool PACKED = decltype(packed)::value;
+        hipError_t e = record(m.events[0], st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((module_outer_fwd_kernel<A, HB, R, T, CB, PACKED>),
+                           dim3((uint32_t)(m.B << HB)), dim3(1u << (A - VB)), 0, st,
+                           static_cast<const T *>(m.x), w_in, m.ws, m.nvalid);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = record(m.events[1], st)) != hipSuccess) return e;
+        if ((e = launch_middle(middle_args(m, false))) != hipSuccess) return e;
+        if ((e = record(m.events[2], st)) != hipSuccess) return e;
+        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, PACKED, false>),
+                           dim3((uint32_t)(m.B << HB)), dim3(1u << (A - VB)), 0, st, m.ws, w_out,
+                           static_cast<T *>(m.y), nullptr, m.nvalid);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return record(m.events[3], st);
+    };
+    const T *w_in = static_cast<const T *>(m.w_in), *w_out = static_cast<const T *>(m.w_out);
+    if constexpr (Proj<T, CB>::BF && module_packs_shape(A, CB)) {
+        if (module_packs_for_tiles(m.dtype, CB, m.K, m.B)) {
+            T *pk = static_cast<T *>(m.wpack);
+            constexpr uint32_t CC = 1u << (2 * CB);
+            const hipError_t e =
+                launch_pack_x32({{w_in, w_out, nullptr},
+                                 {pk, pk + CC, nullptr},
+                                 {PACK_PROLOGUE, PACK_EPILOGUE, 0}}, CB, st);
+            return e != hipSuccess ? e : run(std::true_type{}, pk, pk + CC);
+        }
+    }
+    return run(std::false_type{}, w_in, w_out);
 }
 
 // C = 256 (bf16): the three passes on 2^16 outer tiles.
@@ -2100,9 +2131,7 @@ hipError_t launch_module_pair(const ModuleArgs &m)
                             static_cast<const __bf16 *>(m.w_out), nullptr},
                            {pin, pin + kPairC * kPairC, nullptr},
                            {PACK_PROLOGUE, PACK_EPILOGUE, 0}};
-    hipLaunchKernelGGL(pack_x32_kernel, dim3(kPairC * kPairC / 256u), dim3(256), 0, st, jobs,
-                       kPairCB);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_pack_x32(jobs, kPairCB, st);
     if (e != hipSuccess) return e;
     if ((e = record(m.events[0], st)) != hipSuccess) return e;
     hipLaunchKernelGGL((module_outer_fwd_pair_kernel<HB, R>), grid, block, 0, st,
@@ -2708,17 +2737,37 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
     const T *dy = static_cast<const T *>(m.dy);
     const T *w_in = static_cast<const T *>(m.w_in);
     const T *w_out = static_cast<const T *>(m.w_out);
+    // the repacked matrices (W_in; W_out^T; W_in^T) where module_packs_for_tiles
+    constexpr bool CAN_PACK = Proj<T, CB>::BF && module_packs_shape(A, CB);
+    const bool packed = CAN_PACK && module_packs_for_tiles(m.dtype, CB, K, m.B);
+    [[maybe_unused]] T *pk = static_cast<T *>(m.wpack);
+    [[maybe_unused]] constexpr uint32_t CC = 1u << (2 * CB);
     hipError_t e;
+    if constexpr (CAN_PACK) {
+        if (packed && (e = launch_pack_x32({{w_in, w_out, w_in},
+                                            {pk, pk + CC, pk + 2 * CC},
+                                            {PACK_PROLOGUE, PACK_PROLOGUE_T, PACK_EPILOGUE_T}},
+                                           CB, st)) != hipSuccess)
+            return e;
+    }
     if ((e = record(m.events[0], st)) != hipSuccess) return e;
     const bool separable = m.gain_kind == GAIN_LOG_SEPARABLE;
     const BackwardLayout lay =
         backward_layout(PLAN_THREE_PASS, K, m.B, int64_t(1) << CB, separable);
     float *wsx = m.bwd_ws + lay.wsx;
     float *wsd = m.bwd_ws + lay.wsd;
-    hipLaunchKernelGGL((module_outer_fwd2_kernel<A, HB, R, T, CB>),
-                       dim3((uint32_t)(2 * (m.B << HB))), dim3(1u << (A - VB)), 0, st, x, w_in,
-                       dy, w_out, wsx, wsd, m.nvalid);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const auto first_pass = [&](auto p, const T *wa, const T *wb) {
+        hipLaunchKernelGGL((module_outer_fwd2_kernel<A, HB, R, T, CB, decltype(p)::value>),
+                           dim3((uint32_t)(2 * (m.B << HB))), dim3(1u << (A - VB)), 0, st, x, wa,
+                           dy, wb, wsx, wsd, m.nvalid);
+        return hipGetLastError();
+    };
+    if constexpr (CAN_PACK)
+        e = packed ? first_pass(std::true_type{}, pk, pk + CC)
+                   : first_pass(std::false_type{}, w_in, w_out);
+    else
+        e = first_pass(std::false_type{}, w_in, w_out);
+    if (e != hipSuccess) return e;
     BackwardArgs g{};
     g.gain_kind = m.gain_kind;
     g.gain = m.gain;
@@ -2757,8 +2806,8 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
         if ((e = launch_wgrad_tiles(w)) != hipSuccess) return e;
         if ((e = record(m.events[2], st)) != hipSuccess) return e;
         // dX = dZ W_in^T last: dX may be dY itself
-        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true>), grid, block, 0, st,
-                           wsd, w_in, dx, nullptr, m.nvalid);
+        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, false, true>), grid, block,
+                           0, st, wsd, w_in, dx, nullptr, m.nvalid);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         if ((e = launch_outer_inv<K, float>(wsx, m.zp, m.B, m.nvalid, st)) != hipSuccess) return e;
@@ -2766,9 +2815,18 @@ hipError_t module_backward_fused_k(const ModuleBackwardArgs &m)
             return e;
         if ((e = record(m.events[2], st)) != hipSuccess) return e;
         // dZ (float32, for dW_in) and dX = dZ W_in^T from one pass over wsd
-        hipLaunchKernelGGL((module_outer_inv_kernel<A, HB, R, T, CB, true, true>), grid, block, 0,
-                           st, wsd, w_in, dx, m.dzp, m.nvalid);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const auto last_pass = [&](auto p, const T *w) {
+            hipLaunchKernelGGL(
+                (module_outer_inv_kernel<A, HB, R, T, CB, decltype(p)::value, true, true>), grid,
+                block, 0, st, wsd, w, dx, m.dzp, m.nvalid);
+            return hipGetLastError();
+        };
+        if constexpr (CAN_PACK)
+            e = packed ? last_pass(std::true_type{}, pk + 2 * CC)
+                       : last_pass(std::false_type{}, w_in);
+        else
+            e = last_pass(std::false_type{}, w_in);
+        if (e != hipSuccess) return e;
         if ((e = wgrad<T, float>(x, m.dzp, m.wpart, m.dw_in, rows, CB, st)) != hipSuccess)
             return e;
     }

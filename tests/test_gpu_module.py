@@ -216,6 +216,29 @@ def test_module_c256_large_identity_weights(shape, dev):
     assert err <= 2.0 ** -7 and rms < 1e-3, (err, rms)
 
 
+@pytest.mark.parametrize("shape", [(32, 512, 128), (16, 1000, 128)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_module_weights_packed_for_many_tiles(shape, dev):
+    """1024 2^11 outer tiles of bf16, C = 128: the passes read matrices repacked once
+    per call instead of the weights as they lie.  The products are the same, so
+    y and dX equal those of the slices one by one (32 and 64 tiles, not packed)
+    bit for bit."""
+    import torch
+
+    B, N, C = shape
+    x, g, wi, wo = inputs(B, N, C, "bf16", seed=90 + N)
+    dy = to_device(inputs(B, N, C, "bf16", seed=91 + N)[0], "bf16", dev)
+    xd, wid, wod = (to_device(t, "bf16", dev) for t in (x, wi, wo))
+    gd = to_device(g, "f32", dev)
+    say(f"module packed {shape} bf16")
+    y = whtmix.module_forward(xd, wid, gd, wod)
+    dx = whtmix.module_backward(xd, wid, gd, wod, dy)[0]
+    for b in range(0, B, 5):
+        one = slice(b, b + 1)
+        assert torch.equal(y[one], whtmix.module_forward(xd[one], wid, gd, wod))
+        assert torch.equal(dx[one], whtmix.module_backward(xd[one], wid, gd, wod, dy[one])[0])
+
+
 def test_module_deterministic(dev):
     B, N, C = 4, 16384, 128
     x, g, wi, wo = inputs(B, N, C, "bf16", seed=31)
