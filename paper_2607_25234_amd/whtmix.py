@@ -147,15 +147,6 @@ def _options(plan: str | int = "auto", events=None, spin_limit: int = 0) -> Opti
     return o
 
 
-def _opt_arg(plan: str | int = "auto", events=None, spin_limit: int = 0):
-    """The options argument of a ctypes call: NULL when every option is its
-    default (the library then takes AUTO, no events, the default spin
-    limit)."""
-    if events is None and not spin_limit and (plan == "auto" or plan == 0):
-        return None
-    return ctypes.byref(_options(plan, events, spin_limit))
-
-
 def stream_status(stream: int | None = None) -> int:
     """whtmix_stream_status: synchronise the stream and return (and clear)
     the error word of its single-launch calls (SUCCESS or
@@ -215,14 +206,18 @@ def _call_entry(name, *args, plan="auto", events=None) -> int:
     if addr is None:
         addr = _entry[name] = ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
     o, opt = _opt_address(plan, events, 0)
-    st = _call().call(addr, *args, opt)
+    try:
+        st = _call().call(addr, *args, opt)
+    except TypeError:   # a pointer given as a ctypes object: converted as ctypes does
+        st = getattr(lib(), name)(*args, None if o is None else ctypes.byref(o))
     del o
     return st
 
 
 def _opt_address(plan, events, spin_limit):
-    """(structure, address) of the options argument; (None, 0) for NULL.  The
-    caller keeps the structure alive across the call."""
+    """(structure, address) of the options argument; (None, 0) for NULL, when
+    every option is its default (the library then takes AUTO, no events, the
+    default spin limit).  The caller keeps the structure alive across the call."""
     if events is None and not spin_limit and (plan == "auto" or plan == 0):
         return None, 0
     o = _options(plan, events, spin_limit)
@@ -296,18 +291,37 @@ def _gain(t, shape, x, what):
         raise ValueError(f"{what} shape {tuple(t.shape)} != {tuple(shape)}")
 
 
+_current = None
+
+
+def _torch_current():
+    """torch's functions that read the current device's index and the handle of a
+    device's current stream: those that build no object (private to torch), or
+    the public ones in a torch that has not got them."""
+    global _current
+    if _current is None:
+        import torch
+
+        device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+        stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
+                  or (lambda i: torch.cuda.current_stream(i).cuda_stream))
+        _current = device, stream
+    return _current
+
+
 def _on_device(x, stream, raw, ptrs, sizes, *options) -> int:
     """raw(*ptrs, *sizes, stream, *options) with x's device current, on `stream`
     or the device's current stream.  The device is switched only when it is
     not current already, and the stream's handle is read without building a
     Stream object: entering torch.cuda.device and torch.cuda.current_stream
     took 1.4 and 2.0 us of a 16 us call."""
+    i = x.get_device()
+    device, current_stream = _current or _torch_current()
+    st = current_stream(i) if stream is None else stream.cuda_stream
+    if device() == i:
+        return raw(*ptrs, *sizes, st, *options)
     import torch
 
-    i = x.get_device()
-    st = torch._C._cuda_getCurrentRawStream(i) if stream is None else stream.cuda_stream
-    if torch._C._cuda_getDevice() == i:
-        return raw(*ptrs, *sizes, st, *options)
     with torch.cuda.device(i):
         return raw(*ptrs, *sizes, st, *options)
 

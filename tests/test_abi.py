@@ -242,11 +242,15 @@ def test_empty_batch_is_a_no_op():
 def test_default_options_pass_null():
     """With every option at its default the binding passes NULL options
     (documented as the defaults); any other option builds the structure."""
-    assert whtmix._opt_arg() is None
-    assert whtmix._opt_arg("auto", None, 0) is None and whtmix._opt_arg(0) is None
-    assert whtmix._opt_arg("three_pass") is not None
-    assert whtmix._opt_arg("auto", spin_limit=5) is not None
-    assert whtmix._opt_arg("auto", events=[None] * 4) is not None
+    def passed(*a):
+        o, address = whtmix._opt_address(*a)
+        assert (address == 0) == (o is None)
+        assert o is None or address == ctypes.addressof(o)
+        return address
+
+    assert passed("auto", None, 0) == 0 and passed(0, None, 0) == 0
+    assert passed("three_pass", None, 0) and passed("auto", None, 5)
+    assert passed("auto", [None] * 4, 0)
     # the NULL path is checked like the structure path, before any HIP call
     assert whtmix.forward_raw(0, 0, 0, 1, 64, 64, 0, 0) == 1
     assert whtmix.forward_raw(0, 0, 0, 1, 64, 64, 0, 0, "fused") == 1
@@ -303,6 +307,32 @@ def test_call_by_address_marshals_only():
         m.call(0, *([0] * 5), 1, 64, 64, 0, 0, 0)
     with pytest.raises(TypeError):
         m.call(1)
+
+
+def test_call_entry_takes_ctypes_pointers():
+    """Pointers given as ctypes objects, which the call module does not convert, go
+    through ctypes; what neither takes raises ctypes' own error."""
+    far = [ALIGNED + (i << 32) for i in range(5)]
+    for wrap in (ctypes.c_void_p, lambda v: v):
+        ptrs = [wrap(v) for v in far]
+        assert whtmix.module_forward_raw(*ptrs, 1, 64, 12, 0, 0) == 2
+        assert whtmix.backward_raw(*ptrs, 1, 64, 12, 0, wrap(0), plan="three_pass") == 2
+    with pytest.raises(ctypes.ArgumentError):
+        whtmix.backward_raw(*([1.5] * 5), 1, 64, 64, 0, 0)
+
+
+def test_current_stream_without_private_names(monkeypatch):
+    """A torch without the private accessors of device and stream is read through
+    its public ones."""
+    import torch
+
+    monkeypatch.setattr(whtmix, "_current", None)
+    monkeypatch.delattr(torch._C, "_cuda_getDevice", raising=False)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    stream = type("Stream", (), {"cuda_stream": 7})()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda i: stream if i == 3 else None)
+    device, current_stream = whtmix._torch_current()
+    assert device is torch.cuda.current_device and current_stream(3) == 7
 
 
 def test_plan_table():
