@@ -118,6 +118,18 @@ OPS = ("forward", "separable", "backward", "backward_separable", "module", "modu
        "module_backward")
 
 
+def module_backward_phases(plan: dict, C: int) -> list[str]:
+    """Phases between the events of a whtmix_module_backward call.  With the
+    projections inside the mixer's passes (fused) both weight gradients are formed in
+    the second phase, but where they are formed apart: C = 256, C = 128 on 2^11
+    outer tiles and C = 16 on 2^15."""
+    if not plan["module_backward_fused"]:
+        return ["recompute_and_dw_out", "mixer_gradients", "dx_and_dw_in"]
+    apart = C > 128 or (C, plan["module_outer_bits"]) in ((128, 11), (16, 15))
+    return (["transforms_and_gain_gradient", "z_prime_and_dw_out", "dx_and_dw_in"] if apart
+            else ["transforms_and_gain_gradient", "dw_out_and_dw_in", "dx"])
+
+
 def module_kernels(plan: str, path: str) -> list[str]:
     """Kernels between the events of a whtmix_module_forward call (where a weight
     repacking kernel runs, C = 256, it is before the first event); path: the library's
@@ -437,9 +449,7 @@ def main() -> int:
         nk, names = 2, (["fwd_transforms_gain_gradient", "dx_outer_inv"]
                         if backward_plan(plan) == "three_pass" else ["gain_gradient", "dx"])
     elif op == "module_backward":
-        nk, names = 3, (["transforms_and_gain_gradient", "z_prime_and_dw_out", "dx_and_dw_in"]
-                        if plan["module_backward_fused"] else
-                        ["recompute_and_dw_out", "mixer_gradients", "dx_and_dw_in"])
+        nk, names = 3, module_backward_phases(plan, w.C)
     elif op.startswith("module"):
         # the block runs 2^16-element slices with the three-pass plan even
         # where the mixer's forward takes another plan

@@ -61,7 +61,7 @@ def _run(cmd: list[str], verbose: bool, what: str) -> None:
 
 
 def build_pycall(out: str = PYCALL, verbose: bool = False) -> str:
-    """The CPython call module of the forward entry points (no HIP code)."""
+    """The binding's CPython call module (no HIP code)."""
     cc = os.environ.get("CC", "gcc")
     src = os.path.join(CSRC, "whtmix_pycall.c")
     _run([cc, "-O2", "-shared", "-fPIC", "-Wall", "-Wextra", "-Werror",
