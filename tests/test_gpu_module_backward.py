@@ -164,20 +164,9 @@ def test_module_backward_forced_three_pass_and_alias(dev, orc):
                                       alias=True), ref, "bf16")
 
 
-@pytest.mark.parametrize("shape,dtype", [((1, 140000, 256), "bf16"), ((2, 262144, 256), "bf16"),
-                                         ((4, 65536, 128), "bf16"), ((2, 16384, 128), "f32"),
-                                         ((32, 4096, 64), "f32"), ((1, 65536, 16), "bf16")],
-                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else s)
-def test_module_backward_by_composition(shape, dtype, dev):
-    """Shapes whose oracle takes minutes (2^26-element slices), through the
-    projections-inside-the-passes backward, against the chain rule composed
-    from the validated mixer (forward, and backward for dgain) and float32
-    matrix products on the same device:
-        Z = X W_in, Z' = mixer(Z), dZ' = dY W_out^T, dZ = mixer(dZ') (the
-        mixer is self-adjoint), dX = dZ W_in^T, dW_in = X^T dZ, dW_out = Z'^T dY.
-    Both sides are float32 up to rounding order (the weight gradients' three-
-    term split leaves 2^-27), so the float32 bar holds for the float32
-    outputs; dX in bf16 is rounded once."""
+def composed_gradients(shape, dtype, dev):
+    """The block's backward and, on the same device, the chain rule composed from
+    the mixer and float32 matrix products: ((dx, dw_in, dw_out, dgain), the same)."""
     import torch
 
     B, N, C = shape
@@ -191,7 +180,6 @@ def test_module_backward_by_composition(shape, dtype, dev):
     wi = (torch.randn(C, C, generator=gen) / C ** 0.5).to(dev).to(tdt)
     wo = (torch.randn(C, C, generator=gen) / C ** 0.5).to(dev).to(tdt)
     g = (torch.rand(P, C, generator=gen) + 0.5).to(dev)
-    say(f"module backward by composition {shape} {dtype}")
     torch.backends.cuda.matmul.allow_tf32 = False   # float32 products in float32
     dx, dwi, dwo, dg = whtmix.module_backward(x, wi, g, wo, dy)
     xf, dyf, wif, wof = x.float(), dy.float(), wi.float(), wo.float()
@@ -204,9 +192,46 @@ def test_module_backward_by_composition(shape, dtype, dev):
     dwi_ref = torch.matmul(xf.reshape(-1, C).t().contiguous(), dz.reshape(-1, C))
     dwo_ref = torch.matmul(zp.reshape(-1, C).t().contiguous(), dyf.reshape(-1, C))
     torch.cuda.synchronize(dev)
-    check("dx", to_host(dx), to_host(dx_ref), TOL[dtype])
-    for name, a, r in [("dw_in", dwi, dwi_ref), ("dw_out", dwo, dwo_ref), ("dgain", dg, dg_ref)]:
-        check(name, to_host(a), to_host(r), GRAD_TOL)
+    return (dx, dwi, dwo, dg), (dx_ref, dwi_ref, dwo_ref, dg_ref)
+
+
+@pytest.mark.parametrize("shape,dtype", [((1, 140000, 256), "bf16"), ((2, 262144, 256), "bf16"),
+                                         ((4, 65536, 128), "bf16"), ((2, 16384, 128), "f32"),
+                                         ((32, 4096, 64), "f32"), ((1, 65536, 16), "bf16")],
+                         ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else s)
+def test_module_backward_by_composition(shape, dtype, dev):
+    """Shapes whose oracle takes minutes (2^26-element slices), through the
+    projections-inside-the-passes backward, against the chain rule composed
+    from the validated mixer (forward, and backward for dgain) and float32
+    matrix products on the same device:
+        Z = X W_in, Z' = mixer(Z), dZ' = dY W_out^T, dZ = mixer(dZ') (the
+        mixer is self-adjoint), dX = dZ W_in^T, dW_in = X^T dZ, dW_out = Z'^T dY.
+    Both sides are float32 up to rounding order (of the weight gradients' three-
+    term splits, the products left out come to 2^-24 of each at most), so the
+    float32 bar holds for the float32 outputs; dX in bf16 is rounded once."""
+    say(f"module backward by composition {shape} {dtype}")
+    got, ref = composed_gradients(shape, dtype, dev)
+    for name, a, r in zip(["dx", "dw_in", "dw_out", "dgain"], got, ref):
+        check(name, to_host(a), to_host(r), TOL[dtype] if name == "dx" else GRAD_TOL)
+
+
+# Every tile shape of the weight gradients formed in the last pass: outer tiles of
+# 2^11 .. 2^15 (K = 16, 18, .. 24) by C, but C = 128 on 2^11 and C = 16 on 2^15
+EVERY_TILE = [(K, C) for K in (16, 18, 20, 22, 24) for C in (16, 32, 64, 128)
+              if (K, C) not in ((16, 128), (24, 16))]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K,C", EVERY_TILE)
+def test_weight_gradients_every_tile_shape(K, C, dtype, dev):
+    """An odd number of real outer tiles (groups of two and more end on tile 0 again,
+    none of its rows counted), the last of them one token; one slice or three."""
+    P = (1 << K) // C
+    shape = (3 if K <= 18 else 1, 5 * P // 8 + 1, C)
+    say(f"weight gradients {shape} {dtype} (K = {K})")
+    got, ref = composed_gradients(shape, dtype, dev)
+    for name, a, r in zip(["dx", "dw_in", "dw_out", "dgain"], got, ref):
+        check(name, to_host(a), to_host(r), TOL[dtype] if name == "dx" else GRAD_TOL)
 
 
 @pytest.mark.parametrize("case", ["inf_w_in", "huge_dy", "tiny_dy"])

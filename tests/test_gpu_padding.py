@@ -105,3 +105,63 @@ def test_padded_pair_tiles_left_out(dev):
     full = whtmix.forward(x, g)
     torch.cuda.synchronize(dev)
     assert torch.equal(y, full[:, :N])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 9216, 64), (2, 25600, 32), (3, 700, 128), (8, 4700, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_padded_rows_left_out_separable(shape, dtype, dev, orc):
+    """The same with the paper's log gains: the middle passes that form the log-gain
+    gradients' sums themselves, and those of 2^11 tiles that leave dG to a kernel."""
+    import torch
+
+    B, N, C = shape
+    P = whtmix.padded_tokens(N)
+    x, _ = workloads.draw(B, N, C, dtype, seed=710 + N)
+    dy, _ = workloads.draw(B, N, C, dtype, seed=711 + N)
+    gt, gc = workloads.draw_log_gains(P, C, seed=712 + N)
+    wi, wo = workloads.draw_weights(C, dtype, seed=713 + N)
+    say(f"padding separable {shape} {dtype}")
+    xd, dyd = to_device(x, dtype, dev), to_device(dy, dtype, dev)
+    gtd, gcd = to_device(gt, "f32", dev), to_device(gc, "f32", dev)
+    wid, wod = to_device(wi, dtype, dev), to_device(wo, dtype, dev)
+    poison(B, N, C, dtype, dev, False)
+    y = whtmix.forward_separable(xd, gtd, gcd, plan="three_pass")
+    poison(B, N, C, dtype, dev, False)
+    got = whtmix.backward_separable(xd, dyd, gtd, gcd)
+    poison(B, N, C, dtype, dev, True)
+    yb = whtmix.module_forward_separable(xd, wid, gtd, gcd, wod)
+    poison(B, N, C, dtype, dev, True)
+    gotb = whtmix.module_backward_separable(xd, wid, gtd, gcd, wod, dyd)
+    torch.cuda.synchronize(dev)
+    block = {"f32": 1e-5, "bf16": 4e-3}[dtype]
+    checks = [("y", y, orc.whtmix_separable(x, gt, gc), DERIVED[dtype]),
+              ("block y", yb, orc.whtmix_module_separable(x, wi, gt, gc, wo), block)]
+    checks += zip(["dx", "dgt", "dgc"], got, orc.whtmix_grad_separable(x, dy, gt, gc),
+                  [DERIVED[dtype], 1e-5, 1e-5])
+    checks += zip(["block dx", "dw_in", "dw_out", "block dgt", "block dgc"], gotb,
+                  orc.whtmix_module_grad_separable(x, wi, gt, gc, wo, dy), [block] + [1e-5] * 4)
+    for name, t, ref, tol in checks:
+        err = errors(to_host(t), ref)[0]
+        assert err <= tol, (name, err)     # NaN fails too
+
+
+@pytest.mark.parametrize("shape", [(1, 600, 256), (2, 1300, 256)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_padded_block_pair_tiles_left_out(shape, dev, orc):
+    """The bf16 block with C = 256 on 2^16 outer tiles, the last of them wholly padded."""
+    import torch
+
+    B, N, C = shape
+    P = whtmix.padded_tokens(N)
+    x, _ = workloads.draw(B, N, C, "bf16", seed=720 + N)
+    _, g = workloads.draw(1, P, C, "f32", seed=721 + N)
+    wi, wo = workloads.draw_weights(C, "bf16", seed=722 + N)
+    assert whtmix.plan_describe(B, N, C, "bf16")["module_outer_bits"] == 16
+    say(f"padding pair-tile block {shape} bf16")
+    xd, wid, wod = (to_device(t, "bf16", dev) for t in (x, wi, wo))
+    gd = to_device(g, "f32", dev)
+    poison(B, N, C, "bf16", dev, True)
+    y = whtmix.module_forward(xd, wid, gd, wod)
+    torch.cuda.synchronize(dev)
+    assert errors(to_host(y), orc.whtmix_module(x, wi, g, wo))[0] <= 4e-3
