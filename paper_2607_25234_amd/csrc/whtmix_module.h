@@ -170,36 +170,50 @@ constexpr bool wgrad_direct_shape(int A, int cbits)
     return wgrad_tiles_shape(A, cbits) && A - 6 - (sb < tw ? sb : tw) <= 6;
 }
 
-// log2 of the outer tiles a workgroup takes at a time (Wd::E, Wg::E).
-constexpr int wgrad_group_bits(int A, int cbits)
+// log2 of the waves of a workgroup: eight, or as many as a tile has; the direct form
+// with 64 values per lane and less than eight strips of waves: four.
+constexpr int wgrad_wave_bits(int A, int cbits)
 {
     const int tw = A - 11, sb = cbits - 4, sw = sb < tw ? sb : tw;
     if (wgrad_direct_shape(A, cbits))
-        return (A - 6 - sw > 5 && sw < 3 ? 2 : 3) - sw;
-    return (tw > 3 ? tw : 3) - tw;
+        return A - 6 - sw > 5 && sw < 3 ? 2 : 3;
+    return tw > 3 ? tw : 3;
+}
+
+// Waves per SIMD that the registers are held to: four with one strip of channels per
+// wave (two with float32 at C = 128, whose operands take more), two with several;
+// with 64 values per lane three, or two with eight strips of waves.  (float32, C = 64
+// on 2^14 tiles spills 15 registers at three: 28.4 us on 2 slices of 36864 x 64, against
+// 32.2 at two without spills and 32.2 and 45 with a half and a quarter of the k steps
+// per group.)
+constexpr int wgrad_waves(int A, int cbits, int dtype)
+{
+    const int tw = A - 11, sb = cbits - 4, sw = sb < tw ? sb : tw;
+    if (!wgrad_direct_shape(A, cbits))
+        return sb > tw ? 2 : 4;
+    if (A - 6 - sw > 5)
+        return wgrad_wave_bits(A, cbits) == 2 ? 3 : 2;
+    return sb > tw || (dtype == DTYPE_F32 && cbits == 7) ? 2 : 4;
+}
+
+// log2 of the outer tiles a workgroup takes at a time.
+constexpr int wgrad_group_bits(int A, int cbits)
+{
+    const int tw = A - 11, sb = cbits - 4, sw = sb < tw ? sb : tw;
+    return wgrad_wave_bits(A, cbits) - (wgrad_direct_shape(A, cbits) ? sw : tw);
 }
 
 // Workgroups (and partial sums) per weight gradient: as many as fit the CUs
-// over both (two 8-wave ones; three 4-wave ones with 64 values per lane; one
-// with 1024 threads or over 128 registers: several strips of channels per
-// wave, float32 at C = 128), and no more than there are tile groups.  Each adds up its tile
+// over both, and no more than there are tile groups.  Each adds up its tile
 // groups in registers, so its partial C x C matrix is written once.
 inline uint32_t wgrad_tiles_parts(int K, int cbits, int dtype, int64_t B, uint32_t nvalid)
 {
     const Split sp = module_split(K);
     const int e = wgrad_group_bits(sp.A, cbits);
-    const int tw = sp.A - 11, sb = cbits - 4, sw = sb < tw ? sb : tw;
     const uint64_t groups =
         ((uint64_t)B * wgrad_live_tiles(K, nvalid) + (uint64_t(1) << e) - 1) >> e;
-    uint64_t most = sb > tw ? 128 : 256;
-    if (wgrad_direct_shape(sp.A, cbits)) {
-        if (sp.A - 6 - sw > 5)
-            most = sw < 3 ? 384 : 128;
-        else if (dtype == DTYPE_F32 && cbits == 7)
-            most = 128;
-    } else if (sp.A == 15) {
-        most = 128;
-    }
+    const uint64_t most =
+        128u * (4u * (uint32_t)wgrad_waves(sp.A, cbits, dtype) >> wgrad_wave_bits(sp.A, cbits));
     return (uint32_t)(groups < most ? groups : most);
 }
 

@@ -229,13 +229,12 @@ __host__ __device__ constexpr uint32_t oc_bf16(uint32_t C, uint32_t nb, uint32_t
 
 // One thread per packed element.  Packed index = ((nb * KS + kk) * 64 + lane)
 // * 4 + r with lane = 16 q + j (bf16), or ((nb * C/16 + p) * 64 + lane) * 4 + e
-// with step s = 4p + e (fp32).  W_in feeds the B operand of Z = X W_in
-// (column 16 nb + j); W_out feeds the A operand of Y^T = W_out^T Z'^T, or
-// (out_as_in) the B operand of Y = Z' W_out like W_in.
+// with step s = 4p + e (fp32).  Both feed the B operand of the projection kernels
+// (column 16 nb + j).
 template <typename T>
 __global__ void __launch_bounds__(256)
 pack_weights_kernel(const T *__restrict__ w_in, const T *__restrict__ w_out, T *__restrict__ p_in,
-                    T *__restrict__ p_out, int cb, int out_as_in)
+                    T *__restrict__ p_out, int cb)
 {
     const uint32_t C = 1u << cb;
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
@@ -249,15 +248,14 @@ pack_weights_kernel(const T *__restrict__ w_in, const T *__restrict__ w_out, T *
         const uint32_t kk = rest % ks, nb = rest / ks;
         const uint32_t src = k_in_bf16(C, kk, q, e) * C + 16u * nb + j;
         p_in[idx] = w_in[src];
-        p_out[idx] = out_as_in ? w_out[src]
-                               : w_out[(q * (C / 4u) + 4u * kk + e) * C + oc_bf16(C, nb, j)];
+        p_out[idx] = w_out[src];
     } else {
         const uint32_t np = C / 16u;
         const uint32_t p = rest % np, nb = rest / np;
         const uint32_t s = 4u * p + e;
         const uint32_t src = k_in_f32(s, q) * C + 16u * nb + j;
         p_in[idx] = w_in[src];
-        p_out[idx] = out_as_in ? w_out[src] : w_out[(q * (C / 4u) + s) * C + 16u * nb + j];
+        p_out[idx] = w_out[src];
     }
 }
 
@@ -306,44 +304,15 @@ pack_x32_kernel(PackX32Jobs jobs, int cb)
             jobs.p[i][idx] = jobs.w[i][pack_x32_source(idx, C, jobs.mode[i])];
 }
 
-// The orders of pack_weights_kernel (the 16x16x16 bf16 products at C = 16 and
-// the 16x16x4 float32 ones) in the four modes of pack_x32_kernel.
-template <typename T>
-__device__ __forceinline__ uint32_t pack_std_source(uint32_t idx, uint32_t C, int mode)
+// The element of W (or of W^T) at a packed index for C = 16, whose products are the
+// 16x16x16 bf16 and the 16x16x4 float32 ones: index (4 lane + e), one column block;
+// lane group q supplies k = 4 q + e in either order of the operands.
+__device__ __forceinline__ uint32_t pack_c16_source(uint32_t idx, bool trans)
 {
-    const uint32_t e = idx & 3u, lane = (idx >> 2) & 63u;
+    const uint32_t e = idx & 3u, lane = idx >> 2;
     const uint32_t j = lane & 15u, q = lane >> 4;
-    const uint32_t rest = idx >> 8;
-    const bool pro = mode == PACK_PROLOGUE || mode == PACK_PROLOGUE_T;
-    uint32_t k, col;
-    if constexpr (sizeof(T) == 2) {
-        const uint32_t ks = C / 16u, kk = rest % ks, nb = rest / ks;
-        k = pro ? k_in_bf16(C, kk, q, e) : q * (C / 4u) + 4u * kk + e;
-        col = pro ? 16u * nb + j : oc_bf16(C, nb, j);
-    } else {
-        const uint32_t np = C / 16u, p = rest % np, nb = rest / np, s = 4u * p + e;
-        k = pro ? k_in_f32(s, q) : q * (C / 4u) + s;
-        col = 16u * nb + j;
-    }
-    return mode >= PACK_PROLOGUE_T ? col * C + k : k * C + col;
-}
-
-// Three-term bf16 split of two floats, v = hi + mid + lo + d, each term the
-// nearest bf16 of what the previous ones leave: |mid| <= 2^-8 |v|, |lo| <= 2^-17
-// |v|, |d| <= 2^-26 |v|.  For |v| >= 2^-100 each term is a normal bf16 and d = 0.
-__device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, uint32_t &mid,
-                                            uint32_t &lo)
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const auto cvt = [](float a, float b) {
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
-    };
-    const auto f32 = [](uint32_t u) { return __builtin_bit_cast(float, u); };
-    hi = cvt(z0, z1);
-    const float r0 = z0 - f32(hi << 16), r1 = z1 - f32(hi & 0xffff0000u);
-    mid = cvt(r0, r1);
-    lo = cvt(r0 - f32(mid << 16), r1 - f32(mid & 0xffff0000u));
+    const uint32_t k = 4u * q + e;
+    return trans ? j * 16u + k : k * 16u + j;
 }
 
 // Whether three bf16 terms hold the floats seen, each add() a lane's share of one
@@ -571,12 +540,6 @@ __device__ __forceinline__ void project_in(float (&v)[V], const XFrag<T, CB> &f,
 // the stereo64k block, of which the middle pass gives back 2).
 constexpr int kYPolicy = kTemporal;
 
-__device__ __forceinline__ uint32_t pack2_bf16(float a, float b)
-{
-    return (uint32_t)__builtin_bit_cast(unsigned short, (__bf16)a) |
-           ((uint32_t)__builtin_bit_cast(unsigned short, (__bf16)b) << 16);
-}
-
 // Y = Z' W_out for the wave's tokens, Z' in the epilogue layout of a 2^M
 // tile; stores the rows of the tile with element index < valid (a multiple
 // of C), masked explicitly.  wl: packed W_out in LDS.
@@ -608,8 +571,8 @@ __device__ __forceinline__ void project_out(const float (&v)[V], const void *wl,
                     const float z0 = v[(8 * kk + 2 * e) | (rb << RB_SHIFT)];
                     const float z1 = v[(8 * kk + 2 * e + 1) | (rb << RB_SHIFT)];
                     const float h0 = (float)(__bf16)z0, h1 = (float)(__bf16)z1;
-                    h2[e] = pack2_bf16(z0, z1);
-                    l2[e] = pack2_bf16(z0 - h0, z1 - h1);
+                    h2[e] = cvt2_bf16(z0, z1);
+                    l2[e] = cvt2_bf16(z0 - h0, z1 - h1);
                 }
                 hi[kk] = __builtin_bit_cast(bf16x8, h2);
                 lo[kk] = __builtin_bit_cast(bf16x8, l2);
@@ -643,10 +606,10 @@ __device__ __forceinline__ void project_out(const float (&v)[V], const void *wl,
             // blocks 2n, 2n+1: channels 32 n + 8 q + [0, 8)
 #pragma unroll
             for (int n = 0; n < P::NNB / 2; ++n) {
-                const u32x4 d = {pack2_bf16(acc[2 * n][0], acc[2 * n][1]),
-                                 pack2_bf16(acc[2 * n][2], acc[2 * n][3]),
-                                 pack2_bf16(acc[2 * n + 1][0], acc[2 * n + 1][1]),
-                                 pack2_bf16(acc[2 * n + 1][2], acc[2 * n + 1][3])};
+                const u32x4 d = {cvt2_bf16(acc[2 * n][0], acc[2 * n][1]),
+                                 cvt2_bf16(acc[2 * n][2], acc[2 * n][3]),
+                                 cvt2_bf16(acc[2 * n + 1][0], acc[2 * n + 1][1]),
+                                 cvt2_bf16(acc[2 * n + 1][2], acc[2 * n + 1][3])};
                 if (ok)
                     __builtin_amdgcn_raw_buffer_store_b128(d, r, row + 16u * q,
                                                            rb * rb_bytes + 64u * n, kYPolicy);
@@ -686,18 +649,18 @@ __device__ __forceinline__ void project_out(const float (&v)[V], const void *wl,
                 // blocks 2n, 2n+1: channels 32 n + 8 q + [0, 8)
 #pragma unroll
                 for (int n = 0; n < P::NNB / 2; ++n) {
-                    const u32x4 d = {pack2_bf16(acc[2 * n][0], acc[2 * n][1]),
-                                     pack2_bf16(acc[2 * n][2], acc[2 * n][3]),
-                                     pack2_bf16(acc[2 * n + 1][0], acc[2 * n + 1][1]),
-                                     pack2_bf16(acc[2 * n + 1][2], acc[2 * n + 1][3])};
+                    const u32x4 d = {cvt2_bf16(acc[2 * n][0], acc[2 * n][1]),
+                                     cvt2_bf16(acc[2 * n][2], acc[2 * n][3]),
+                                     cvt2_bf16(acc[2 * n + 1][0], acc[2 * n + 1][1]),
+                                     cvt2_bf16(acc[2 * n + 1][2], acc[2 * n + 1][3])};
                     if (ok)
                         __builtin_amdgcn_raw_buffer_store_b128(d, r, row + 16u * q,
                                                                rb * rb_bytes + 64u * n,
                                                                kYPolicy);
                 }
             } else {
-                const u32x2 d = {pack2_bf16(acc[0][0], acc[0][1]),
-                                 pack2_bf16(acc[0][2], acc[0][3])};
+                const u32x2 d = {cvt2_bf16(acc[0][0], acc[0][1]),
+                                 cvt2_bf16(acc[0][2], acc[0][3])};
                 if (ok)
                     __builtin_amdgcn_raw_buffer_store_b64(d, r, row + 8u * q, rb * rb_bytes,
                                                           kYPolicy);
@@ -829,7 +792,7 @@ struct RawWeights {
     static constexpr uint32_t C = 1u << CB, KS2 = P::KS2;
     static constexpr bool TR = MODE >= PACK_PROLOGUE_T;
     static constexpr bool PRO = MODE == PACK_PROLOGUE || MODE == PACK_PROLOGUE_T;
-    static constexpr bool STD = C < 32;                // element order of pack_std_source
+    static constexpr bool STD = C < 32;                // element order of pack_c16_source
     static constexpr uint32_t COLS = C / P::W_ROUNDS;  // columns of a part
     static constexpr uint32_t UNITS =
         STD ? C * C : (!TR && P::BF ? C * C / 16u : COLS * C / 8u);
@@ -865,7 +828,7 @@ struct RawWeights {
             const uint32_t u = tau + i * NT;
             if (UNITS % NT != 0 && u >= UNITS) break;
             if constexpr (STD) {
-                const T e = w[pack_std_source<T>(u, C, MODE)];
+                const T e = w[pack_c16_source(u, TR)];
                 if constexpr (P::BF)
                     raw[i][0] = __builtin_bit_cast(unsigned short, e);
                 else
@@ -948,7 +911,7 @@ struct RawWeights {
 #pragma unroll
                 for (uint32_t e = 0; e < 4u; ++e) {
                     uint32_t x, y, z;
-                    split3_pair(__builtin_bit_cast(float, r[2u * e]),
+                    split3_pair<false>(__builtin_bit_cast(float, r[2u * e]),
                                 __builtin_bit_cast(float, r[2u * e + 1u]), x, y, z);
                     h[e] = x;
                     m[e] = y;
@@ -1037,7 +1000,7 @@ __device__ __forceinline__ void split_x3(bf16x8 (&a0)[KS2], bf16x8 (&a1)[KS2], b
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             uint32_t a, b, c;
-            split3_pair(z[8 * kk + 2 * e], z[8 * kk + 2 * e + 1], a, b, c);
+            split3_pair<false>(z[8 * kk + 2 * e], z[8 * kk + 2 * e + 1], a, b, c);
             h[e] = a;
             m[e] = b;
             l[e] = c;
@@ -1293,6 +1256,8 @@ __device__ __forceinline__ void epilogue(const float (&v)[V], float *lds, const 
 // registers, so that two workgroups share a CU as their LDS allows (left alone
 // they took 130 to 152; 2048 slices of 128 x 128 bf16 95.6 -> 67.1 us, of 256 x 64
 // float32 137 -> 116 us; C = 32 takes 122 and is slower with the bound, 87 -> 91).
+// 2^15 tiles have 128 registers in any case; float32 spills 6 to 31 of them from C = 64
+// (1024 slices of 512 x 64 119 us, 143 on the float32 instruction without spills).
 template <int K, typename T, class Gain, int CB>
 __global__ void __launch_bounds__((1 << (K - VB)), (K == 14 && CB >= 6 ? 4 : 1))
 module_fused_kernel(const T *__restrict__ x, const T *__restrict__ w_in,
@@ -1534,8 +1499,8 @@ __device__ __forceinline__ void split_pair(const float (&v0)[V], const float (&v
             const float z0 = kk < 4 ? v0[8 * kk + 2 * e] : v1[8 * (kk - 4) + 2 * e];
             const float z1 = kk < 4 ? v0[8 * kk + 2 * e + 1] : v1[8 * (kk - 4) + 2 * e + 1];
             const float h0 = (float)(__bf16)z0, h1 = (float)(__bf16)z1;
-            h2[e] = pack2_bf16(z0, z1);
-            l2[e] = pack2_bf16(z0 - h0, z1 - h1);
+            h2[e] = cvt2_bf16(z0, z1);
+            l2[e] = cvt2_bf16(z0 - h0, z1 - h1);
         }
         hi[kk] = __builtin_bit_cast(bf16x8, h2);
         lo[kk] = __builtin_bit_cast(bf16x8, l2);
@@ -1568,8 +1533,8 @@ __device__ __forceinline__ void project_out_pair(const bf16x8 (&hi)[kPairKs],
             acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, hi[kk], acc1, 0, 0, 0);
             acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, lo[kk], acc1, 0, 0, 0);
         }
-        const u32x4 d = {pack2_bf16(acc0[0], acc0[1]), pack2_bf16(acc0[2], acc0[3]),
-                         pack2_bf16(acc1[0], acc1[1]), pack2_bf16(acc1[2], acc1[3])};
+        const u32x4 d = {cvt2_bf16(acc0[0], acc0[1]), cvt2_bf16(acc0[2], acc0[3]),
+                         cvt2_bf16(acc1[0], acc1[1]), cvt2_bf16(acc1[2], acc1[3])};
         if (ok)
             __builtin_amdgcn_raw_buffer_store_b128(d, r, voff, 64u * n, kYPolicy);
     }
@@ -2037,13 +2002,12 @@ inline hipError_t launch_pack_x32(const PackX32Jobs &jobs, int cb, hipStream_t s
 }
 
 template <typename T>
-hipError_t launch_pack(const ModuleArgs &m, bool out_as_in)
+hipError_t launch_pack(const ModuleArgs &m)
 {
     const uint32_t n = 1u << (2 * m.cbits);
     hipLaunchKernelGGL((pack_weights_kernel<T>), dim3((n + 255u) / 256u), dim3(256), 0, m.stream,
                        static_cast<const T *>(m.w_in), static_cast<const T *>(m.w_out),
-                       static_cast<T *>(m.wpack), static_cast<T *>(m.wpack) + n, m.cbits,
-                       out_as_in ? 1 : 0);
+                       static_cast<T *>(m.wpack), static_cast<T *>(m.wpack) + n, m.cbits);
     return hipGetLastError();
 }
 
@@ -2232,7 +2196,7 @@ hipError_t project_pair_mfma(const ModuleArgs &m, LaunchArgs &mix)
     const T *pin = static_cast<const T *>(m.wpack);
     const T *pout = pin + ((size_t)1 << (2 * CB));
     const hipStream_t st = m.stream;
-    hipError_t e = launch_pack<T>(m, true);
+    hipError_t e = launch_pack<T>(m);
     if (e != hipSuccess) return e;
     if ((e = record(m.events[0], st)) != hipSuccess) return e;
     hipLaunchKernelGGL((project_mfma_kernel<T, float, T, CB>), grid, dim3(256), 0, st,
@@ -2416,23 +2380,24 @@ __device__ __forceinline__ void wgrad_stage(float *lds, const u32x4 (&r)[N])
     }
 }
 
-// Eight k-slot values (two groups of four) for the 16x16x32 instruction.
-// Three-term bf16 split of floats: v = hi + mid + lo + d with each term the
-// nearest bf16 of what the previous ones leave (the differences are exact in
-// float32) and |d| <= 2^-27 |v|.
+// Eight k-slot values (two groups of four) for the 16x16x32 instruction, in three
+// terms.
 __device__ __forceinline__ void split3_bf16x8(const f32x4 &z0, const f32x4 &z1, bf16x8 &hi,
                                               bf16x8 &mid, bf16x8 &lo)
 {
+    u32x4 h, m, l;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float z = e < 4 ? z0[e] : z1[e - 4];
-        const __bf16 h = (__bf16)z;
-        const float r1 = z - (float)h;
-        const __bf16 m = (__bf16)r1;
-        hi[e] = h;
-        mid[e] = m;
-        lo[e] = (__bf16)(r1 - (float)m);
+    for (int e = 0; e < 4; ++e) {
+        uint32_t a, b, c;
+        const f32x4 &z = e < 2 ? z0 : z1;
+        split3_pair<false>(z[2 * (e & 1)], z[2 * (e & 1) + 1], a, b, c);
+        h[e] = a;
+        m[e] = b;
+        l[e] = c;
     }
+    hi = __builtin_bit_cast(bf16x8, h);
+    mid = __builtin_bit_cast(bf16x8, m);
+    lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // bf16-origin values as bf16: their high halves, exactly.  (Whole vectors are

@@ -92,6 +92,48 @@ struct Elt<__bf16> {
     }
 };
 
+// ---------------------------------------------------------------- bf16 terms
+// The high halves of two words: two bf16, the first in the low half.
+__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b)   // round to nearest even
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
+}
+__device__ __forceinline__ float as_f32(uint32_t v) { return __builtin_bit_cast(float, v); }
+__device__ __forceinline__ uint32_t as_u32(float v) { return __builtin_bit_cast(uint32_t, v); }
+
+// Three-term bf16 split of two floats, v = hi + mid + lo.
+// EXACT: each term the leading 8 bits of what is left, so 24 bits are split
+// without residue (the terms have v's sign and shrink by 2^-7 only).
+// Otherwise each term is the nearest bf16 of what is left: |mid| <= 2^-8 |v|,
+// |lo| <= 2^-17 |v|, of either sign, which the products dropped from float32
+// times float32 rely on, and what is left at the end at most 2^-26 |v|, nothing from
+// 2^-100 up, where every term is a normal bf16.
+template <bool EXACT>
+__device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, uint32_t &mid,
+                                            uint32_t &lo)
+{
+    if constexpr (EXACT) {
+        const float r0 = z0 - as_f32(as_u32(z0) & 0xffff0000u);
+        const float r1 = z1 - as_f32(as_u32(z1) & 0xffff0000u);
+        hi = high_halves(as_u32(z0), as_u32(z1));
+        const float s0 = r0 - as_f32(as_u32(r0) & 0xffff0000u);
+        const float s1 = r1 - as_f32(as_u32(r1) & 0xffff0000u);
+        mid = high_halves(as_u32(r0), as_u32(r1));
+        lo = high_halves(as_u32(s0), as_u32(s1));
+    } else {
+        hi = cvt2_bf16(z0, z1);
+        const float r0 = z0 - as_f32(hi << 16), r1 = z1 - as_f32(hi & 0xffff0000u);
+        mid = cvt2_bf16(r0, r1);
+        lo = cvt2_bf16(r0 - as_f32(mid << 16), r1 - as_f32(mid & 0xffff0000u));
+    }
+}
+
 // ---------------------------------------------------------------- layouts
 template <int S>
 __device__ __forceinline__ uint32_t layout_base(uint32_t tau)

@@ -19,9 +19,9 @@
 // Measured on 4 slices of 2^23 (C = 128, bf16), both gradients: 91 us, and
 // 7.7 us for the final sums, where storing Z' and dZ took 63 and 30 us, the
 // products from memory 2 x 65 us and their sums 4 x 5.6 us.  The 403 MB it
-// reads take 65 us at the copy rate; the VALU (530 instructions per wave and
-// tile) is busy 33 us and the matrix unit 20 us, in phases that two workgroups
-// per CU overlap in part.
+// reads take 87 us at the rate of a large copy (4.6 TB/s), so it is near its floor;
+// the VALU (530 instructions per wave and tile) is busy 33 us and the matrix unit
+// 20 us.
 //
 // Products (float32 accumulation), Z' / dZ rows against dY / X columns:
 //   v_mfma_f32_16x16x32_bf16 on three-term bf16 splits of the float operand,
@@ -73,6 +73,29 @@ struct Plane {
         (16u << (CB - 4 + NB)) + (NB < 4 ? ((15u >> NB) << NB) : 0u);
 };
 
+// LDS of a workgroup whose tiles lie as W (Wg, Wd below).  The tile of dY / X is
+// transposed: [channel][8-token chunk] of bf16 with the chunks of a channel permuted
+// (Plane).  float32 takes three such planes (the three-term split), half of the tokens
+// at a time where there are two k steps or more.  One region per tile serves the
+// exchange and the planes, one after the other, and the teams' sums at the end.
+template <class W, typename T>
+struct Staged {
+    static constexpr int ROUNDS = sizeof(T) == 2 || W::RT == 3 ? 1 : 2;
+    static constexpr int CHUNK_BITS = W::NCHB - (ROUNDS - 1);
+    static constexpr uint32_t WORDS =
+        (sizeof(T) == 2 ? 1u : 3u) * 4u * Plane<CHUNK_BITS, W::CBITS>::UNITS;
+    static constexpr uint32_t REGION = ((W::XCH > WORDS ? W::XCH : WORDS) + 3u) & ~3u;
+    static constexpr uint32_t SUMS = W::TEAMS > 1 ? (uint32_t)(W::C * W::C) : 0u;
+    static constexpr uint32_t LDS = REGION << W::E > SUMS ? REGION << W::E : SUMS;
+};
+
+// Waves per SIMD of the product kernels, for their launch bounds.
+template <int A, int CB, typename T>
+constexpr int waves_per_simd()
+{
+    return wgrad_waves(A, CB, sizeof(T) == 2 ? DTYPE_BF16 : DTYPE_F32);
+}
+
 // How a 2^A tile of C = 2^CB channels lies in the waves for the products: lane
 // 16 q + i of the MFMA operand holds channel 16 strip + i and, per k step,
 // eight consecutive tokens of group q.
@@ -84,15 +107,15 @@ struct Plane {
 // Workgroups have at least 8 waves: 2^E tiles of fewer waves go side by side.
 template <int A, int CB>
 struct Wg {
-    static constexpr int C = 1 << CB;
+    static constexpr int CBITS = CB, C = 1 << CB;
     static constexpr int TW = A - 11;                  // wave bits of one tile
     static constexpr int SB = CB - 4;                  // strip bits
     static constexpr int SW = SB < TW ? SB : TW;
     static constexpr int SR = SB - SW;
     static constexpr int RT = VB - SR;
     static constexpr int REM = A - VB - CB;            // token bits below layout A-5
-    static constexpr int WB = TW > 3 ? TW : 3;         // wave bits of the workgroup
-    static constexpr int E = WB - TW;
+    static constexpr int WB = wgrad_wave_bits(A, CB);  // wave bits of the workgroup
+    static constexpr int E = wgrad_group_bits(A, CB);
     static constexpr uint32_t THREADS = 64u << WB;
     static constexpr uint32_t TEAMS = 1u << (WB - SW); // wave sets covering all strips
     static constexpr int NNB = C / 16;
@@ -110,35 +133,6 @@ struct Wg {
         return t + (t >> 5) + SHIFT * (t >> QB);
     }
     static constexpr uint32_t XCH = (1u << A) + (1u << (A - 5)) + SHIFT * ((1u << (A - QB)) - 1u);
-    // The tile of dY / X, transposed: [channel][8-token chunk] of bf16 with the
-    // chunks of a channel permuted (swz).  float32 takes three such planes (the
-    // three-term split), half of the tokens at a time where there are two k
-    // steps or more.
-    template <typename T>
-    static constexpr int rounds() { return sizeof(T) == 2 || RT == 3 ? 1 : 2; }
-    template <typename T>
-    static constexpr int chunk_bits() { return rounds<T>() == 1 ? NCHB : NCHB - 1; }
-    template <typename T>
-    static constexpr uint32_t plane_bytes() { return 16u * Plane<chunk_bits<T>(), CB>::UNITS; }
-    template <typename T>
-    static constexpr uint32_t xwords()
-    {
-        return (sizeof(T) == 2 ? 1u : 3u) * plane_bytes<T>() / 4u;
-    }
-    // One region serves both, one after the other.
-    template <typename T>
-    static constexpr uint32_t region()
-    {
-        const uint32_t w = XCH > xwords<T>() ? XCH : xwords<T>();
-        return (w + 3u) & ~3u;
-    }
-    template <typename T>
-    static constexpr uint32_t lds_words()
-    {
-        const uint32_t w = region<T>() << E;
-        const uint32_t cc = TEAMS > 1 ? (uint32_t)C * C : 0u;   // team sums at the end
-        return w > cc ? w : cc;
-    }
     __device__ static uint32_t base(uint32_t t)   // thread t of the tile
     {
         const uint32_t lane = t & 63u, w = t >> 6;
@@ -150,46 +144,6 @@ struct Wg {
         return ((k & ((1u << SR) - 1u)) << (4 + SW)) | ((k >> SR) << CB);
     }
 };
-
-// The high halves of two words: two bf16, the first in the low half.
-__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b)
-{
-    return __builtin_amdgcn_perm(b, a, 0x07060302u);
-}
-__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b)   // round to nearest even
-{
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
-}
-__device__ __forceinline__ float as_f32(uint32_t v) { return __builtin_bit_cast(float, v); }
-__device__ __forceinline__ uint32_t as_u32(float v) { return __builtin_bit_cast(uint32_t, v); }
-
-// Three-term bf16 split of two floats, v = hi + mid + lo.
-// EXACT: each term the leading 8 bits of what is left, so 24 bits are split
-// without residue (the terms have v's sign and shrink by 2^-7 only).
-// Otherwise each term is the nearest bf16 of what is left: |mid| <= 2^-8 |v|,
-// |lo| <= 2^-17 |v|, of either sign, which the products dropped from float32
-// times float32 rely on.
-template <bool EXACT>
-__device__ __forceinline__ void split3_pair(float z0, float z1, uint32_t &hi, uint32_t &mid,
-                                            uint32_t &lo)
-{
-    if constexpr (EXACT) {
-        const float r0 = z0 - as_f32(as_u32(z0) & 0xffff0000u);
-        const float r1 = z1 - as_f32(as_u32(z1) & 0xffff0000u);
-        hi = high_halves(as_u32(z0), as_u32(z1));
-        const float s0 = r0 - as_f32(as_u32(r0) & 0xffff0000u);
-        const float s1 = r1 - as_f32(as_u32(r1) & 0xffff0000u);
-        mid = high_halves(as_u32(r0), as_u32(r1));
-        lo = high_halves(as_u32(s0), as_u32(s1));
-    } else {
-        hi = cvt2_bf16(z0, z1);
-        const float r0 = z0 - as_f32(hi << 16), r1 = z1 - as_f32(hi & 0xffff0000u);
-        mid = cvt2_bf16(r0, r1);
-        lo = cvt2_bf16(r0 - as_f32(mid << 16), r1 - as_f32(mid & 0xffff0000u));
-    }
-}
 
 template <bool EXACT>
 __device__ __forceinline__ void split3(const float (&z)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
@@ -440,12 +394,12 @@ __device__ __forceinline__ void stage_x(float *lds, const u32x4 (&xr)[V * sizeof
                                         uint32_t t, [[maybe_unused]] int h)
 {
     using W = Wg<A, CB>;
-    constexpr int NB = W::template chunk_bits<T>();
+    constexpr int NB = Staged<W, T>::CHUNK_BITS;
     constexpr int LV = sizeof(T) == 2 ? 3 : 2;
     const uint32_t cg = t & ((1u << (CB - LV)) - 1u), u = t >> (CB - LV);
     if constexpr (sizeof(T) == 2) {
         stage_quad<NB, CB, T>(lds, xr, cg, u);
-    } else if constexpr (W::template rounds<T>() == 1) {
+    } else if constexpr (Staged<W, T>::ROUNDS == 1) {
         // u gets its missing bit back (RT = 3: bit 0)
 #pragma unroll
         for (uint32_t hh = 0; hh < 2; ++hh)
@@ -460,7 +414,7 @@ __device__ __forceinline__ void stage_x(float *lds, const u32x4 (&xr)[V * sizeof
 // as part[p][b][a], a the workspace's channel (still a channel frequency), b
 // the channel of dY / X.
 template <int A, int HB, int R, typename T, int CB>
-__global__ void __launch_bounds__((Wg<A, CB>::THREADS), (Wg<A, CB>::NS == 1 ? 4 : 2))
+__global__ void __launch_bounds__((Wg<A, CB>::THREADS), (waves_per_simd<A, CB, T>()))
 wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                    const float *__restrict__ wsd, const T *__restrict__ x,
                    float *__restrict__ part, uint32_t *__restrict__ seen_words, uint32_t nvalid,
@@ -469,7 +423,7 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
     using W = Wg<A, CB>;
     using Run = RunMap<HB, R>;
     constexpr int C = W::C, NNB = W::NNB, NS = W::NS;
-    __shared__ __attribute__((aligned(16))) float lds[W::template lds_words<T>()];
+    __shared__ __attribute__((aligned(16))) float lds[Staged<W, T>::LDS];
     const uint32_t tau = threadIdx.x;
     const uint32_t t = tau & ((1u << (A - VB)) - 1u);   // thread of the tile
     const uint32_t lane = tau & 63u;
@@ -477,7 +431,7 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tau >> 6);
     const uint32_t sub = wave >> W::TW;
     const uint32_t tw = (wave & ((1u << W::TW) - 1u)) >> W::SW;
-    float *const region = lds + sub * W::template region<T>();
+    float *const region = lds + sub * Staged<W, T>::REGION;
     const bool second = blockIdx.x >= nwg;
     const uint32_t p = blockIdx.x - (second ? nwg : 0u);
     const float *ws = second ? wsd : wsx;
@@ -503,8 +457,8 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
 
     // The next group's dY / X (bf16) is loaded once this group's is staged and
     // its workspace registers after the products, ahead of the next exchange.
-    constexpr int ROUNDS = W::template rounds<T>(), STEPS = 1 << (W::RT - 3);
-    constexpr int NB = W::template chunk_bits<T>();
+    constexpr int ROUNDS = Staged<W, T>::ROUNDS, STEPS = 1 << (W::RT - 3);
+    constexpr int NB = Staged<W, T>::CHUNK_BITS;
     [[maybe_unused]] Seen seen;   // float32
     float v[V];
     u32x4 xr[V * sizeof(T) / 16];
@@ -601,7 +555,7 @@ wgrad_tiles_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
 // before the operand addresses and splits were cut down).
 template <int A, int CB>
 struct Wd {
-    static constexpr int C = 1 << CB;
+    static constexpr int CBITS = CB, C = 1 << CB;
     static constexpr int TW = A - 11;
     static constexpr int SB = CB - 4;
     static constexpr int SW = SB < TW ? SB : TW;       // wave bits of a tile
@@ -609,44 +563,21 @@ struct Wd {
     static constexpr int LB = A - 6 - SW;              // log2 of values per lane
     static constexpr int VV = 1 << LB;
     static constexpr int RT = LB - SR;
-    static constexpr int WB = LB > VB && SW < 3 ? 2 : 3;   // wave bits of the workgroup
-    static constexpr int E = WB - SW;
+    static constexpr int WB = wgrad_wave_bits(A, CB);  // wave bits of the workgroup
+    static constexpr int E = wgrad_group_bits(A, CB);
     static constexpr uint32_t THREADS = 64u << WB;
     static constexpr uint32_t TEAMS = 1u << E;
     static constexpr int NNB = C / 16;
     static constexpr int NS = 1 << SR;
     static constexpr int NCHB = A - CB - 3;
     static_assert(A - CB == RT + 2, "every token bit in a lane or its registers");
-    // waves per SIMD the registers are held to: two 8-wave workgroups per CU
-    // with one strip (one with float32 at C = 128, whose operands take more),
-    // three 4-wave ones with 64 values per lane
-    template <typename T>
-    static constexpr int waves()
-    {
-        return LB > VB ? (WB == 2 ? 3 : 2) : (NS == 1 && !(sizeof(T) == 4 && CB == 7) ? 4 : 2);
-    }
-
-    template <typename T>
-    static constexpr int rounds() { return sizeof(T) == 2 || RT == 3 ? 1 : 2; }
-    template <typename T>
-    static constexpr int chunk_bits() { return rounds<T>() == 1 ? NCHB : NCHB - 1; }
-    template <typename T>
-    static constexpr uint32_t plane_bytes() { return 16u * Plane<chunk_bits<T>(), CB>::UNITS; }
-    template <typename T>
-    static constexpr uint32_t region()   // words of one tile
-    {
-        return (sizeof(T) == 2 ? 1u : 3u) * plane_bytes<T>() / 4u;
-    }
-    template <typename T>
-    static constexpr uint32_t lds_words()
-    {
-        const uint32_t w = region<T>() << E;
-        const uint32_t cc = TEAMS > 1 ? (uint32_t)C * C : 0u;
-        return w > cc ? w : cc;
-    }
+    static constexpr uint32_t XCH = 0;   // no exchange
     // 16-byte pieces of dY / X a thread stages per round
     template <typename T>
-    static constexpr int pieces() { return VV * (int)sizeof(T) / 16 / rounds<T>(); }
+    static constexpr int pieces()
+    {
+        return VV * (int)sizeof(T) / 16 / Staged<Wd, T>::ROUNDS;
+    }
 
     __device__ static uint32_t base(uint32_t lane, uint32_t strips)
     {
@@ -706,7 +637,7 @@ template <int A, int CB, typename T>
 struct StageX {
     using W = Wd<A, CB>;
     static constexpr int LV = sizeof(T) == 2 ? 3 : 2;
-    static constexpr int ROUNDS = W::template rounds<T>();
+    static constexpr int ROUNDS = Staged<W, T>::ROUNDS;
     static constexpr int NP = W::template pieces<T>();
     static constexpr int NM = NP / 4;
     static constexpr uint32_t QS = (64u << W::SW) >> (CB - LV);   // quads per pass of the threads
@@ -754,12 +685,12 @@ struct StageX {
         const uint32_t cg = t & ((1u << (CB - LV)) - 1u), q0 = t >> (CB - LV);
 #pragma unroll
         for (int m = 0; m < NM; ++m)
-            stage_quad<W::template chunk_bits<T>(), CB, T>(lds, xr + 4 * m, cg, q0 + m * QS);
+            stage_quad<Staged<W, T>::CHUNK_BITS, CB, T>(lds, xr + 4 * m, cg, q0 + m * QS);
     }
 };
 
 template <int A, int HB, int R, typename T, int CB>
-__global__ void __launch_bounds__((Wd<A, CB>::THREADS), (Wd<A, CB>::template waves<T>()))
+__global__ void __launch_bounds__((Wd<A, CB>::THREADS), (waves_per_simd<A, CB, T>()))
 wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
                     const float *__restrict__ wsd, const T *__restrict__ x,
                     float *__restrict__ part, uint32_t *__restrict__ seen_words, uint32_t nvalid,
@@ -769,14 +700,14 @@ wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
     using X = StageX<A, CB, T>;
     using Run = RunMap<HB, R>;
     constexpr int C = W::C, NNB = W::NNB, NS = W::NS, VV = W::VV;
-    __shared__ __attribute__((aligned(16))) float lds[W::template lds_words<T>()];
+    __shared__ __attribute__((aligned(16))) float lds[Staged<W, T>::LDS];
     const uint32_t tau = threadIdx.x;
     const uint32_t t = tau & ((64u << W::SW) - 1u);   // thread of the tile
     const uint32_t lane = tau & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tau >> 6);
     const uint32_t team = wave >> W::SW;              // tile of the group
     const uint32_t strip0 = wave & ((1u << W::SW) - 1u);
-    float *const region = lds + team * W::template region<T>();
+    float *const region = lds + team * Staged<W, T>::REGION;
     const bool second = blockIdx.x >= nwg;
     const uint32_t p = blockIdx.x - (second ? nwg : 0u);
     const float *ws = second ? wsd : wsx;
@@ -800,7 +731,7 @@ wgrad_direct_kernel(const float *__restrict__ wsx, const T *__restrict__ dy,
             acc[s][n] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
 
     constexpr int ROUNDS = X::ROUNDS, STEPS = 1 << (W::RT - 3);
-    constexpr int NB = W::template chunk_bits<T>();
+    constexpr int NB = Staged<W, T>::CHUNK_BITS;
     [[maybe_unused]] Seen seen;   // float32
     float v[VV];
     u32x4 xr[X::NP];
