@@ -1311,22 +1311,27 @@ __device__ __forceinline__ void module_outer_fwd_tile(float *lds,
     const uint32_t valid = tile_valid<A>(nvalid, hi);
     if (hi >= middle_rows(nvalid, A, HB))
         return;   // wholly padding: the middle pass leaves it out (uniform per workgroup)
-    const T *const tile = x + b * nvalid + ((size_t)hi << A);
     XFrag<T, CB> f;
     // The weights come from L2, x from memory: issued first, they are in LDS
     // by the time x arrives (with project_in's reads ahead, this kernel on 4 x
     // 65536 x 128 bf16: 48.1 -> 41.9 us).
     if constexpr (PACKED) {
-        load_x_frags<T, CB>(f, tile, valid, tau);
+        load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, tau);
         stage_weights<L::CHUNKS, L::NT>(lds, w_in, tau);
     } else {
         stage_raw<T, CB, true, L::NT>(lds, flags, w_in, trans, tau, 0, [&] {
-            load_x_frags<T, CB>(f, tile, valid, tau);
+            // The compiler moved the last weight load behind x's, so that staging it
+            // waited for x (two-operand pass of 4 x 65536 x 128 bf16: 90 us, 85 in
+            // order).  Not in the fused kernel, where it costs: 512 slices of 64 x 128
+            // 11.9 -> 12.7 us.
+            __builtin_amdgcn_sched_barrier(0);
+            load_x_frags<T, CB>(f, x + b * nvalid + ((size_t)hi << A), valid, tau);
         });
     }
     float v[V];
     if constexpr (Proj<T, CB>::X3) {
-        project_in_x3<CB, L::NT>(v, f, lds, flags, w_in, trans, tile, valid, tau);
+        project_in_x3<CB, L::NT>(v, f, lds, flags, w_in, trans,
+                                 x + b * nvalid + ((size_t)hi << A), valid, tau);
     } else {
         __syncthreads();
         project_in<T, CB>(v, f, lds, tau);
