@@ -200,7 +200,7 @@ static PyMethodDef methods[] = {
     {NULL, NULL, 0, NULL}};
 
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_whtmix_call",
-                                    "CPython-level calls of the WHTMix forward entry points",
+                                    "CPython-level calls of the WHTMix entry points",
                                     -1, methods, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__whtmix_call(void) { return PyModule_Create(&module); }
